@@ -81,7 +81,8 @@ hipError_t noalloc_reduce(int device, int num_cu, int op, int dt, const void *in
     if (grid_out)
         *grid_out = g;
     uint32_t *cnt = (uint32_t *)p;
-    hipError_t e = launch_clear_u32(cnt, 1, s);
+    // one workgroup alone uses no counter
+    hipError_t e = g > 1 ? launch_clear_u32(cnt, 1, s) : hipSuccess;
     if (e != hipSuccess)
         return e;
     return launch_reduce_into(op, dt, in, n, out, p + kNaLine, cnt, g, s);
