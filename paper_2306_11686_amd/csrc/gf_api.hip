@@ -1528,6 +1528,93 @@ struct InstShape {
     double weight;
 };
 
+// ---- fused sweeps (gf_fused.h) ------------------------------------------
+// A program whose body is one 2D stencil region, scalar steps and, after the
+// region, the SWAP of the region's two grids can run several sweeps per pass
+// over the grid. Returns the region's step index, or -1. The prologue may
+// hold scalar steps; a host call anywhere could read or write the grids
+// between two sweeps, and nowait promises nothing about the next sweep.
+int fusable_region(const DProg &p)
+{
+    int rs = -1, swap = -1;
+    for (int i = 0; i < p.n_steps; ++i) {
+        const DStep &s = p.steps[i];
+        if (s.kind == GF_S_CALL || (is_region(s.kind) && (i < p.n_pro || rs >= 0)))
+            return -1;
+        if (is_region(s.kind))
+            rs = i;
+        if (s.kind == GF_S_SWAP && i >= p.n_pro) {
+            if (swap >= 0 || rs < 0)
+                return -1;
+            swap = i;
+        }
+    }
+    if (rs < 0 || swap < 0 || p.iters < kFusedMinIters)
+        return -1;
+    const DStep &r = p.steps[rs], &w = p.steps[swap];
+    if (r.kind != GF_R_JACOBI2D || (r.flags & GF_STEP_NOWAIT) || r.arr[0] == r.arr[1])
+        return -1;
+    const bool same = (w.arr[0] == r.arr[0] && w.arr[1] == r.arr[1]) || (w.arr[0] == r.arr[1] && w.arr[1] == r.arr[0]);
+    return same ? rs : -1;
+}
+
+// Partial values the largest pass over an n-sided grid writes.
+int64_t fused_partials(int kind, int64_t n)
+{
+    int64_t most = 0;
+    for (int m : {1, 3, kFusedMax})
+        most = std::max<int64_t>(most, m * fused_items(kind, n, m));
+    return most;
+}
+
+// The grids of an instance and the arrays its body records into do not
+// overlap (a sweep left in registers is seen by nobody else), and the
+// partial sums of a pass fit.
+bool fusable_instance(const gf_ctx *ctx, const DProg &p, int rs, const gf_instance &in)
+{
+    const DStep &r = p.steps[rs];
+    const uint64_t n = (uint64_t)in.ip[r.np];
+    const uint64_t bytes = n * n * 8;
+    // slots as the prologue's swaps leave them
+    void *arr[GF_MAX_ARRAYS];
+    std::memcpy(arr, in.arr, sizeof arr);
+    for (int i = 0; i < p.n_pro; ++i)
+        if (p.steps[i].kind == GF_S_SWAP)
+            std::swap(arr[p.steps[i].arr[0]], arr[p.steps[i].arr[1]]);
+    auto apart = [](const void *a, uint64_t na, const void *b, uint64_t nb) {
+        const uint64_t x = (uint64_t)(uintptr_t)a, y = (uint64_t)(uintptr_t)b;
+        return x + na <= y || y + nb <= x;
+    };
+    const void *u = arr[r.arr[0]], *w = arr[r.arr[1]];
+    if (!apart(u, bytes, w, bytes))
+        return false;
+    for (int i = p.n_pro; i < p.n_steps; ++i)
+        if (p.steps[i].kind == GF_S_RECORD) {
+            const void *rec = arr[p.steps[i].arr[0]];
+            const uint64_t nb = (uint64_t)p.iters * 8;
+            if (!apart(rec, nb, u, bytes) || !apart(rec, nb, w, bytes))
+                return false;
+        }
+    return fused_partials(r.kind, (int64_t)n) <= ctx->scr.partials_cap;
+}
+
+// Workgroup items of a pass (a wavefront takes one item at a time).
+int64_t fused_wg_items(int kind, int64_t n, int wg_size)
+{
+    const int64_t waves = wg_size / kWave;
+    return std::max<int64_t>(1, (fused_items(kind, n, n < kFusedMinSide ? 1 : kFusedMax) + waves - 1) / waves);
+}
+
+// Grid barriers of a fused run: one per pass, none after a last pass
+// without a reduction.
+int64_t fused_barriers(const DProg &p, int rs, int64_t n)
+{
+    int64_t passes = 0;
+    for (int32_t left = p.iters; left > 0; left -= fused_sweeps(n, left))
+        ++passes;
+    return p.steps[rs].red_op == GF_OP_NONE ? passes - 1 : passes;
+}
+
 // Workgroups for the instances `ids` out of `budget` (each >= 1 and at most
 // its item count). A group of g_i workgroups deals its items_i tiles
 // round-robin, so its time per region is ceil(items_i / g_i) tiles at a cost
@@ -1645,7 +1732,7 @@ int plan_batch(int n, const std::vector<int64_t> &items, const std::vector<doubl
 // rewritten only after the previous copy has executed.
 gf_status run_batched(gf_ctx *ctx, const DProg &p, const gf_instance *inst, int n_inst, const Tiling &t,
                       const gf_launch *launch, int cap, gf_run_stats *stats, hipStream_t stream,
-                      const InstShape *shape)
+                      const InstShape *shape, int fused_rs)
 {
     if (program_is_hist_family(p))
         return fail(ctx, GF_EUNSUPPORTED, "batched persistent runs of histogram programs are not supported");
@@ -1665,11 +1752,18 @@ gf_status run_batched(gf_ctx *ctx, const DProg &p, const gf_instance *inst, int 
             ti.tile_y = ty[i] = shape[i].tile_y;
         items[i] = std::max<int64_t>(1, max_items(p, inst[i], ti));
         int64_t r = 0;
-        for (int k = 0; k < p.n_steps; ++k)
+        if (fused_rs >= 0) {
+            const DStep &st = p.steps[fused_rs];
+            items[i] = fused_wg_items(st.kind, inst[i].ip[st.np], t.wg_size);
+            r = fused_partials(st.kind, inst[i].ip[st.np]);
+        }
+        for (int k = 0; k < p.n_steps && fused_rs < 0; ++k)
             if (is_region(p.steps[k].kind) && p.steps[k].red_op != GF_OP_NONE)
                 r = std::max<int64_t>(r, region_items(p.steps[k], inst[i].ip[p.steps[k].np], ti));
         red[i] = r;
         w[i] = (shape && shape[i].weight > 0.0) ? shape[i].weight : (double)items[i];
+        if (fused_rs >= 0)
+            w[i] *= fused_item_cost(p.steps[fused_rs].kind, inst[i].ip[p.steps[fused_rs].np]);
     }
     // pack onto XCDs and size the groups
     std::vector<int> g(n_inst, 1), xcd_of(n_inst, -1);
@@ -1752,7 +1846,7 @@ gf_status run_batched(gf_ctx *ctx, const DProg &p, const gf_instance *inst, int 
     std::memset(&dummy, 0, sizeof dummy);
     ctx->scr.epoch += 1;
     ctx->batch_check_epoch = aligned ? ctx->scr.epoch : 0;
-    e = launch_persistent(p, dummy, t, wg, ctx->scr, ring_of(ctx), stream, &bt);
+    e = launch_persistent(p, dummy, t, wg, ctx->scr, ring_of(ctx), stream, &bt, fused_rs >= 0);
     if (e != hipSuccess)
         return hipfail(ctx, e, "batched persistent launch");
     if (stats) {
@@ -1763,7 +1857,13 @@ gf_status run_batched(gf_ctx *ctx, const DProg &p, const gf_instance *inst, int 
         for (int k = p.n_pro; k < p.n_steps; ++k)
             nb += is_region(p.steps[k].kind);
         stats->regions = n_inst * nb * p.iters;
-        stats->barriers = (int32_t)p.barriers;
+        int64_t bars = p.barriers;
+        if (fused_rs >= 0) {
+            bars = 0;
+            for (int i = 0; i < n_inst; ++i)
+                bars = std::max(bars, fused_barriers(p, fused_rs, inst[i].ip[p.steps[fused_rs].np]));
+        }
+        stats->barriers = (int32_t)bars;
     }
     return GF_OK;
 }
@@ -1977,16 +2077,52 @@ static gf_status region_run(gf_ctx *ctx, const gf_program *prog, const gf_instan
         const int cap = std::min(4096, persistent_capacity(p, t, ctx->num_cu));
         if (cap <= 0)
             return fail(ctx, GF_EHIP, "occupancy query failed");
+        // Several sweeps per pass where the caller leaves the tile to the
+        // library; a given tile is run as given, one sweep per pass. A grid
+        // size the plain kernel can hold and the fused one cannot, and a
+        // batch with more instances than its capacity, run plainly too.
+        int fused_rs = -1, fcap = 0;
+        if (!shape && (!launch || (!launch->wg_size && !launch->tile_y && !launch->tile_z && !launch->items &&
+                                   !launch->prefetch)))
+            fused_rs = fusable_region(p);
+        for (int i = 0; i < n_inst && fused_rs >= 0; ++i)
+            if (!fusable_instance(ctx, p, fused_rs, inst[i]))
+                fused_rs = -1;
+        if (fused_rs >= 0) {
+            Tiling ft = t;
+            ft.wg_size = kFusedWg;
+            fcap = std::min(4096, persistent_capacity(p, ft, ctx->num_cu, true));
+            if (fcap <= 0 || n_inst > fcap || (launch && launch->num_wg > fcap && n_inst == 1))
+                fused_rs = -1;
+        }
+        if (n_inst > 1 && fused_rs >= 0) {
+            int64_t part = 0;
+            for (int i = 0; i < n_inst; ++i)
+                part += fused_partials(p.steps[fused_rs].kind, inst[i].ip[p.steps[fused_rs].np]);
+            if (part > ctx->scr.partials_cap)
+                fused_rs = -1;
+        }
+        if (fused_rs >= 0)
+            t.wg_size = kFusedWg;
         if (n_inst > 1)
-            return run_batched(ctx, p, inst, n_inst, t, launch, cap, stats, stream, shape);
+            return run_batched(ctx, p, inst, n_inst, t, launch, fused_rs >= 0 ? fcap : cap, stats, stream, shape,
+                               fused_rs);
         for (int i = 0; i < n_inst; ++i) {
             // default grid: at most two workgroups per CU (the grid barrier's
             // cost grows with the number of members), sized so that every
             // workgroup gets the same number of work items (balanced rounds)
-            const int64_t gmax = std::min<int64_t>(cap, 2 * (int64_t)ctx->num_cu);
-            const int64_t items = max_items(p, inst[i], t);
+            int64_t gmax = std::min<int64_t>(cap, 2 * (int64_t)ctx->num_cu);
+            int64_t items = max_items(p, inst[i], t);
+            if (fused_rs >= 0) {
+                const DStep &st = p.steps[fused_rs];
+                items = fused_wg_items(st.kind, inst[i].ip[st.np], t.wg_size);
+                gmax = fcap;
+            }
             const int64_t rounds = (items + gmax - 1) / gmax;
             int grid = (int)((items + rounds - 1) / rounds);
+            // one workgroup more for the serial steps, without work items
+            if (fused_rs >= 0 && grid < fcap)
+                ++grid;
             if (launch && launch->num_wg > 0) {
                 if (launch->num_wg > cap)
                     return fail(ctx, GF_EINVAL, "num_wg %d exceeds the co-resident capacity %d", launch->num_wg, cap);
@@ -2010,9 +2146,11 @@ static gf_status region_run(gf_ctx *ctx, const gf_program *prog, const gf_instan
             // the XCD barrier's per-launch registration costs a tree barrier:
             // programs with few barriers keep the tree barrier
             Scratch scr = ctx->scr;
-            if (p.barriers < kXcdBarrierMinBarriers)
+            const int64_t bars =
+                fused_rs >= 0 ? fused_barriers(p, fused_rs, inst[i].ip[p.steps[fused_rs].np]) : p.barriers;
+            if (bars < kXcdBarrierMinBarriers)
                 scr.barrier_kind = kBarrierTree;
-            hipError_t e = launch_persistent(p, di, t, grid, scr, ring_of(ctx), stream);
+            hipError_t e = launch_persistent(p, di, t, grid, scr, ring_of(ctx), stream, nullptr, fused_rs >= 0);
             if (e != hipSuccess)
                 return hipfail(ctx, e, "persistent launch");
             if (stats) {
@@ -2026,7 +2164,7 @@ static gf_status region_run(gf_ctx *ctx, const gf_program *prog, const gf_instan
                 for (int k = p.n_pro; k < p.n_steps; ++k)
                     nbody += is_region(p.steps[k].kind);
                 stats->regions += nreg + nbody * p.iters;
-                stats->barriers = (int32_t)p.barriers;
+                stats->barriers = (int32_t)bars;
             }
         }
         return GF_OK;

@@ -1,0 +1,315 @@
+// gf_fused.h -- several sweeps of a stencil program per pass over the grid
+// (temporal blocking) for the persistent kernel. Included only by
+// gf_kernels.hip, after its wavefront shifts.
+//
+// A program whose body is one Jacobi region, scalar steps and the SWAP of the
+// region's two grids is a chain of sweeps u^0, u^1, .., u^S in which sweep k
+// reads buffer k mod 2 and writes the other. Only u^S and u^(S-1) are left in
+// memory at the end, so a pass may read u^k, compute M sweeps in registers
+// and write u^(k+M) alone: one read and one write of the grid, one grid
+// barrier and one hand-over of the reduction per M sweeps instead of per
+// sweep. M is odd, so u^(k+M) lands in the buffer the sequence would have
+// put it in, and the last sweep is a pass of its own, so that u^(S-1) stays
+// in the other buffer. Every point goes through the same operations in the
+// same order as sweep by sweep (bit-exact), and every sweep's reduction is
+// taken over the same points.
+//
+// Sweep by sweep the 2D stencil is bound by HBM on large grids and batches,
+// and by the barrier, the reduction and the serial steps on small grids.
+// Fused it moves a seventh of the bytes and is bound by FP64 issue (about 20
+// instructions per pair of points and sweep) plus the steps at the ends of
+// the segments. Measured, sweep by sweep and fused: 256 uneven instances, 50
+// sweeps, 28.4 and 7.3 ms; 256^2 with printf, 100 sweeps, 1,246 and 312 us.
+//
+// Points of the outer layer are never written by a sweep, so u^s and u^(s-2)
+// agree there, in whichever buffers they are: a stage takes the values of the
+// outer layer from two stages earlier (the first stage from the destination
+// buffer), also where the two buffers' outer layers differ.
+#pragma once
+
+namespace gf {
+
+// 16-byte accesses of two columns; rows of an odd-sided grid start on 8-byte
+// boundaries, which gfx950's dwordx4 accesses take.
+typedef double gf_d2u __attribute__((ext_vector_type(2), aligned(8)));
+
+// A row's address as an opaque scalar, so that accesses use it as their
+// scalar base with the lane's fixed 32-bit offset (left alone, the compiler
+// keeps a 64-bit address per lane for every access of the unrolled march).
+template <typename V, typename T>
+__device__ __forceinline__ GF_GLOBAL V *row_at(GF_GLOBAL T *p, uint32_t byte)
+{
+    asm("" : "+s"(p));
+    return (GF_GLOBAL V *)((GF_GLOBAL const char *)p + byte);
+}
+
+// The neighbouring lanes' values; the wavefront's end lanes get 0 (their
+// results are never used).
+__device__ __forceinline__ double lane_left(double v)
+{
+    const int lo = __builtin_amdgcn_mov_dpp(__double2loint(v), 0x138, 0xf, 0xf, true);
+    const int hi = __builtin_amdgcn_mov_dpp(__double2hiint(v), 0x138, 0xf, 0xf, true);
+    return __hiloint2double(hi, lo);
+}
+__device__ __forceinline__ double lane_right(double v)
+{
+    const int lo = __builtin_amdgcn_mov_dpp(__double2loint(v), 0x130, 0xf, 0xf, true);
+    const int hi = __builtin_amdgcn_mov_dpp(__double2hiint(v), 0x130, 0xf, 0xf, true);
+    return __hiloint2double(hi, lo);
+}
+
+// Values of a pass's reductions over one work item or all of them.
+template <int OP, int M>
+__device__ __forceinline__ void wave_reduce_m(double (&v)[M])
+{
+#pragma unroll
+    for (int off = kWave / 2; off > 0; off >>= 1)
+#pragma unroll
+        for (int s = 0; s < M; ++s)
+            v[s] = RedOp<OP>::apply(v[s], __shfl_xor(v[s], off, kWave));
+}
+
+// M reductions at once over p[s * n + i], i < n, in a fixed order (strided
+// per thread, then the wavefronts in order). lds: M doubles per wavefront.
+// out[s] (LDS) holds the values when the workgroup returns.
+template <int OP, int M>
+__device__ __forceinline__ void reduce_partials_m(const double *p, int64_t n, double *lds, double *out)
+{
+    double acc[M];
+#pragma unroll
+    for (int s = 0; s < M; ++s)
+        acc[s] = RedOp<OP>::identity();
+    for (int64_t i = threadIdx.x; i < n; i += blockDim.x)
+#pragma unroll
+        for (int s = 0; s < M; ++s)
+            acc[s] = RedOp<OP>::apply(acc[s], p[s * n + i]);
+    wave_reduce_m<OP, M>(acc);
+    const int wid = threadIdx.x / kWave, nw = blockDim.x / kWave;
+    if ((threadIdx.x & (kWave - 1)) == 0)
+#pragma unroll
+        for (int s = 0; s < M; ++s)
+            lds[wid * M + s] = acc[s];
+    __syncthreads();
+    if (threadIdx.x < M) {
+        double v = lds[threadIdx.x];
+        for (int w = 1; w < nw; ++w)
+            v = RedOp<OP>::apply(v, lds[w * M + threadIdx.x]);
+        out[threadIdx.x] = v;
+    }
+    __syncthreads();
+}
+
+// ---------------------------------------------------------------------------
+// 2D. A work item belongs to one wavefront: 128 adjacent columns (two per
+// lane), a segment of `rows` output rows. The wavefront marches down the
+// rows; when row y arrives, stage s (s = 1 .. M) computes row y - s of sweep
+// k + s from the rows y-s-1, y-s, y-s+1 of stage s-1, all in registers, with
+// the x-neighbours taken from the adjacent lanes. Columns next to the
+// wavefront's ends go wrong one per stage, so items overlap by M columns on
+// each side, and by M rows above and below; wavefronts share nothing.
+// ---------------------------------------------------------------------------
+
+constexpr int kJ2fAhead = 3;              // rows in flight
+constexpr int kJ2fRing = kJ2fAhead + 3;   // stage 0's rows; a multiple of 3, the other stages' period
+
+struct J2fGeom {
+    int32_t chunks;   // items across a row
+    int32_t width;    // output columns per item (even)
+    int32_t rows;     // output rows per item
+    int64_t segs;     // items down the grid
+    int64_t items;
+};
+
+__host__ __device__ inline J2fGeom j2f_geom(int64_t n, int M)
+{
+    J2fGeom g;
+    const int64_t halo = (M + 1) & ~1;   // whole lanes lost on an inner side
+    const int64_t cols = (n + 1) & ~(int64_t)1;
+    int64_t c = 1;
+    if (cols > 128) {
+        c = 2;
+        if (cols > 2 * (128 - halo))
+            c = (cols + (128 - 2 * halo) - 1) / (128 - 2 * halo);
+    }
+    g.chunks = (int32_t)c;
+    g.width = (int32_t)(((cols + c - 1) / c + 1) & ~(int64_t)1);
+    // long segments repeat less at their ends (M rows of the neighbours on
+    // each side), short ones give a small grid more wavefronts
+    const int64_t r = n / 32;
+    g.rows = (int32_t)(r < 8 ? 8 : (r > 64 ? 64 : r));
+    g.segs = (n - 2 + g.rows - 1) / g.rows;
+    g.items = g.chunks * g.segs;
+    return g;
+}
+
+// Output rows [y0, y1) of u^(k+M) from u = u^k; w holds the other buffer
+// (outer layer of the odd stages, output). x0: the wavefront's first column
+// (even), [xa, xb): its output columns (even bounds). acc[s] (s < M): the
+// lane's sum of squared differences of sweep k + s + 1 over its output
+// points. XE: the 128 columns include column 0 or n-1.
+// Every load is issued unconditionally, rows past the last one read again:
+// with loads under a branch the compiler cannot count what is in flight and
+// waits for all of it at every row (the batch of 256 instances: a fifth
+// slower).
+template <int M, bool XE>
+__device__ __forceinline__ void j2f_tile(GF_GLOBAL const double *__restrict__ u, GF_GLOBAL double *w, int32_t n,
+                                         int32_t x0, int32_t xa, int32_t xb, int32_t y0, int32_t y1,
+                                         double (&acc)[M])
+{
+    const int lane = threadIdx.x & (kWave - 1);
+    const int32_t x = x0 + 2 * lane;
+    // lanes past the row's end load its last pair and are never used
+    const uint32_t xs = 8u * (uint32_t)(XE && x > n - 2 ? n - 2 : x);
+    const bool lone = XE && x == n - 1;               // odd n: column n-1 alone, second of its pair
+    const bool bx = XE && (x == 0 || x == n - 1);     // first value is of the outer layer
+    const bool by = XE && x + 1 == n - 1;             // second value is
+    const bool zy = by || lone;                       // second value takes no part in the sum
+    const bool mine = x >= xa && x < xb && x < n;
+    const uint32_t xe = 8u * (uint32_t)(bx ? x : (by ? x + 1 : 0));  // the lane's outer column
+    const int32_t ya = y0 - M > 0 ? y0 - M : 0;                      // first row read
+    const int32_t yb = y1 - 1 + M < n - 1 ? y1 - 1 + M : n - 1;      // last row read
+    const int32_t ye = y1 - 1 + M;                                   // last step
+    const int64_t pitch = n;
+    auto ld = [&](int32_t y) -> gf_d2 {
+        const gf_d2 v = *row_at<const gf_d2u>(u + (y < yb ? y : yb) * pitch, xs);
+        if constexpr (XE)
+            return gf_d2{lone ? v.y : v.x, v.y};
+        return v;
+    };
+    // the lane's outer column in the other buffer, row y
+    auto ldb = [&](int32_t y) -> double { return *row_at<const double>(w + (y < yb ? y : yb) * pitch, xe); };
+    auto ldrow = [&](int32_t y) -> gf_d2 {  // an outer row of the other buffer
+        const gf_d2 v = *row_at<const gf_d2u>(w + y * pitch, xs);
+        return gf_d2{lone ? v.y : v.x, v.y};
+    };
+    gf_d2 ring[kJ2fRing];        // stage 0: rows of u^k, row ya + j in slot j mod the ring
+    double bc[XE ? kJ2fRing : 1];
+    gf_d2 st[M > 1 ? M - 1 : 1][3];  // stage s = 1 .. M-1: its last three rows
+    const gf_d2 zero2 = {0.0, 0.0};
+#pragma unroll
+    for (int s = 0; s < M - 1; ++s)
+#pragma unroll
+        for (int j = 0; j < 3; ++j)
+            st[s][j] = zero2;
+    // the outer row in the other buffer: the first row, later the last one
+    // (used by segments that reach it)
+    gf_d2 eb = ldrow(0);
+#pragma unroll
+    for (int j = 0; j < kJ2fRing; ++j) {
+        ring[j] = j < kJ2fAhead ? ld(ya + j) : zero2;
+        if constexpr (XE)
+            bc[j] = j < kJ2fAhead ? ldb(ya + j) : 0.0;
+    }
+    // One step: row y arrives in slot k. The checks on the stages' rows are
+    // scalar; a second version of the steps without them (for the middle of a
+    // segment) doubled the code and, merged with this one in the loop, spilled.
+    auto step = [&](auto kc, int32_t y) {
+        constexpr int k = decltype(kc)::value;
+        ring[(k + kJ2fAhead) % kJ2fRing] = ld(y + kJ2fAhead);
+        if constexpr (XE)
+            bc[(k + kJ2fAhead) % kJ2fRing] = ldb(y + kJ2fAhead);
+#pragma unroll
+        for (int s = 1; s <= M; ++s) {
+            const int32_t r = y - s;
+            // stage s-1's rows r-1, r, r+1
+            const gf_d2 up = s == 1 ? ring[(k + kJ2fRing - 2) % kJ2fRing] : st[s >= 2 ? s - 2 : 0][(k + 1) % 3];
+            const gf_d2 c = s == 1 ? ring[(k + kJ2fRing - 1) % kJ2fRing] : st[s >= 2 ? s - 2 : 0][(k + 2) % 3];
+            const gf_d2 dn = s == 1 ? ring[k] : st[s >= 2 ? s - 2 : 0][k % 3];
+            gf_d2 out;
+            const int32_t lo = y0 - (M - s) > 0 ? y0 - (M - s) : 0;
+            const int32_t hi = y1 - 1 + (M - s) < n - 1 ? y1 - 1 + (M - s) : n - 1;
+            if (r < lo || r > hi)
+                continue;
+            gf_d2 prev = zero2;  // the same row two stages earlier
+            if (s >= 3)
+                prev = st[s >= 3 ? s - 3 : 0][(k + 1) % 3];
+            else if (s == 2)
+                prev = ring[(k + kJ2fRing - 2) % kJ2fRing];
+            if (r == 0 || r == n - 1) {
+                out = s == 1 ? eb : prev;
+            } else {
+                const double xl = lane_left(c.y);
+                const double xr = lane_right(c.x);
+                out.x = ((xl + c.y) + (up.x + dn.x)) * 0.25;
+                out.y = ((c.x + xr) + (up.y + dn.y)) * 0.25;
+                if constexpr (XE) {
+                    const double b = s == 1 ? bc[(k + kJ2fRing - 1) % kJ2fRing] : 0.0;
+                    out.x = bx ? (s == 1 ? b : prev.x) : out.x;
+                    out.y = by ? (s == 1 ? b : prev.y) : out.y;
+                }
+                if (r >= y0 && r < y1) {
+                    double dx = out.x - c.x, dy = out.y - c.y;
+                    if constexpr (XE) {
+                        dx = bx ? 0.0 : dx;
+                        dy = zy ? 0.0 : dy;
+                    }
+                    acc[s - 1] = __builtin_fma(dx, dx, acc[s - 1]);
+                    acc[s - 1] = __builtin_fma(dy, dy, acc[s - 1]);
+                    // accumulate here: sunk to the end of the unrolled steps,
+                    // the sums keep every step's rows in registers
+                    asm volatile("" : "+v"(acc[s - 1]));
+                    if (s == M && mine) {
+                        GF_GLOBAL double *o = row_at<double>(w + r * pitch, xs);
+                        if (!XE || (!bx && !by))
+                            __builtin_nontemporal_store(out, (GF_GLOBAL gf_d2u *)o);
+                        else if (!bx)
+                            __builtin_nontemporal_store(out.x, o);
+                        else if (!zy)
+                            __builtin_nontemporal_store(out.y, o + 1);
+                    }
+                }
+            }
+            if (s < M)
+                st[s < M ? s - 1 : 0][k % 3] = out;
+        }
+    };
+    for (int32_t y = ya; y <= ye; y += kJ2fRing) {
+        // past the first row at every stage: from here the outer row is the
+        // last one (the first stage reaches it at step n)
+        if (y > M)
+            eb = ldrow(n - 1);
+        step(std::integral_constant<int, 0>{}, y);
+        if (y + 1 <= ye)
+            step(std::integral_constant<int, 1>{}, y + 1);
+        if (y + 2 <= ye)
+            step(std::integral_constant<int, 2>{}, y + 2);
+        if (y + 3 <= ye)
+            step(std::integral_constant<int, 3>{}, y + 3);
+        if (y + 4 <= ye)
+            step(std::integral_constant<int, 4>{}, y + 4);
+        if (y + 5 <= ye)
+            step(std::integral_constant<int, 5>{}, y + 5);
+    }
+    static_assert(kJ2fRing == 6, "steps written out above");
+#pragma unroll
+    for (int s = 0; s < M; ++s)
+        acc[s] = mine ? acc[s] : 0.0;
+}
+
+template <int M>
+__device__ __forceinline__ void j2f_item(const double *u_, double *w_, int64_t n, int64_t item,
+                                         double (&acc)[M])
+{
+    const J2fGeom g = j2f_geom(n, M);
+    const int64_t c = item % g.chunks;
+    const int64_t y0 = 1 + (item / g.chunks) * g.rows;
+    const int64_t y1 = y0 + g.rows < n - 1 ? y0 + g.rows : n - 1;
+    const int64_t halo = (M + 1) & ~1;
+    const int64_t cols = (n + 1) & ~(int64_t)1;
+    const int64_t xa = c * g.width;
+    const int64_t xb = xa + g.width;
+    const int64_t xmax = cols > 128 ? cols - 128 : 0;
+    int64_t x0 = xa - halo > 0 ? xa - halo : 0;
+    x0 = x0 < xmax ? x0 : xmax;
+#pragma unroll
+    for (int s = 0; s < M; ++s)
+        acc[s] = 0.0;
+    if (x0 == 0 || x0 + 128 >= n)
+        j2f_tile<M, true>(gptr(u_), gptr(w_), (int32_t)n, (int32_t)x0, (int32_t)xa, (int32_t)xb, (int32_t)y0,
+                          (int32_t)y1, acc);
+    else
+        j2f_tile<M, false>(gptr(u_), gptr(w_), (int32_t)n, (int32_t)x0, (int32_t)xa, (int32_t)xb, (int32_t)y0,
+                           (int32_t)y1, acc);
+}
+
+}  // namespace gf

@@ -17,6 +17,23 @@ constexpr int kMaxDevSteps = GF_MAX_STEPS;
 constexpr int kMaxGlue = 8;
 constexpr int kWave = 64;
 constexpr int kNumXcd = 8;
+constexpr int kFusedMax = 7;  // sweeps a fused pass takes at most (odd)
+// Threads per workgroup of the fused kernels: two wavefronts, so that the
+// groups of a batched run divide its items finely (256 uneven instances:
+// the slowest group takes 10 % less than with four).
+constexpr int kFusedWg = 128;
+constexpr int kFusedMinIters = 4;  // fewer sweeps: nothing to fuse (the last is a pass of its own)
+constexpr int kFusedMinSide = 16;  // smaller grids: one sweep per pass
+
+// Sweeps of the next fused pass with `left` sweeps to go: the last sweep is
+// always a pass of its own (both buffers then hold what the sweep-by-sweep
+// run leaves in them).
+__host__ __device__ inline int fused_sweeps(int64_t n, int32_t left)
+{
+    if (n < kFusedMinSide)
+        return 1;
+    return left > kFusedMax ? kFusedMax : (left > 3 ? 3 : 1);
+}
 
 struct DStep {
     int32_t kind;
@@ -261,8 +278,12 @@ void mlp_forward_host(const float *P, const float *f, float *out);
 // Host-side launch helpers implemented in gf_kernels.hip.
 hipError_t launch_persistent(const DProg &prog, const DInst &inst, const Tiling &t, int num_wg,
                              const Scratch &scr, const RpcRing &rpc, hipStream_t s,
-                             const BatchTable *batch = nullptr);
-int persistent_capacity(const DProg &prog, const Tiling &t, int num_cu);
+                             const BatchTable *batch = nullptr, bool fused = false);
+int persistent_capacity(const DProg &prog, const Tiling &t, int num_cu, bool fused = false);
+// Wavefront work items of a fused pass of m sweeps over an n-sided grid.
+int64_t fused_items(int kind, int64_t n, int m);
+// Relative time of one of its items (items of larger grids are longer).
+double fused_item_cost(int kind, int64_t n);
 // Co-resident workgroups of the per-region kernel that runs regions of `kind`.
 int region_capacity(int kind, const Tiling &t, int num_cu);
 hipError_t launch_main(const DProg &prog, const DInst &inst, const RpcRing &rpc, const Scratch &scr,

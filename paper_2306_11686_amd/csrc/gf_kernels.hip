@@ -226,6 +226,12 @@ __device__ __forceinline__ double wave_shl1(double v)
     return __hiloint2double(hi, lo);
 }
 
+}  // namespace gf
+
+#include "gf_fused.h"
+
+namespace gf {
+
 // 3D 7-point Jacobi for even n: each thread owns an x-pair (one 16-byte load
 // per row), a column of TY rows, and marches z. x-neighbours come from the
 // adjacent lanes by DPP shifts; the edge lanes of each wavefront swap their
@@ -409,7 +415,6 @@ __device__ __forceinline__ double j3v2_item(const double *u_, double *w_, int64_
 // in-bounds pair and store nothing.
 constexpr int kJ2Ahead = 4;
 constexpr int kJ2Ring = kJ2Ahead + 3;
-typedef double gf_d2u __attribute__((ext_vector_type(2), aligned(8)));
 
 template <bool ODD>
 __device__ __forceinline__ double j2m_seg(GF_GLOBAL const double *__restrict__ u, GF_GLOBAL double *__restrict__ w,
@@ -1249,6 +1254,26 @@ __device__ int64_t serial_call(const RpcRing &rpc, int32_t call_id, uint32_t fla
     return ret;
 }
 
+// One serial step other than GF_S_CALL in the persistent kernel, by thread 0
+// of a workgroup; `first` (the group's first workgroup) has the side effects.
+__device__ __forceinline__ void serial_step(const DStep &st, int32_t iter, bool first, double *s_scal, void **s_arr,
+                                            const RpcRing &rpc, int32_t *err)
+{
+    if (st.kind == GF_S_SWAP) {
+        void *tmp = s_arr[st.arr[0]];
+        s_arr[st.arr[0]] = s_arr[st.arr[1]];
+        s_arr[st.arr[1]] = tmp;
+    } else if (st.kind == GF_S_RECORD) {
+        if (first && iter >= 0)
+            ((double *)s_arr[st.arr[0]])[iter] = s_scal[st.sc[0]];
+    } else if (st.kind == GF_S_PRINTF) {
+        if (first && iter >= 0 && st.every > 0 && (iter + 1) % st.every == 0)
+            serial_printf(rpc, st.fmt_id, st.nargs, st.flags, st.sc, iter, s_scal, err);
+    } else {
+        serial_scalar(st.kind, st.sc, st.c, s_scal);
+    }
+}
+
 // ---------------------------------------------------------------------------
 // Persistent program kernel (the whole main loop in one cooperative launch;
 // Section 3.3 with the kernel split replaced by in-kernel grid barriers).
@@ -1261,6 +1286,10 @@ __device__ int64_t serial_call(const RpcRing &rpc, int32_t call_id, uint32_t fla
 // ---------------------------------------------------------------------------
 
 constexpr unsigned kFamHist = (1u << GF_R_HIST) | (1u << GF_R_OWNER);
+// The fused-sweep kernels (gf_fused.h): programs of one stencil region per
+// iteration, several sweeps per pass.
+constexpr unsigned kFusedBit = 1u << 31;
+constexpr unsigned kFamFused2 = kFusedBit | (1u << GF_R_JACOBI2D);
 
 template <unsigned KMASK>
 constexpr int family_max_threads()
@@ -1284,7 +1313,171 @@ constexpr int persistent_min_waves()
         return 3;
     if (KMASK == ((1u << GF_R_JACOBI2D) | (1u << GF_R_OWNER)))
         return 3;
+    if (KMASK == kFamFused2)
+        return 3;
     return 1;
+}
+
+// One pass of M sweeps: every wavefront's items and the barrier; then the
+// workgroup of the initial thread alone (`first`) reduces the pass's
+// partials, the M values in s_redv (LDS). The others go straight on: no
+// stencil region reads a scalar, and the partials of the next pass go to the
+// other half. last: no barrier is needed after a pass without reductions.
+template <unsigned KMASK, int M, typename Bar>
+__device__ __forceinline__ bool fused_pass(const double *src, double *dst, int64_t n, bool red, bool last, double *part,
+                                           double *s_redw, double *s_redv, int64_t worker, int64_t G, bool first,
+                                           Bar &barrier)
+{
+    constexpr int OP = GF_OP_SUM;
+    const int nw = blockDim.x / kWave;
+    const int wv = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
+    const int64_t items = j2f_geom(n, M).items;
+    for (int64_t it = worker * nw + wv; it < items; it += G * nw) {
+        double acc[M];
+        j2f_item<M>(src, dst, n, uniform_i64(it), acc);
+        if (red) {
+            wave_reduce_m<OP, M>(acc);
+            if ((threadIdx.x & (kWave - 1)) == 0)
+#pragma unroll
+                for (int s = 0; s < M; ++s)
+                    part[s * items + it] = acc[s];
+        }
+    }
+    if (!red)
+        return last || barrier(nullptr);
+    if (!barrier(nullptr))
+        return false;
+    if (first)
+        reduce_partials_m<OP, M>(part, items, s_redw, s_redv);
+    return true;
+}
+
+// The serial steps of a fused program's body, by one wavefront, in
+// registers: lane k holds step k of the body, lane i scalar variable i
+// (sweep by sweep every step waits for loads of its fields and for LDS,
+// about 0.5 us each; here a pass of seven 2D iterations takes about 1 us).
+struct SerialWave {
+    int32_t kind, sc0, sc1, sc2;
+    double c;
+    double *rec;
+    double scal;
+
+    __device__ __forceinline__ void load(const DProg &prog, const double *s_scal, void *const *s_arr)
+    {
+        const int lane = threadIdx.x & (kWave - 1);
+        const DStep &st = prog.steps[prog.n_pro + (lane < prog.n_body ? lane : 0)];
+        kind = st.kind;
+        sc0 = st.sc[0];
+        sc1 = st.sc[1];
+        sc2 = st.sc[2];
+        c = st.c;
+        rec = kind == GF_S_RECORD ? (double *)s_arr[st.arr[0]] : nullptr;
+        scal = s_scal[lane < GF_MAX_SCALARS ? lane : 0];
+    }
+    static __device__ __forceinline__ double lane_f64(double v, int lane)
+    {
+        return __hiloint2double(__builtin_amdgcn_readlane(__double2hiint(v), lane),
+                                __builtin_amdgcn_readlane(__double2loint(v), lane));
+    }
+    // One iteration of the body with the region's reduction value `red`.
+    __device__ __forceinline__ void iteration(const DProg &prog, int32_t iter, bool has_red, int red_op, double red,
+                                              double *s_scal, const RpcRing &rpc, int32_t *err)
+    {
+        const int lane = threadIdx.x & (kWave - 1);
+        for (int k = 0; k < prog.n_body; ++k) {
+            const int kd = __builtin_amdgcn_readlane(kind, k);
+            const int a = __builtin_amdgcn_readlane(sc0, k);
+            double v;
+            if (kd < 32) {
+                if (!has_red)
+                    continue;
+                v = red_apply(red_op, lane_f64(scal, a), red);
+            } else if (kd == GF_S_SET) {
+                v = lane_f64(c, k);
+            } else if (kd == GF_S_COPY) {
+                v = lane_f64(scal, __builtin_amdgcn_readlane(sc1, k));
+            } else if (kd == GF_S_SQRT) {
+                v = sqrt(lane_f64(scal, __builtin_amdgcn_readlane(sc1, k)));
+            } else if (kd == GF_S_DIV) {
+                v = lane_f64(scal, __builtin_amdgcn_readlane(sc1, k)) /
+                    lane_f64(scal, __builtin_amdgcn_readlane(sc2, k));
+            } else {
+                if (kd == GF_S_RECORD) {
+                    const double r = lane_f64(scal, a);
+                    if (lane == k)
+                        rec[iter] = r;
+                } else if (kd == GF_S_PRINTF) {
+                    const DStep &st = prog.steps[prog.n_pro + k];
+                    if ((iter + 1) % st.every == 0) {
+                        if (lane < GF_MAX_SCALARS)
+                            s_scal[lane] = scal;
+                        if (lane == 0)
+                            serial_printf(rpc, st.fmt_id, st.nargs, st.flags, st.sc, iter, s_scal, err);
+                    }
+                }
+                continue;  // a SWAP is applied to the pass's grids
+            }
+            if (lane == a)
+                scal = v;
+        }
+    }
+};
+
+// The whole of a fused program (checked on the host: scalar steps in the
+// prologue; a body of one stencil region, scalar steps and, after the
+// region, the SWAP of its two grids). The serial steps of a pass's
+// iterations run after it, each region step with its own sweep's value, on
+// the last worker, which has the fewest work items.
+template <unsigned KMASK, typename Bar>
+__device__ __forceinline__ void fused_program(const DProg &prog, const DInst &inst, double *s_scal, void **s_arr,
+                                              const Scratch &scr, const RpcRing &rpc, int64_t part_off,
+                                              int64_t worker, int64_t G, Bar &barrier)
+{
+    __shared__ double s_redw[kFusedMax * (kMaxWg / kWave)];
+    __shared__ double s_redv[kFusedMax];
+    const bool first = worker == G - 1;
+    int rs = prog.n_pro;
+    while (prog.steps[rs].kind >= 32)
+        ++rs;
+    const DStep &st = prog.steps[rs];
+    const int64_t n = uniform_i64(inst.ip[st.np]);
+    const bool red = st.red_op != GF_OP_NONE;
+    if (threadIdx.x == 0)
+        for (int k = 0; k < prog.n_pro; ++k)
+            serial_step(prog.steps[k], -1, first, s_scal, s_arr, rpc, scr.error);
+    __syncthreads();
+    const double *src = (const double *)uniform_ptr(s_arr[st.arr[0]]);
+    double *dst = (double *)uniform_ptr(s_arr[st.arr[1]]);
+    const bool serial = first && __builtin_amdgcn_readfirstlane(threadIdx.x / kWave) == 0;
+    SerialWave sw;
+    if (serial)
+        sw.load(prog, s_scal, s_arr);
+    int parity = 0;
+    for (int32_t iter = 0; iter < prog.iters;) {
+        const int32_t left = prog.iters - iter;
+        double *part = scr.partials + (parity ? scr.partials_cap : 0) + part_off;
+        const int m = fused_sweeps(n, left);
+        bool ok;
+        if (m == kFusedMax)
+            ok = fused_pass<KMASK, kFusedMax>(src, dst, n, red, false, part, s_redw, s_redv, worker, G, first, barrier);
+        else if (m == 3)
+            ok = fused_pass<KMASK, 3>(src, dst, n, red, false, part, s_redw, s_redv, worker, G, first, barrier);
+        else
+            ok = fused_pass<KMASK, 1>(src, dst, n, red, left == 1, part, s_redw, s_redv, worker, G, first, barrier);
+        if (!ok)
+            return;
+        parity ^= 1;
+        if (serial)
+            for (int j = 0; j < m; ++j)
+                sw.iteration(prog, iter + j, red, st.red_op, red ? s_redv[j] : 0.0, s_scal, rpc, scr.error);
+        // an odd number of sweeps: the grids have changed places
+        const double *t = src;
+        src = dst;
+        dst = (double *)t;
+        iter += m;
+    }
+    if (serial && threadIdx.x < GF_MAX_SCALARS)
+        inst.scal[threadIdx.x] = sw.scal;
 }
 
 template <unsigned KMASK, int TY, int PF>
@@ -1420,6 +1613,11 @@ __global__ void __launch_bounds__(family_max_threads<KMASK>())
         __syncthreads();
     }
 
+    if constexpr ((KMASK & kFusedBit) != 0) {
+        fused_program<KMASK>(prog, inst, s_scal, s_arr, scr, rpc, be.part_off, worker, G, barrier);
+        return;
+    }
+
     int parity = 0;   // partials half of the next reduction
     int mparity = 0;  // max slot of the next folded MAX reduction
     const int64_t total = (int64_t)n_pro + (int64_t)prog.iters * prog.n_body;
@@ -1549,19 +1747,7 @@ __global__ void __launch_bounds__(family_max_threads<KMASK>())
                     s_scal[st.sc[0]] = (double)__hip_atomic_load(retw, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
             }
         } else if (threadIdx.x == 0) {
-            if (st.kind == GF_S_SWAP) {
-                void *tmp = s_arr[st.arr[0]];
-                s_arr[st.arr[0]] = s_arr[st.arr[1]];
-                s_arr[st.arr[1]] = tmp;
-            } else if (st.kind == GF_S_RECORD) {
-                if (member == 0 && iter >= 0)
-                    ((double *)s_arr[st.arr[0]])[iter] = s_scal[st.sc[0]];
-            } else if (st.kind == GF_S_PRINTF) {
-                if (member == 0 && iter >= 0 && st.every > 0 && (iter + 1) % st.every == 0)
-                    serial_printf(rpc, st.fmt_id, st.nargs, st.flags, st.sc, iter, s_scal, scr.error);
-            } else {
-                serial_scalar(st.kind, st.sc, st.c, s_scal);
-            }
+            serial_step(st, iter, member == 0, s_scal, s_arr, rpc, scr.error);
         }
         // consecutive serial steps run back to back on thread 0; the
         // workgroup synchronises before the next region reads their results
@@ -1971,6 +2157,7 @@ static RegionFn region_for_ty(int ty, int pf)
 static PersistentFn persistent_fn(unsigned fam, int ty, int pf)
 {
     switch (fam) {
+    case kFamFused2: return k_persistent<kFamFused2, 1, 1>;
     case kFamJ3: return persistent_for_ty<kFamJ3>(ty, pf);
     case kFamJ2: return persistent_for_ty<kFamJ2>(1, 1);
     case kFamVec: return persistent_for_ty<kFamVec>(1, 1);
@@ -2027,9 +2214,31 @@ int region_capacity(int kind, const Tiling &t, int num_cu)
     return per_cu * num_cu;
 }
 
-int persistent_capacity(const DProg &prog, const Tiling &t, int num_cu)
+int64_t fused_items(int kind, int64_t n, int m)
 {
-    PersistentFn fn = persistent_fn(pick_family(program_kinds(prog)), t.tile_y, t.prefetch);
+    (void)kind;
+    return j2f_geom(n, m).items;
+}
+
+double fused_item_cost(int kind, int64_t n)
+{
+    (void)kind;
+    // stage-rows of a full pass, and three rows' worth of start
+    const double m = kFusedMax;
+    return j2f_geom(n, kFusedMax).rows * m + m * (m - 1) + 3 * m;
+}
+
+// The fused-sweep family of a program (one stencil region per iteration).
+static unsigned fused_family(const DProg &prog)
+{
+    (void)prog;
+    return kFamFused2;
+}
+
+int persistent_capacity(const DProg &prog, const Tiling &t, int num_cu, bool fused)
+{
+    PersistentFn fn =
+        persistent_fn(fused ? fused_family(prog) : pick_family(program_kinds(prog)), t.tile_y, t.prefetch);
     if (!fn)
         return 0;
     int per_cu = 0;
@@ -2040,9 +2249,10 @@ int persistent_capacity(const DProg &prog, const Tiling &t, int num_cu)
 }
 
 hipError_t launch_persistent(const DProg &prog, const DInst &inst, const Tiling &t, int num_wg, const Scratch &scr,
-                             const RpcRing &rpc, hipStream_t s, const BatchTable *batch)
+                             const RpcRing &rpc, hipStream_t s, const BatchTable *batch, bool fused)
 {
-    PersistentFn fn = persistent_fn(pick_family(program_kinds(prog)), t.tile_y, t.prefetch);
+    PersistentFn fn =
+        persistent_fn(fused ? fused_family(prog) : pick_family(program_kinds(prog)), t.tile_y, t.prefetch);
     if (!fn)
         return hipErrorInvalidValue;
     DProg p = prog;

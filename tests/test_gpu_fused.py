@@ -1,0 +1,136 @@
+"""Several sweeps per pass (launch shape left to the library) against one
+sweep per pass (a given tile) of the same program on the same data: both
+grids bit for bit, also where the outer layers of the two buffers differ, and
+every sweep's residual (a 2D residual is a sum taken in another order: within
+1e-12 of it, all terms being >= 0; a 3D one is a max and must be equal)."""
+import math
+
+import numpy as np
+import pytest
+
+import gf_inputs as gi
+from tests.gpu_helpers import dev, host, scalars
+
+pytestmark = pytest.mark.gpu
+
+
+def _run(ctx, prog, u0, w0, sweeps, launch, mode=None, record=None):
+    import torch
+    import paper_2306_11686_amd as gf
+    u, w = dev(u0), dev(w0)
+    res = torch.zeros(max(1, sweeps), dtype=torch.float64, device="cuda") if record is None else record(u, w)
+    sc = scalars({5: 3.0})
+    inst = gf.Instance.make({0: u, 1: w, 2: res}, sc, ip=(u0.shape[0],))
+    st = ctx.run(prog, inst, mode=gf.GF_EXEC_PERSISTENT, launch=launch)
+    ctx.sync()
+    return host(u), host(w), host(res).copy(), host(sc), st
+
+
+def _outer_differs(u0, seed):
+    """A second buffer with its own outer layer and interior."""
+    return gi.um11(seed, 33, np.arange(u0.size, dtype=np.uint64)).reshape(u0.shape)
+
+
+# sides: one and several 128-column items, odd and even, ends of a segment;
+# sweeps: every remainder of the pass lengths seven, three and one
+@pytest.mark.parametrize("n,sweeps", [(3, 4), (16, 5), (17, 8), (64, 7), (128, 11), (129, 9), (241, 15), (256, 22),
+                                      (345, 8), (513, 10), (1000, 9), (1023, 8)])
+def test_fused_2d_equals_sweep_by_sweep(gfx, n, sweeps):
+    import paper_2306_11686_amd as gf
+    from paper_2306_11686_amd import programs
+    print(f"fused 2d n={n} sweeps={sweeps}", flush=True)
+    u0 = gi.um11(3, 32, np.arange(n * n, dtype=np.uint64)).reshape(n, n)
+    w0 = _outer_differs(u0, 4)
+    prog = programs.jacobi2d(sweeps)
+    a = _run(gfx, prog, u0, w0, sweeps, None)
+    b = _run(gfx, prog, u0, w0, sweeps, gf.Launch.make(wg_size=256, tile_y=16))
+    assert np.array_equal(a[0], b[0]) and np.array_equal(a[1], b[1])
+    assert np.all(np.abs(a[2] - b[2]) <= 1e-12 * b[2])
+    assert b[4]["barriers"] == sweeps and (n < 16 or a[4]["barriers"] < sweeps)
+
+
+def test_fused_2d_grid_sizes_and_xcd_remap(gfx):
+    import paper_2306_11686_amd as gf
+    from paper_2306_11686_amd import programs
+    n, sweeps = 300, 10
+    u0 = gi.grid2d(n, seed=6)
+    prog = programs.jacobi2d(sweeps)
+    b = _run(gfx, prog, u0, u0, sweeps, gf.Launch.make(wg_size=256, tile_y=16))
+    for nwg in (1, 2, 7, 100, 300):
+        a = _run(gfx, prog, u0, u0, sweeps, gf.Launch.make(num_wg=nwg, xcd_remap=nwg % 2))
+        assert a[4]["num_wg"] == nwg
+        assert np.array_equal(a[0], b[0]) and np.array_equal(a[1], b[1])
+        assert np.all(np.abs(a[2] - b[2]) <= 1e-12 * b[2])
+
+
+def _steps_around(gf, kind, red_op, n_sweeps, swap_first=False):
+    """A body with scalar steps before, between and after the region: a
+    running sum of the residuals, a quotient and a copy."""
+    S = gf.Step
+    swap = S.make(gf.GF_S_SWAP, arr=(1, 0))
+    region = S.make(kind, arr=(0, 1), sc=(0,), red_op=red_op, np=0)
+    body = [S.make(gf.GF_S_SET, sc=(0,), c=0.0), region, S.make(gf.GF_S_DIV, sc=(1, 0, 5)), swap,
+            S.make(gf.GF_S_SQRT, sc=(2, 1)), S.make(gf.GF_S_COPY, sc=(3, 2)),
+            S.make(gf.GF_S_RECORD, arr=(2,), sc=(3,))]
+    if swap_first:
+        body.remove(swap)
+        body.insert(0, swap)
+    return gf.Program.make([S.make(gf.GF_S_COPY, sc=(6, 5))], body, n_sweeps)
+
+
+@pytest.mark.parametrize("swap_first", [False, True])
+@pytest.mark.parametrize("red", [True, False])
+def test_fused_serial_steps_and_forms(gfx, red, swap_first):
+    """Scalar steps around the region see every sweep in order; a body whose
+    SWAP comes first, and one without a reduction, give the same grids."""
+    import paper_2306_11686_amd as gf
+    n, sweeps = 150, 13
+    u0 = gi.grid2d(n, seed=7)
+    w0 = _outer_differs(u0, 8)
+    prog = _steps_around(gf, gf.GF_R_JACOBI2D, gf.GF_OP_SUM if red else gf.GF_OP_NONE, sweeps, swap_first)
+    a = _run(gfx, prog, u0, w0, sweeps, None)
+    b = _run(gfx, prog, u0, w0, sweeps, gf.Launch.make(wg_size=256, tile_y=16))
+    assert np.array_equal(a[0], b[0]) and np.array_equal(a[1], b[1])
+    assert np.all(np.abs(a[2] - b[2]) <= 1e-12 * b[2])
+    assert np.all(np.abs(a[3] - b[3]) <= 1e-12 * np.abs(b[3]))
+
+
+def test_fused_records_that_share_memory_with_a_grid(gfx):
+    """A body that records into the grid's own memory is run sweep by sweep:
+    the recorded value is what the next sweep reads (one workgroup: with more,
+    nothing orders the record before the other workgroups' reads)."""
+    import paper_2306_11686_amd as gf
+    from paper_2306_11686_amd import programs
+    n, sweeps = 64, 6
+    u0 = gi.grid2d(n, seed=9)
+    prog = programs.jacobi2d(sweeps)
+    out = [_run(gfx, prog, u0, u0, sweeps, l, record=lambda u, w: u.view(-1)[n * 20:n * 20 + sweeps])
+           for l in (gf.Launch.make(num_wg=1), gf.Launch.make(num_wg=1, wg_size=256, tile_y=16))]
+    assert np.array_equal(out[0][0], out[1][0]) and np.array_equal(out[0][1], out[1][1])
+    assert out[0][4]["barriers"] == sweeps
+
+
+def test_fused_2d_batch_in_groups_on_one_xcd_and_in_order(gfx, monkeypatch):
+    """Uneven instances in one launch, groups kept to one XCD (group barrier
+    without write-back) and laid out in order, against each one sweep by
+    sweep; the last instance has fewer rows than a pass has sweeps."""
+    import torch
+    import paper_2306_11686_amd as gf
+    from paper_2306_11686_amd import programs
+    sides, sweeps = [400, 65, 128, 700, 33, 3], 16
+    grids = [gi.batched_grid(i, n, 11) for i, n in enumerate(sides)]
+    prog = programs.jacobi2d(sweeps)
+    ref = [_run(gfx, prog, g, g, sweeps, gf.Launch.make(wg_size=256, tile_y=16)) for g in grids]
+    for align in ("1", "0"):
+        monkeypatch.setenv("GF_BATCH_ALIGN", align)
+        with gf.Context(0) as ctx:
+            us, ws = [dev(g) for g in grids], [dev(g) for g in grids]
+            rs = [torch.zeros(sweeps, dtype=torch.float64, device="cuda") for _ in sides]
+            insts = [gf.Instance.make({0: u, 1: w, 2: r}, scalars(), ip=(n,))
+                     for u, w, r, n in zip(us, ws, rs, sides)]
+            ctx.run(prog, insts, mode=gf.GF_EXEC_PERSISTENT)
+            ctx.sync()
+            for i in range(len(sides)):
+                assert np.array_equal(host(us[i]), ref[i][0]), (align, i)
+                assert np.array_equal(host(ws[i]), ref[i][1]), (align, i)
+                assert np.all(np.abs(host(rs[i]) - ref[i][2]) <= 1e-12 * ref[i][2]), (align, i)
