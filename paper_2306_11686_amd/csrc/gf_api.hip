@@ -1529,7 +1529,7 @@ struct InstShape {
 };
 
 // ---- fused sweeps (gf_fused.h) ------------------------------------------
-// A program whose body is one 2D stencil region, scalar steps and, after the
+// A program whose body is one stencil region, scalar steps and, after the
 // region, the SWAP of the region's two grids can run several sweeps per pass
 // over the grid. Returns the region's step index, or -1. The prologue may
 // hold scalar steps; a host call anywhere could read or write the grids
@@ -1552,29 +1552,34 @@ int fusable_region(const DProg &p)
     if (rs < 0 || swap < 0 || p.iters < kFusedMinIters)
         return -1;
     const DStep &r = p.steps[rs], &w = p.steps[swap];
-    if (r.kind != GF_R_JACOBI2D || (r.flags & GF_STEP_NOWAIT) || r.arr[0] == r.arr[1])
+    if ((r.kind != GF_R_JACOBI2D && r.kind != GF_R_JACOBI3D) || (r.flags & GF_STEP_NOWAIT) || r.arr[0] == r.arr[1])
         return -1;
     const bool same = (w.arr[0] == r.arr[0] && w.arr[1] == r.arr[1]) || (w.arr[0] == r.arr[1] && w.arr[1] == r.arr[0]);
     return same ? rs : -1;
 }
 
+// Sweeps of a full pass, and the sides below which a pass takes one.
+int fused_max(int kind, int64_t n) { return fused_sweeps(kind, n, kFusedMax2 + 1); }
+
+// Planes per segment a batched 3D run's shares are computed with.
+constexpr int32_t kFusedBatchZ = 32;
+
 // Partial values the largest pass over an n-sided grid writes.
-int64_t fused_partials(int kind, int64_t n)
+int64_t fused_partials(int kind, int64_t n, int32_t zlen)
 {
     int64_t most = 0;
-    for (int m : {1, 3, kFusedMax})
-        most = std::max<int64_t>(most, m * fused_items(kind, n, m));
+    for (int m : {1, 3, kFusedMax2})
+        most = std::max<int64_t>(most, m * fused_items(kind, n, m, zlen));
     return most;
 }
 
 // The grids of an instance and the arrays its body records into do not
-// overlap (a sweep left in registers is seen by nobody else), and the
-// partial sums of a pass fit.
-bool fusable_instance(const gf_ctx *ctx, const DProg &p, int rs, const gf_instance &in)
+// overlap: a sweep left in registers is seen by nobody else.
+bool fusable_instance(const DProg &p, int rs, const gf_instance &in)
 {
     const DStep &r = p.steps[rs];
     const uint64_t n = (uint64_t)in.ip[r.np];
-    const uint64_t bytes = n * n * 8;
+    const uint64_t bytes = (r.kind == GF_R_JACOBI3D ? n * n * n : n * n) * 8;
     // slots as the prologue's swaps leave them
     void *arr[GF_MAX_ARRAYS];
     std::memcpy(arr, in.arr, sizeof arr);
@@ -1595,22 +1600,25 @@ bool fusable_instance(const gf_ctx *ctx, const DProg &p, int rs, const gf_instan
             if (!apart(rec, nb, u, bytes) || !apart(rec, nb, w, bytes))
                 return false;
         }
-    return fused_partials(r.kind, (int64_t)n) <= ctx->scr.partials_cap;
+    return true;
 }
 
-// Workgroup items of a pass (a wavefront takes one item at a time).
-int64_t fused_wg_items(int kind, int64_t n, int wg_size)
+// Workgroup items of a full pass (a wavefront takes one item at a time).
+int64_t fused_wg_items(int kind, int64_t n, int32_t zlen)
 {
-    const int64_t waves = wg_size / kWave;
-    return std::max<int64_t>(1, (fused_items(kind, n, n < kFusedMinSide ? 1 : kFusedMax) + waves - 1) / waves);
+    const int64_t waves = fused_wg(kind) / kWave;
+    return std::max<int64_t>(1, (fused_items(kind, n, fused_max(kind, n), zlen) + waves - 1) / waves);
 }
 
 // Grid barriers of a fused run: one per pass, none after a last pass
-// without a reduction.
+// without a reduction; 3D: one after the comparison of the outer layers
+// (where they differ, the run takes one sweep per pass all the same).
 int64_t fused_barriers(const DProg &p, int rs, int64_t n)
 {
     int64_t passes = 0;
-    for (int32_t left = p.iters; left > 0; left -= fused_sweeps(n, left))
+    for (int32_t left = p.iters; left > 0; left -= fused_sweeps(p.steps[rs].kind, n, left))
+        ++passes;
+    if (p.steps[rs].kind == GF_R_JACOBI3D)
         ++passes;
     return p.steps[rs].red_op == GF_OP_NONE ? passes - 1 : passes;
 }
@@ -1750,12 +1758,13 @@ gf_status run_batched(gf_ctx *ctx, const DProg &p, const gf_instance *inst, int 
         Tiling ti = t;
         if (shape && shape[i].tile_y > 0)
             ti.tile_y = ty[i] = shape[i].tile_y;
-        items[i] = std::max<int64_t>(1, max_items(p, inst[i], ti));
         int64_t r = 0;
-        if (fused_rs >= 0) {
+        if (fused_rs < 0) {
+            items[i] = std::max<int64_t>(1, max_items(p, inst[i], ti));
+        } else {
             const DStep &st = p.steps[fused_rs];
-            items[i] = fused_wg_items(st.kind, inst[i].ip[st.np], t.wg_size);
-            r = fused_partials(st.kind, inst[i].ip[st.np]);
+            items[i] = fused_wg_items(st.kind, inst[i].ip[st.np], kFusedBatchZ);
+            r = fused_partials(st.kind, inst[i].ip[st.np], 1);  // 3D: whatever segments the group takes
         }
         for (int k = 0; k < p.n_steps && fused_rs < 0; ++k)
             if (is_region(p.steps[k].kind) && p.steps[k].red_op != GF_OP_NONE)
@@ -1763,7 +1772,7 @@ gf_status run_batched(gf_ctx *ctx, const DProg &p, const gf_instance *inst, int 
         red[i] = r;
         w[i] = (shape && shape[i].weight > 0.0) ? shape[i].weight : (double)items[i];
         if (fused_rs >= 0)
-            w[i] *= fused_item_cost(p.steps[fused_rs].kind, inst[i].ip[p.steps[fused_rs].np]);
+            w[i] *= fused_item_cost(p.steps[fused_rs].kind, inst[i].ip[p.steps[fused_rs].np], kFusedBatchZ);
     }
     // pack onto XCDs and size the groups
     std::vector<int> g(n_inst, 1), xcd_of(n_inst, -1);
@@ -2082,15 +2091,16 @@ static gf_status region_run(gf_ctx *ctx, const gf_program *prog, const gf_instan
         // size the plain kernel can hold and the fused one cannot, and a
         // batch with more instances than its capacity, run plainly too.
         int fused_rs = -1, fcap = 0;
+        int32_t fused_z = 0;  // 3D: planes per segment
         if (!shape && (!launch || (!launch->wg_size && !launch->tile_y && !launch->tile_z && !launch->items &&
                                    !launch->prefetch)))
             fused_rs = fusable_region(p);
         for (int i = 0; i < n_inst && fused_rs >= 0; ++i)
-            if (!fusable_instance(ctx, p, fused_rs, inst[i]))
+            if (!fusable_instance(p, fused_rs, inst[i]))
                 fused_rs = -1;
         if (fused_rs >= 0) {
             Tiling ft = t;
-            ft.wg_size = kFusedWg;
+            ft.wg_size = fused_wg(p.steps[fused_rs].kind);
             fcap = std::min(4096, persistent_capacity(p, ft, ctx->num_cu, true));
             if (fcap <= 0 || n_inst > fcap || (launch && launch->num_wg > fcap && n_inst == 1))
                 fused_rs = -1;
@@ -2098,12 +2108,20 @@ static gf_status region_run(gf_ctx *ctx, const gf_program *prog, const gf_instan
         if (n_inst > 1 && fused_rs >= 0) {
             int64_t part = 0;
             for (int i = 0; i < n_inst; ++i)
-                part += fused_partials(p.steps[fused_rs].kind, inst[i].ip[p.steps[fused_rs].np]);
+                part += fused_partials(p.steps[fused_rs].kind, inst[i].ip[p.steps[fused_rs].np], 1);
             if (part > ctx->scr.partials_cap)
                 fused_rs = -1;
         }
-        if (fused_rs >= 0)
-            t.wg_size = kFusedWg;
+        if (n_inst == 1 && fused_rs >= 0) {
+            const int64_t n = inst[0].ip[p.steps[fused_rs].np];
+            fused_z = fused_zlen(n, launch && launch->num_wg > 0 ? launch->num_wg : fcap);
+            if (fused_partials(p.steps[fused_rs].kind, n, fused_z) > ctx->scr.partials_cap)
+                fused_rs = -1;
+        }
+        if (fused_rs >= 0) {
+            t.wg_size = fused_wg(p.steps[fused_rs].kind);
+            t.tile_z = fused_z;  // a batched 3D run (0): chosen by each group
+        }
         if (n_inst > 1)
             return run_batched(ctx, p, inst, n_inst, t, launch, fused_rs >= 0 ? fcap : cap, stats, stream, shape,
                                fused_rs);
@@ -2112,11 +2130,13 @@ static gf_status region_run(gf_ctx *ctx, const gf_program *prog, const gf_instan
             // cost grows with the number of members), sized so that every
             // workgroup gets the same number of work items (balanced rounds)
             int64_t gmax = std::min<int64_t>(cap, 2 * (int64_t)ctx->num_cu);
-            int64_t items = max_items(p, inst[i], t);
-            if (fused_rs >= 0) {
+            int64_t items = 0;
+            if (fused_rs < 0) {
+                items = max_items(p, inst[i], t);
+            } else {
                 const DStep &st = p.steps[fused_rs];
-                items = fused_wg_items(st.kind, inst[i].ip[st.np], t.wg_size);
                 gmax = fcap;
+                items = fused_wg_items(st.kind, inst[i].ip[st.np], fused_z);
             }
             const int64_t rounds = (items + gmax - 1) / gmax;
             int grid = (int)((items + rounds - 1) / rounds);

@@ -39,7 +39,8 @@ typedef double gf_d2u __attribute__((ext_vector_type(2), aligned(8)));
 template <typename V, typename T>
 __device__ __forceinline__ GF_GLOBAL V *row_at(GF_GLOBAL T *p, uint32_t byte)
 {
-    asm("" : "+s"(p));
+    // the offset too: its extension to 64 bits has to stay beside the access
+    asm("" : "+s"(p), "+v"(byte));
     return (GF_GLOBAL V *)((GF_GLOBAL const char *)p + byte);
 }
 
@@ -120,9 +121,10 @@ struct J2fGeom {
     int64_t items;
 };
 
-__host__ __device__ inline J2fGeom j2f_geom(int64_t n, int M)
+// Items of 128 loaded columns across an n-column row when M columns are lost
+// on an inner side, and the output columns of each.
+__host__ __device__ inline void j2f_chunks(int64_t n, int M, int32_t *chunks, int32_t *width)
 {
-    J2fGeom g;
     const int64_t halo = (M + 1) & ~1;   // whole lanes lost on an inner side
     const int64_t cols = (n + 1) & ~(int64_t)1;
     int64_t c = 1;
@@ -131,8 +133,14 @@ __host__ __device__ inline J2fGeom j2f_geom(int64_t n, int M)
         if (cols > 2 * (128 - halo))
             c = (cols + (128 - 2 * halo) - 1) / (128 - 2 * halo);
     }
-    g.chunks = (int32_t)c;
-    g.width = (int32_t)(((cols + c - 1) / c + 1) & ~(int64_t)1);
+    *chunks = (int32_t)c;
+    *width = (int32_t)(((cols + c - 1) / c + 1) & ~(int64_t)1);
+}
+
+__host__ __device__ inline J2fGeom j2f_geom(int64_t n, int M)
+{
+    J2fGeom g;
+    j2f_chunks(n, M, &g.chunks, &g.width);
     // long segments repeat less at their ends (M rows of the neighbours on
     // each side), short ones give a small grid more wavefronts
     const int64_t r = n / 32;
@@ -263,22 +271,29 @@ __device__ __forceinline__ void j2f_tile(GF_GLOBAL const double *__restrict__ u,
                 st[s < M ? s - 1 : 0][k % 3] = out;
         }
     };
-    for (int32_t y = ya; y <= ye; y += kJ2fRing) {
+    for (int32_t y = ya;;) {
         // past the first row at every stage: from here the outer row is the
         // last one (the first stage reaches it at step n)
         if (y > M)
             eb = ldrow(n - 1);
         step(std::integral_constant<int, 0>{}, y);
-        if (y + 1 <= ye)
-            step(std::integral_constant<int, 1>{}, y + 1);
-        if (y + 2 <= ye)
-            step(std::integral_constant<int, 2>{}, y + 2);
-        if (y + 3 <= ye)
-            step(std::integral_constant<int, 3>{}, y + 3);
-        if (y + 4 <= ye)
-            step(std::integral_constant<int, 4>{}, y + 4);
-        if (y + 5 <= ye)
-            step(std::integral_constant<int, 5>{}, y + 5);
+        if (++y > ye)
+            break;
+        step(std::integral_constant<int, 1>{}, y);
+        if (++y > ye)
+            break;
+        step(std::integral_constant<int, 2>{}, y);
+        if (++y > ye)
+            break;
+        step(std::integral_constant<int, 3>{}, y);
+        if (++y > ye)
+            break;
+        step(std::integral_constant<int, 4>{}, y);
+        if (++y > ye)
+            break;
+        step(std::integral_constant<int, 5>{}, y);
+        if (++y > ye)
+            break;
     }
     static_assert(kJ2fRing == 6, "steps written out above");
 #pragma unroll
@@ -310,6 +325,249 @@ __device__ __forceinline__ void j2f_item(const double *u_, double *w_, int64_t n
     else
         j2f_tile<M, false>(gptr(u_), gptr(w_), (int32_t)n, (int32_t)x0, (int32_t)xa, (int32_t)xb, (int32_t)y0,
                            (int32_t)y1, acc);
+}
+
+// ---------------------------------------------------------------------------
+// 3D. A wavefront owns 128 columns (two per lane) by kJ3fRows output rows and
+// marches z; the four wavefronts of a workgroup sit above each other in y.
+// When plane z arrives, stage s computes plane z - s of sweep k + s for the
+// output rows and M - s rows on each side, from stage s-1's planes z-s-1,
+// z-s, z-s+1, all in registers. The rows a neighbouring wavefront also reads
+// come from the CU's L1. A plane's rows are requested as soon as the
+// registers of the plane three before are free, one step ahead of their use.
+// Only run when the two buffers' outer layers agree (the kernel compares
+// them first), so a point of the outer layer keeps its value at every stage.
+// ---------------------------------------------------------------------------
+
+constexpr int kJ3fRows = 3;    // output rows per wavefront
+constexpr int kJ3fWaves = 4;   // wavefronts of a workgroup, along y
+
+struct J3fGeom {
+    int32_t chunks, width;  // items across a row, output columns of one (even)
+    int32_t yt;             // workgroup tiles along y
+    int32_t zlen, zs;       // planes per segment, segments
+    int64_t items;          // workgroup items
+};
+
+__host__ __device__ inline J3fGeom j3f_geom(int64_t n, int M, int32_t zlen)
+{
+    J3fGeom g;
+    j2f_chunks(n, M, &g.chunks, &g.width);
+    const int64_t in = n > 2 ? n - 2 : 0;
+    g.yt = (int32_t)((in + kJ3fRows * kJ3fWaves - 1) / (kJ3fRows * kJ3fWaves));
+    g.zlen = zlen;
+    g.zs = (int32_t)((in + zlen - 1) / zlen);
+    g.items = (int64_t)g.chunks * g.yt * g.zs;
+    return g;
+}
+
+// Planes per segment for a pass of M sweeps shared by G workgroups: the
+// fewest plane steps of the slowest workgroup (a segment repeats M planes on
+// each side), and one more step per 64 workgroups for the barrier.
+__host__ __device__ inline int32_t j3f_zlen(int64_t n, int M, int64_t G)
+{
+    const int64_t in = n > 2 ? n - 2 : 1;
+    int64_t best = 0, best_cost = 0;
+    for (int64_t zs = 1; zs <= in && zs <= 64; ++zs) {
+        const int64_t zl = (in + zs - 1) / zs;
+        const int64_t items = j3f_geom(n, M, (int32_t)zl).items;
+        const int64_t rounds = (items + G - 1) / G;
+        const int64_t cost = rounds * (zl + 2 * M) * 64 + (items < G ? items : G);
+        if (best == 0 || cost < best_cost) {
+            best = zl;
+            best_cost = cost;
+        }
+    }
+    return (int32_t)best;
+}
+
+// Whether the outer layers of the two n-sided 3D grids hold the same bits,
+// in the points of worker `worker` of G.
+__device__ __forceinline__ bool outer3_agrees(GF_GLOBAL const double *a_, GF_GLOBAL const double *b_, int64_t n,
+                                              int64_t worker, int64_t G)
+{
+    GF_GLOBAL const uint64_t *a = (GF_GLOBAL const uint64_t *)a_;
+    GF_GLOBAL const uint64_t *b = (GF_GLOBAL const uint64_t *)b_;
+    const int64_t sq = n * n, far = n - 1;
+    uint64_t diff = 0;
+    for (int64_t i = worker * blockDim.x + threadIdx.x; i < sq; i += G * blockDim.x) {
+        const int64_t p = i / n, q = i - p * n;
+        diff |= (a[i] ^ b[i]) | (a[far * sq + i] ^ b[far * sq + i]);                          // z faces
+        diff |= (a[p * sq + q] ^ b[p * sq + q]) | (a[p * sq + far * n + q] ^ b[p * sq + far * n + q]);  // y faces
+        diff |= (a[i * n] ^ b[i * n]) | (a[i * n + far] ^ b[i * n + far]);                    // x faces
+    }
+    return diff == 0;
+}
+
+// Planes [z0, z1), rows [y0, y0 + kJ3fRows) of u^(k+M). EDGE: the tile or the
+// rows, columns and planes around it that it computes touch the outer layer.
+// valid: false for a wavefront past the last row (it keeps step with the
+// others and stores nothing). acc[s]: the lane's max |difference| of sweep
+// k + s + 1.
+template <int M, bool EDGE>
+__device__ __forceinline__ void j3f_tile(GF_GLOBAL const double *__restrict__ u, GF_GLOBAL double *__restrict__ w,
+                                         int32_t n, int32_t x0, int32_t xa, int32_t xb, int32_t y0, bool valid,
+                                         int32_t z0, int32_t z1, double (&acc)[M])
+{
+    constexpr int TY = kJ3fRows;
+    constexpr int R0 = TY + 2 * M;
+    const int lane = threadIdx.x & (kWave - 1);
+    const int32_t x = x0 + 2 * lane;
+    const uint32_t xs = 8u * (uint32_t)(EDGE && x > n - 2 ? n - 2 : x);
+    const bool lone = EDGE && x == n - 1;
+    const bool bx = EDGE && (x == 0 || x == n - 1);
+    const bool by = EDGE && x + 1 == n - 1;
+    const bool zy = by || lone;
+    const bool mine = valid && x >= xa && x < xb && x < n;
+    const int64_t pitch = n, plane = (int64_t)n * n;
+    const int32_t za = z0 - M > 0 ? z0 - M : 0;                    // first plane read
+    const int32_t zb = z1 - 1 + M < n - 1 ? z1 - 1 + M : n - 1;    // last plane read
+    const int32_t ze = z1 - 1 + M;                                 // last step
+    auto ld = [&](int32_t z, int j) -> gf_d2 {
+        int32_t y = y0 - M + j;
+        if constexpr (EDGE)
+            y = y < 0 ? 0 : (y > n - 1 ? n - 1 : y);
+        const gf_d2 v = *row_at<const gf_d2u>(u + (z < zb ? z : zb) * plane + y * pitch, xs);
+        if constexpr (EDGE)
+            return gf_d2{lone ? v.y : v.x, v.y};
+        return v;
+    };
+    const gf_d2 zero2 = {0.0, 0.0};
+    // q[s][slot][row]: stage s's planes, row j of stage s is y0 - (M - s) + j
+    gf_d2 q[M][3][R0];
+#pragma unroll
+    for (int s = 0; s < M; ++s)
+#pragma unroll
+        for (int k = 0; k < 3; ++k)
+#pragma unroll
+            for (int j = 0; j < R0 - 2 * s; ++j)
+                q[s][k][j] = zero2;
+#pragma unroll
+    for (int j = 0; j < R0; ++j)
+        q[0][0][j] = ld(za, j);
+    const double c6 = 1.0 / 6.0;
+    gf_d2 fin[TY];  // the last stage's rows
+#pragma unroll
+    for (int j = 0; j < TY; ++j)
+        fin[j] = zero2;
+    // one step: plane z is in slot k of stage 0
+    auto step = [&](auto kc, int32_t z) {
+        constexpr int k = decltype(kc)::value;
+        constexpr int kc1 = (k + 2) % 3, km = (k + 1) % 3;  // the planes one and two before
+        __syncthreads();
+        // stage 0's plane z-2 is read for its middle rows only
+        q[0][km][0] = ld(z + 1, 0);
+#pragma unroll
+        for (int j = 0; j < R0 - 2 + M - 1; ++j) {
+            // row j of stage 1, then row j-1 of stage 2, j-2 of stage 3
+#pragma unroll
+            for (int s = 1; s <= M; ++s) {
+                const int i = j - (s - 1);
+                if (i < 0 || i >= R0 - 2 * s)
+                    continue;
+                const gf_d2 c = q[s - 1][kc1][i + 1];
+                const gf_d2 up = q[s - 1][kc1][i], dn = q[s - 1][kc1][i + 2];
+                const gf_d2 zm = q[s - 1][km][i + 1], zp = q[s - 1][k][i + 1];
+                const double xl = lane_left(c.y);
+                const double xr = lane_right(c.x);
+                gf_d2 out;
+                out.x = (((xl + c.y) + (up.x + dn.x)) + (zm.x + zp.x)) * c6;
+                out.y = (((c.x + xr) + (up.y + dn.y)) + (zm.y + zp.y)) * c6;
+                if constexpr (EDGE) {
+                    const int32_t y = y0 - (M - s) + i;
+                    const bool flat = y <= 0 || y >= n - 1 || z - s <= 0 || z - s >= n - 1;
+                    out.x = (bx || flat) ? c.x : out.x;
+                    out.y = (by || flat) ? c.y : out.y;
+                }
+                // computed here: sunk towards its use in the next steps, the
+                // value keeps all of its inputs in registers
+                asm volatile("" : "+v"(out.x), "+v"(out.y));
+                if (s < M)
+                    q[s < M ? s : 0][k][i] = out;
+                else
+                    fin[i < TY ? i : 0] = out;
+                if (s == 1)
+                    q[0][km][i + 1] = ld(z + 1, i + 1);
+            }
+        }
+        q[0][km][R0 - 1] = ld(z + 1, R0 - 1);
+        // the output rows' differences, planes of this segment
+#pragma unroll
+        for (int s = 1; s <= M; ++s)
+            if (z - s >= z0 && z - s < z1) {
+#pragma unroll
+                for (int t = 0; t < TY; ++t) {
+                    if (EDGE && y0 + t > n - 2)
+                        continue;
+                    const gf_d2 o = s < M ? q[s < M ? s : 0][k][t + M - s] : fin[t];
+                    const gf_d2 c = q[s - 1][kc1][t + M - s + 1];
+                    double dx = __builtin_fabs(o.x - c.x), dy = __builtin_fabs(o.y - c.y);
+                    if constexpr (EDGE) {
+                        dx = bx ? -INFINITY : dx;
+                        dy = zy ? -INFINITY : dy;
+                    }
+                    acc[s - 1] = __builtin_fmax(acc[s - 1], __builtin_fmax(dx, dy));
+                    if (s == M && mine) {
+                        GF_GLOBAL double *p = row_at<double>(w + (z - M) * plane + (y0 + t) * pitch, xs);
+                        if (!EDGE || (!bx && !by))
+                            __builtin_nontemporal_store(o, (GF_GLOBAL gf_d2u *)p);
+                        else if (!bx)
+                            __builtin_nontemporal_store(o.x, p);
+                        else if (!zy)
+                            __builtin_nontemporal_store(o.y, p + 1);
+                    }
+                }
+            }
+    };
+    for (int32_t z = za;;) {
+        step(std::integral_constant<int, 0>{}, z);
+        if (++z > ze)
+            break;
+        step(std::integral_constant<int, 1>{}, z);
+        if (++z > ze)
+            break;
+        step(std::integral_constant<int, 2>{}, z);
+        if (++z > ze)
+            break;
+    }
+#pragma unroll
+    for (int s = 0; s < M; ++s)
+        acc[s] = mine ? acc[s] : -INFINITY;
+}
+
+// One workgroup item: wavefront wv's rows.
+template <int M>
+__device__ __forceinline__ void j3f_item(const double *u_, double *w_, int64_t n, int32_t zlen, int64_t item, int wv,
+                                         double (&acc)[M])
+{
+    const J3fGeom g = j3f_geom(n, M, zlen);
+    const int64_t c = item % g.chunks;
+    const int64_t rest = item / g.chunks;
+    const int64_t yt = rest % g.yt;
+    const int64_t zi = rest / g.yt;
+    const int64_t z0 = 1 + zi * g.zlen;
+    const int64_t z1 = z0 + g.zlen < n - 1 ? z0 + g.zlen : n - 1;
+    int64_t y0 = 1 + (yt * kJ3fWaves + wv) * kJ3fRows;
+    const bool valid = y0 <= n - 2;
+    y0 = valid ? y0 : 1;
+    const int64_t halo = (M + 1) & ~1;
+    const int64_t cols = (n + 1) & ~(int64_t)1;
+    const int64_t xa = c * g.width;
+    const int64_t xmax = cols > 128 ? cols - 128 : 0;
+    int64_t x0 = xa - halo > 0 ? xa - halo : 0;
+    x0 = x0 < xmax ? x0 : xmax;
+#pragma unroll
+    for (int s = 0; s < M; ++s)
+        acc[s] = -INFINITY;
+    // rows and planes the stages compute, and the columns they load
+    const bool edge = x0 == 0 || x0 + 128 >= n || y0 - M < 0 || y0 + kJ3fRows + M > n || z0 - (M - 1) <= 0 ||
+                      z1 - 1 + (M - 1) >= n - 1;
+    if (edge)
+        j3f_tile<M, true>(gptr(u_), gptr(w_), (int32_t)n, (int32_t)x0, (int32_t)xa, (int32_t)(xa + g.width),
+                          (int32_t)y0, valid, (int32_t)z0, (int32_t)z1, acc);
+    else
+        j3f_tile<M, false>(gptr(u_), gptr(w_), (int32_t)n, (int32_t)x0, (int32_t)xa, (int32_t)(xa + g.width),
+                           (int32_t)y0, valid, (int32_t)z0, (int32_t)z1, acc);
 }
 
 }  // namespace gf

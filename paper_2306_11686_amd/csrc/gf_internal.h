@@ -17,22 +17,31 @@ constexpr int kMaxDevSteps = GF_MAX_STEPS;
 constexpr int kMaxGlue = 8;
 constexpr int kWave = 64;
 constexpr int kNumXcd = 8;
-constexpr int kFusedMax = 7;  // sweeps a fused pass takes at most (odd)
-// Threads per workgroup of the fused kernels: two wavefronts, so that the
-// groups of a batched run divide its items finely (256 uneven instances:
-// the slowest group takes 10 % less than with four).
-constexpr int kFusedWg = 128;
+// Fused sweeps (gf_fused.h): sweeps of a full pass per stencil (odd). More
+// would take fewer passes, but in 3D the sweeps' planes fill the registers,
+// and in 2D the steps at the ends of the segments outweigh the bytes saved.
+constexpr int kFusedMax2 = 7;
+constexpr int kFusedMax3 = 3;
+// Threads per workgroup. 2D: two wavefronts, so that the groups of a batched
+// run divide its items finely (256 uneven instances: the slowest group takes
+// 10 % less than with four); 3D: four, which share the rows between them.
+constexpr int kFusedWg2 = 128;
+constexpr int kFusedWg3 = 256;
 constexpr int kFusedMinIters = 4;  // fewer sweeps: nothing to fuse (the last is a pass of its own)
-constexpr int kFusedMinSide = 16;  // smaller grids: one sweep per pass
+constexpr int kFusedMinSide2 = 16;  // smaller 2D grids: one sweep per pass
 
 // Sweeps of the next fused pass with `left` sweeps to go: the last sweep is
 // always a pass of its own (both buffers then hold what the sweep-by-sweep
 // run leaves in them).
-__host__ __device__ inline int fused_sweeps(int64_t n, int32_t left)
+__host__ __device__ inline int fused_sweeps(int kind, int64_t n, int32_t left)
 {
-    if (n < kFusedMinSide)
-        return 1;
-    return left > kFusedMax ? kFusedMax : (left > 3 ? 3 : 1);
+    if (kind == GF_R_JACOBI2D) {
+        if (n < kFusedMinSide2)
+            return 1;
+        if (left > kFusedMax2)
+            return kFusedMax2;
+    }
+    return left > 3 ? 3 : 1;
 }
 
 struct DStep {
@@ -206,6 +215,9 @@ constexpr int kLineWords = 32;  // uint32 words per 128-byte line
 // at lines kFinalizeSubLine0 + i * kNumXcd + g. Words 4-5 of a group line
 // carry the return value of a GF_S_CALL from the group's first workgroup to
 // the others.
+// Word kGroupOuterWord: the epoch of the last fused 3D run whose two grids'
+// outer layers differed.
+constexpr int kGroupOuterWord = 8;
 constexpr int kTreeFanIn = 16;
 constexpr int kTreeLine0 = 1;
 constexpr int kTreeLines = 512;  // >= 4096/16 + 4096/256 + 1
@@ -280,10 +292,13 @@ hipError_t launch_persistent(const DProg &prog, const DInst &inst, const Tiling 
                              const Scratch &scr, const RpcRing &rpc, hipStream_t s,
                              const BatchTable *batch = nullptr, bool fused = false);
 int persistent_capacity(const DProg &prog, const Tiling &t, int num_cu, bool fused = false);
-// Wavefront work items of a fused pass of m sweeps over an n-sided grid.
-int64_t fused_items(int kind, int64_t n, int m);
+// Wavefront work items of a fused pass of m sweeps over an n-sided grid, its
+// threads per workgroup, and the planes per segment of a 3D pass.
+int64_t fused_items(int kind, int64_t n, int m, int32_t zlen);
+int fused_wg(int kind);
+int32_t fused_zlen(int64_t n, int64_t num_wg);
 // Relative time of one of its items (items of larger grids are longer).
-double fused_item_cost(int kind, int64_t n);
+double fused_item_cost(int kind, int64_t n, int32_t zlen);
 // Co-resident workgroups of the per-region kernel that runs regions of `kind`.
 int region_capacity(int kind, const Tiling &t, int num_cu);
 hipError_t launch_main(const DProg &prog, const DInst &inst, const RpcRing &rpc, const Scratch &scr,

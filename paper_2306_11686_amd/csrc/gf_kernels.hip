@@ -1290,6 +1290,7 @@ constexpr unsigned kFamHist = (1u << GF_R_HIST) | (1u << GF_R_OWNER);
 // iteration, several sweeps per pass.
 constexpr unsigned kFusedBit = 1u << 31;
 constexpr unsigned kFamFused2 = kFusedBit | (1u << GF_R_JACOBI2D);
+constexpr unsigned kFamFused3 = kFusedBit | (1u << GF_R_JACOBI3D);
 
 template <unsigned KMASK>
 constexpr int family_max_threads()
@@ -1315,6 +1316,8 @@ constexpr int persistent_min_waves()
         return 3;
     if (KMASK == kFamFused2)
         return 3;
+    if (KMASK == kFamFused3)
+        return 2;
     return 1;
 }
 
@@ -1324,17 +1327,22 @@ constexpr int persistent_min_waves()
 // stencil region reads a scalar, and the partials of the next pass go to the
 // other half. last: no barrier is needed after a pass without reductions.
 template <unsigned KMASK, int M, typename Bar>
-__device__ __forceinline__ bool fused_pass(const double *src, double *dst, int64_t n, bool red, bool last, double *part,
-                                           double *s_redw, double *s_redv, int64_t worker, int64_t G, bool first,
-                                           Bar &barrier)
+__device__ __forceinline__ bool fused_pass(const double *src, double *dst, int64_t n, int32_t zlen, bool red, bool last,
+                                           double *part, double *s_redw, double *s_redv, int64_t worker, int64_t G,
+                                           bool first, Bar &barrier)
 {
-    constexpr int OP = GF_OP_SUM;
+    constexpr bool k3D = KMASK == kFamFused3;
+    constexpr int OP = k3D ? GF_OP_MAX : GF_OP_SUM;
     const int nw = blockDim.x / kWave;
     const int wv = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
-    const int64_t items = j2f_geom(n, M).items;
+    // 2D: a wavefront takes an item; 3D: a workgroup, one part per wavefront
+    const int64_t items = k3D ? j3f_geom(n, M, zlen).items * kJ3fWaves : j2f_geom(n, M).items;
     for (int64_t it = worker * nw + wv; it < items; it += G * nw) {
         double acc[M];
-        j2f_item<M>(src, dst, n, uniform_i64(it), acc);
+        if constexpr (k3D)
+            j3f_item<M>(src, dst, n, zlen, uniform_i64(it) / kJ3fWaves, wv, acc);
+        else
+            j2f_item<M>(src, dst, n, uniform_i64(it), acc);
         if (red) {
             wave_reduce_m<OP, M>(acc);
             if ((threadIdx.x & (kWave - 1)) == 0)
@@ -1352,8 +1360,8 @@ __device__ __forceinline__ bool fused_pass(const double *src, double *dst, int64
     return true;
 }
 
-// The serial steps of a fused program's body, by one wavefront, in
-// registers: lane k holds step k of the body, lane i scalar variable i
+// The serial steps of a fused pass, by one wavefront, in registers: lane k
+// holds step k of the body, lane i scalar variable i
 // (sweep by sweep every step waits for loads of its fields and for LDS,
 // about 0.5 us each; here a pass of seven 2D iterations takes about 1 us).
 struct SerialWave {
@@ -1430,11 +1438,13 @@ struct SerialWave {
 // the last worker, which has the fewest work items.
 template <unsigned KMASK, typename Bar>
 __device__ __forceinline__ void fused_program(const DProg &prog, const DInst &inst, double *s_scal, void **s_arr,
-                                              const Scratch &scr, const RpcRing &rpc, int64_t part_off,
-                                              int64_t worker, int64_t G, Bar &barrier)
+                                              const Scratch &scr, const RpcRing &rpc, uint32_t *gline,
+                                              int64_t part_off, int32_t zlen, int64_t worker, int64_t G, Bar &barrier)
 {
-    __shared__ double s_redw[kFusedMax * (kMaxWg / kWave)];
-    __shared__ double s_redv[kFusedMax];
+    constexpr bool k3D = KMASK == kFamFused3;
+    constexpr int kMax = k3D ? kFusedMax3 : kFusedMax2;
+    __shared__ double s_redw[kMax * (kMaxWg / kWave)];
+    __shared__ double s_redv[kMax];
     const bool first = worker == G - 1;
     int rs = prog.n_pro;
     while (prog.steps[rs].kind >= 32)
@@ -1448,28 +1458,47 @@ __device__ __forceinline__ void fused_program(const DProg &prog, const DInst &in
     __syncthreads();
     const double *src = (const double *)uniform_ptr(s_arr[st.arr[0]]);
     double *dst = (double *)uniform_ptr(s_arr[st.arr[1]]);
+    bool fuse = true;
+    if constexpr (k3D) {
+        if (zlen <= 0)
+            zlen = j3f_zlen(n, kFusedMax3, G);
+        zlen = __builtin_amdgcn_readfirstlane(zlen);
+        // several sweeps per pass only where the two outer layers agree; a
+        // difference leaves this launch's epoch in the group line's word
+        uint32_t *word = gline + kGroupOuterWord;
+        if (!outer3_agrees(gptr(src), gptr((const double *)dst), n, worker, G))
+            __hip_atomic_store(word, scr.epoch, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        if (!barrier(nullptr))
+            return;
+        fuse = __builtin_amdgcn_readfirstlane(
+                   (int)__hip_atomic_load(word, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT)) != (int)scr.epoch;
+    }
     const bool serial = first && __builtin_amdgcn_readfirstlane(threadIdx.x / kWave) == 0;
-    SerialWave sw;
-    if (serial)
-        sw.load(prog, s_scal, s_arr);
     int parity = 0;
     for (int32_t iter = 0; iter < prog.iters;) {
         const int32_t left = prog.iters - iter;
         double *part = scr.partials + (parity ? scr.partials_cap : 0) + part_off;
-        const int m = fused_sweeps(n, left);
+        const int m = fuse ? fused_sweeps(k3D ? GF_R_JACOBI3D : GF_R_JACOBI2D, n, left) : 1;
         bool ok;
-        if (m == kFusedMax)
-            ok = fused_pass<KMASK, kFusedMax>(src, dst, n, red, false, part, s_redw, s_redv, worker, G, first, barrier);
+        if (!k3D && m == kMax)
+            ok = fused_pass<KMASK, kMax>(src, dst, n, zlen, red, false, part, s_redw, s_redv, worker, G, first,
+                                         barrier);
         else if (m == 3)
-            ok = fused_pass<KMASK, 3>(src, dst, n, red, false, part, s_redw, s_redv, worker, G, first, barrier);
+            ok = fused_pass<KMASK, 3>(src, dst, n, zlen, red, false, part, s_redw, s_redv, worker, G, first, barrier);
         else
-            ok = fused_pass<KMASK, 1>(src, dst, n, red, left == 1, part, s_redw, s_redv, worker, G, first, barrier);
+            ok = fused_pass<KMASK, 1>(src, dst, n, zlen, red, left == 1, part, s_redw, s_redv, worker, G, first,
+                                      barrier);
         if (!ok)
             return;
         parity ^= 1;
-        if (serial)
+        if (serial) {
+            SerialWave sw;
+            sw.load(prog, s_scal, s_arr);
             for (int j = 0; j < m; ++j)
                 sw.iteration(prog, iter + j, red, st.red_op, red ? s_redv[j] : 0.0, s_scal, rpc, scr.error);
+            if (threadIdx.x < GF_MAX_SCALARS)
+                s_scal[threadIdx.x] = sw.scal;
+        }
         // an odd number of sweeps: the grids have changed places
         const double *t = src;
         src = dst;
@@ -1477,7 +1506,7 @@ __device__ __forceinline__ void fused_program(const DProg &prog, const DInst &in
         iter += m;
     }
     if (serial && threadIdx.x < GF_MAX_SCALARS)
-        inst.scal[threadIdx.x] = sw.scal;
+        inst.scal[threadIdx.x] = s_scal[threadIdx.x];
 }
 
 template <unsigned KMASK, int TY, int PF>
@@ -1614,7 +1643,7 @@ __global__ void __launch_bounds__(family_max_threads<KMASK>())
     }
 
     if constexpr ((KMASK & kFusedBit) != 0) {
-        fused_program<KMASK>(prog, inst, s_scal, s_arr, scr, rpc, be.part_off, worker, G, barrier);
+        fused_program<KMASK>(prog, inst, s_scal, s_arr, scr, rpc, gline, be.part_off, t.tile_z, worker, G, barrier);
         return;
     }
 
@@ -2158,6 +2187,7 @@ static PersistentFn persistent_fn(unsigned fam, int ty, int pf)
 {
     switch (fam) {
     case kFamFused2: return k_persistent<kFamFused2, 1, 1>;
+    case kFamFused3: return k_persistent<kFamFused3, 1, 1>;
     case kFamJ3: return persistent_for_ty<kFamJ3>(ty, pf);
     case kFamJ2: return persistent_for_ty<kFamJ2>(1, 1);
     case kFamVec: return persistent_for_ty<kFamVec>(1, 1);
@@ -2214,25 +2244,28 @@ int region_capacity(int kind, const Tiling &t, int num_cu)
     return per_cu * num_cu;
 }
 
-int64_t fused_items(int kind, int64_t n, int m)
+int64_t fused_items(int kind, int64_t n, int m, int32_t zlen)
 {
-    (void)kind;
-    return j2f_geom(n, m).items;
+    return kind == GF_R_JACOBI3D ? j3f_geom(n, m, zlen).items * kJ3fWaves : j2f_geom(n, m).items;
 }
 
-double fused_item_cost(int kind, int64_t n)
+int fused_wg(int kind) { return kind == GF_R_JACOBI3D ? kFusedWg3 : kFusedWg2; }
+
+int32_t fused_zlen(int64_t n, int64_t num_wg) { return j3f_zlen(n, kFusedMax3, num_wg); }
+
+double fused_item_cost(int kind, int64_t n, int32_t zlen)
 {
-    (void)kind;
+    if (kind == GF_R_JACOBI3D)
+        return zlen + 2 * kFusedMax3;
     // stage-rows of a full pass, and three rows' worth of start
-    const double m = kFusedMax;
-    return j2f_geom(n, kFusedMax).rows * m + m * (m - 1) + 3 * m;
+    const double m = kFusedMax2;
+    return j2f_geom(n, kFusedMax2).rows * m + m * (m - 1) + 3 * m;
 }
 
 // The fused-sweep family of a program (one stencil region per iteration).
 static unsigned fused_family(const DProg &prog)
 {
-    (void)prog;
-    return kFamFused2;
+    return (program_kinds(prog) >> GF_R_JACOBI3D) & 1u ? kFamFused3 : kFamFused2;
 }
 
 int persistent_capacity(const DProg &prog, const Tiling &t, int num_cu, bool fused)

@@ -134,3 +134,70 @@ def test_fused_2d_batch_in_groups_on_one_xcd_and_in_order(gfx, monkeypatch):
                 assert np.array_equal(host(us[i]), ref[i][0]), (align, i)
                 assert np.array_equal(host(ws[i]), ref[i][1]), (align, i)
                 assert np.all(np.abs(host(rs[i]) - ref[i][2]) <= 1e-12 * ref[i][2]), (align, i)
+
+
+# sides: one and several 128-column items, odd and even, rows and planes that
+# do not fill the last tile or segment; sweeps: every remainder of the pass
+# lengths three and one
+@pytest.mark.parametrize("n,sweeps", [(3, 4), (4, 5), (13, 7), (14, 6), (15, 8), (32, 4), (65, 9), (128, 5), (129, 10),
+                                      (137, 7), (250, 5), (257, 6)])
+def test_fused_3d_equals_sweep_by_sweep(gfx, n, sweeps):
+    import paper_2306_11686_amd as gf
+    from paper_2306_11686_amd import programs
+    print(f"fused 3d n={n} sweeps={sweeps}", flush=True)
+    u0 = gi.um11(13, 32, np.arange(n ** 3, dtype=np.uint64)).reshape(n, n, n)
+    prog = programs.jacobi3d(sweeps)
+    given = gf.Launch.make(wg_size=256, tile_y=4, tile_z=32)
+    for w0 in (u0, _outer_differs(u0, 14)):   # the second: outer layers differ, one sweep per pass
+        a = _run(gfx, prog, u0, w0, sweeps, None)
+        b = _run(gfx, prog, u0, w0, sweeps, given)
+        for k in range(3):
+            assert np.array_equal(a[k], b[k]), k
+        assert a[3][0] == b[3][0]
+
+
+@pytest.mark.parametrize("face", range(6))
+def test_fused_3d_notices_one_differing_outer_value(gfx, face):
+    """One value of one face differs between the two buffers (by its sign
+    bit alone): the run has to take the sweep-by-sweep course."""
+    import paper_2306_11686_amd as gf
+    from paper_2306_11686_amd import programs
+    n, sweeps = 40, 7
+    u0 = gi.um11(15, 32, np.arange(n ** 3, dtype=np.uint64)).reshape(n, n, n)
+    w0 = u0.copy()
+    at = [17, 23, 29]
+    at[face // 2] = 0 if face % 2 == 0 else n - 1
+    w0[tuple(at)] = -w0[tuple(at)]
+    prog = programs.jacobi3d(sweeps)
+    a = _run(gfx, prog, u0, w0, sweeps, None)
+    b = _run(gfx, prog, u0, w0, sweeps, gf.Launch.make(wg_size=256, tile_y=4, tile_z=32))
+    assert np.array_equal(a[0], b[0]) and np.array_equal(a[1], b[1]) and np.array_equal(a[2], b[2])
+
+
+def test_fused_3d_grid_sizes_no_reduction_and_batch(gfx):
+    import torch
+    import paper_2306_11686_amd as gf
+    from paper_2306_11686_amd import programs
+    n, sweeps = 70, 8
+    u0 = gi.grid3d(n, seed=16)
+    given = gf.Launch.make(wg_size=256, tile_y=4, tile_z=32)
+    prog = programs.jacobi3d(sweeps)
+    b = _run(gfx, prog, u0, u0, sweeps, given)
+    for nwg in (1, 3, 130, 255):
+        a = _run(gfx, prog, u0, u0, sweeps, gf.Launch.make(num_wg=nwg, xcd_remap=nwg % 2))
+        assert a[4]["num_wg"] == nwg
+        assert all(np.array_equal(a[k], b[k]) for k in range(3))
+    plain = programs.jacobi3d(sweeps, reduce=False)
+    a = _run(gfx, plain, u0, u0, sweeps, None)
+    assert np.array_equal(a[0], b[0]) and np.array_equal(a[1], b[1])
+    sides = [33, 70, 8, 131]
+    grids = [gi.grid3d(m, seed=17 + i) for i, m in enumerate(sides)]
+    ref = [_run(gfx, prog, g, g, sweeps, given) for g in grids]
+    us, ws = [dev(g) for g in grids], [dev(g) for g in grids]
+    rs = [torch.zeros(sweeps, dtype=torch.float64, device="cuda") for _ in sides]
+    gfx.run(prog, [gf.Instance.make({0: u, 1: w, 2: r}, scalars(), ip=(m,))
+                   for u, w, r, m in zip(us, ws, rs, sides)], mode=gf.GF_EXEC_PERSISTENT)
+    gfx.sync()
+    for i in range(len(sides)):
+        assert np.array_equal(host(us[i]), ref[i][0]) and np.array_equal(host(ws[i]), ref[i][1])
+        assert np.array_equal(host(rs[i]), ref[i][2])
