@@ -1086,19 +1086,55 @@ unsigned program_region_mask(const DProg &p)
     return m;
 }
 
-// Defaults: 3D stencil 256-wide rows x 8 rows x 64-plane segments; 2D
-// stencil single-row tiles (the 2D grid is small and latency-bound);
-// streaming regions 4 elements per thread.
-Tiling choose_tiling(const DProg &p, const gf_launch *l)
+// Largest grid side of the program's stencil regions over the instances (0:
+// no stencil or no instance given).
+int64_t stencil_side(const DProg &p, const gf_instance *inst, int n_inst)
+{
+    int64_t n = 0;
+    for (int k = 0; k < p.n_steps; ++k)
+        if (p.steps[k].kind == GF_R_JACOBI2D || p.steps[k].kind == GF_R_JACOBI3D)
+            for (int i = 0; inst && i < n_inst; ++i)
+                n = std::max<int64_t>(n, std::min<int64_t>(inst[i].ip[p.steps[k].np], 1 << 20));
+    return n;
+}
+
+// Defaults. Streaming regions: 4 elements per thread. Stencils follow the
+// grid side n, so that small grids still give every CU several wavefronts
+// (one launch per sweep, us per sweep, one fixed tile against these rules:
+// 3D 256 x 8 rows x 64 planes, n = 65 / 129 / 257 / 450 / 512: 165 / 173 /
+// 186 / 321 / 450 and 14 / 23 / 75 / 278 / 412; 2D 256 x 16 rows, n = 64 /
+// 512 / 2048: 12.8 / 13.1 / 22.6 and 9.5 / 10.2 / 22.6):
+// - workgroups no wider than a row (two columns per thread);
+// - 2D: n / 128 rows per segment as a power of two, between 2 and 32;
+// - 3D: 2 rows per tile and z split into the segments that give 3,840
+//   wavefronts (a segment reads two planes more than it writes: no shorter
+//   than 8 planes, 4 below side 96); from side 416, where the rows fill
+//   whole workgroups and halo rows cost more than wavefronts gain, 4 rows and
+//   2,048 wavefronts (n = 450: 278 against 330 us), but for sides that are a
+//   multiple of 64, whose rows start on the same channels.
+// Without an instance (the persistent capacity of a program): 3D tiles of 8
+// rows, the largest the tuner takes.
+Tiling choose_tiling(const DProg &p, const gf_launch *l, const gf_instance *inst = nullptr, int n_inst = 0)
 {
     Tiling t;
     std::memset(&t, 0, sizeof t);
     const unsigned m = program_region_mask(p);
+    const bool is3 = m & (1u << GF_R_JACOBI3D), is2 = m & (1u << GF_R_JACOBI2D);
+    // a launch that names a tile keeps the fixed defaults for what it leaves
+    // out (the tuner's and the predictor's shapes are meant that way)
+    const bool named = l && (l->wg_size || l->tile_y || l->tile_z);
+    const int64_t n = named ? 0 : stencil_side(p, inst, n_inst);
     t.wg_size = program_is_hist_family(p) ? 1024 : 256;
+    if (n > 0 && (m & ~((1u << GF_R_JACOBI3D) | (1u << GF_R_JACOBI2D))) == 0)
+        t.wg_size = (int32_t)std::min<int64_t>(256, std::max<int64_t>(64, ((n + 1) / 2 + 63) / 64 * 64));
     if (program_is_hist_family(p))
         t.items = 8;
-    t.tile_y = (m & (1u << GF_R_JACOBI3D)) ? 8 : ((m & (1u << GF_R_JACOBI2D)) ? 16 : 1);
-    t.tile_z = 64;
+    const bool tall = n >= 416 && n % 64 != 0;
+    t.tile_y = is3 ? 8 : (is2 ? 16 : 1);
+    if (n > 0)
+        t.tile_y = is3 && tall ? 4 : 2;
+    for (int64_t r = 512; n > 0 && is2 && !is3 && r <= n && t.tile_y < 32; r *= 2)
+        t.tile_y *= 2;
     t.prefetch = 1;
     if (!program_is_hist_family(p))
         t.items = 4;
@@ -1108,14 +1144,21 @@ Tiling choose_tiling(const DProg &p, const gf_launch *l)
             t.wg_size = l->wg_size;
         if (l->tile_y)
             t.tile_y = l->tile_y;
-        if (l->tile_z)
-            t.tile_z = l->tile_z;
         if (l->items)
             t.items = l->items;
         t.xcd_remap = l->xcd_remap;
         if (l->prefetch)
             t.prefetch = l->prefetch;
     }
+    t.tile_z = 64;
+    if (n > 2 && t.wg_size >= kWave && t.tile_y > 0) {
+        const int64_t tiles = ((n + 2 * t.wg_size - 1) / (2 * t.wg_size)) * ((n - 2 + t.tile_y - 1) / t.tile_y);
+        int64_t segs = (tall ? 2048 : 3840) / (t.wg_size / kWave) / tiles;
+        segs = std::max<int64_t>(1, std::min<int64_t>(segs, (n - 2) / (n < 96 ? 4 : 8)));
+        t.tile_z = (int32_t)std::min<int64_t>((n - 2 + segs - 1) / segs, 1 << 20);
+    }
+    if (l && l->tile_z)
+        t.tile_z = l->tile_z;
     return t;
 }
 
@@ -2060,7 +2103,7 @@ static gf_status region_run(gf_ctx *ctx, const gf_program *prog, const gf_instan
             }
         }
     }
-    Tiling t = choose_tiling(p, launch);
+    Tiling t = choose_tiling(p, launch, inst, n_inst);
     if ((st = check_tiling(ctx, p, t)) != GF_OK)
         return st;
     // per instance: its own rows per tile when a shape gives them (the 3D
@@ -2477,7 +2520,7 @@ bool launch_runnable(gf_ctx *ctx, const DProg &p, const gf_instance *inst, int n
 {
     const std::string saved = ctx->err;
     bool ok = true;
-    const Tiling t = choose_tiling(p, &l);
+    const Tiling t = choose_tiling(p, &l, inst, n_inst);
     if (check_tiling(ctx, p, t) != GF_OK)
         ok = false;
     for (int i = 0; ok && i < n_inst; ++i)
@@ -2970,7 +3013,7 @@ int32_t gf_tune_batched(gf_ctx *ctx, const gf_program *prog, const gf_instance *
                 seg_of[kv.first] = bs;
                 // workgroup-milliseconds per work item at the chosen rows
                 double items = 0.0;
-                Tiling tt = choose_tiling(p, &common);
+                Tiling tt = choose_tiling(p, &common, inst, n_inst);
                 tt.tile_y = bs;
                 for (int i : kv.second)
                     items += (double)std::max<int64_t>(1, max_items(p, inst[i], tt));
@@ -2982,7 +3025,7 @@ int32_t gf_tune_batched(gf_ctx *ctx, const gf_program *prog, const gf_instance *
                 std::vector<double> wv(n_inst, 0.0);
                 for (int i = 0; i < n_inst; ++i) {
                     per[i].tile_y = seg_of[cls[i]];
-                    Tiling tt = choose_tiling(p, &common);
+                    Tiling tt = choose_tiling(p, &common, inst, n_inst);
                     tt.tile_y = per[i].tile_y;
                     const double items = (double)std::max<int64_t>(1, max_items(p, inst[i], tt));
                     wv[i] = variant == 0 ? items * cost_of[cls[i]] : items;

@@ -22,11 +22,13 @@ struct StencilGeom {
     int64_t nxc, nyt, nzs;  // x chunks, y tiles, z segments
 };
 
+// 3D: a work item is a chunk of columns (two per thread) times tile_y rows
+// times a segment of tile_z planes.
 __host__ __device__ inline StencilGeom j3_geom(int64_t n, const Tiling &t)
 {
     StencilGeom g;
     const int64_t interior = n > 2 ? n - 2 : 0;
-    g.nxc = cdiv(n, t.wg_size);
+    g.nxc = cdiv(n, 2 * (int64_t)t.wg_size);
     g.nyt = cdiv(interior, t.tile_y);
     g.nzs = cdiv(interior, t.tile_z);
     return g;
@@ -34,15 +36,7 @@ __host__ __device__ inline StencilGeom j3_geom(int64_t n, const Tiling &t)
 
 typedef double gf_d2 __attribute__((ext_vector_type(2)));
 
-__host__ __device__ inline StencilGeom j3v2_geom(int64_t n, const Tiling &t)
-{
-    StencilGeom g = j3_geom(n, t);
-    g.nxc = cdiv(n, 2 * (int64_t)t.wg_size);
-    return g;
-}
-
-// 2D: a work item is a chunk of columns (two per thread for even n, one for
-// odd n) times a segment of tile_y rows that the workgroup marches through.
+// 2D: a work item is a chunk of columns (two per thread) times a segment of tile_y rows that the workgroup marches through.
 __host__ __device__ inline StencilGeom j2_geom(int64_t n, const Tiling &t)
 {
     StencilGeom g;
@@ -81,7 +75,7 @@ int64_t region_items(const DStep &st, int64_t n, const Tiling &t)
 {
     switch (st.kind) {
     case GF_R_JACOBI3D: {
-        StencilGeom g = (n & 1) ? j3_geom(n, t) : j3v2_geom(n, t);
+        StencilGeom g = j3_geom(n, t);
         return g.nxc * g.nyt * g.nzs;
     }
     case GF_R_JACOBI2D: {
@@ -106,7 +100,7 @@ __device__ inline int64_t region_items_dev(const DStep &st, int64_t n, const Til
 {
     switch (st.kind) {
     case GF_R_JACOBI3D: {
-        StencilGeom g = (n & 1) ? j3_geom(n, t) : j3v2_geom(n, t);
+        StencilGeom g = j3_geom(n, t);
         return g.nxc * g.nyt * g.nzs;
     }
     case GF_R_JACOBI2D: {
@@ -130,86 +124,6 @@ __device__ inline int64_t region_items_dev(const DStep &st, int64_t n, const Til
 // returns the thread's private reduction value (identity if none).
 // ---------------------------------------------------------------------------
 
-// 3D 7-point Jacobi, 2.5-D blocking: the workgroup owns a (row chunk of
-// wg_size x) x (TY rows) column of the grid and marches along z over one
-// segment. Each thread keeps its column of planes z-1, z, z+1 in registers,
-// so every value of u is fetched from memory once per tile plus the two
-// y-halo rows and two z-halo planes; x neighbours are re-read from L1.
-template <int TY>
-__device__ __forceinline__ double j3_item(const double *u_, double *w_, int64_t n, int64_t item, const Tiling &t,
-                                          bool want_red)
-{
-    GF_GLOBAL const double *__restrict__ u = gptr(u_);
-    GF_GLOBAL double *__restrict__ w = gptr(w_);
-    const StencilGeom g = j3_geom(n, t);
-    const int64_t xc = item % g.nxc;
-    const int64_t rest = item / g.nxc;
-    const int64_t yt = rest % g.nyt;
-    const int64_t zs = rest / g.nyt;
-    const int64_t x = xc * blockDim.x + threadIdx.x;
-    const int64_t y0 = 1 + yt * TY;
-    const int ny = (int)(n - 1 - y0 < TY ? n - 1 - y0 : TY);
-    const int64_t z0 = 1 + zs * t.tile_z;
-    const int64_t z1 = (z0 + t.tile_z < n - 1) ? z0 + t.tile_z : n - 1;
-    const bool xload = x < n;
-    const bool xin = x >= 1 && x <= n - 2;
-    const int64_t SY = n, SZ = n * n;
-    const double c6 = 1.0 / 6.0;
-    double mx = -INFINITY;
-    double pm[TY], pc[TY + 2], pn[TY + 2];
-#pragma unroll
-    for (int r = 0; r < TY; ++r)
-        pm[r] = 0.0;
-#pragma unroll
-    for (int r = 0; r < TY + 2; ++r)
-        pc[r] = pn[r] = 0.0;
-    if (xload) {
-        GF_GLOBAL const double *b = u + (z0 - 1) * SZ + y0 * SY + x;
-#pragma unroll
-        for (int r = 0; r < TY; ++r)
-            if (r < ny)
-                pm[r] = b[r * SY];
-        b = u + z0 * SZ + (y0 - 1) * SY + x;
-#pragma unroll
-        for (int r = 0; r < TY + 2; ++r)
-            if (r < ny + 2)
-                pc[r] = b[r * SY];
-    }
-    for (int64_t z = z0; z < z1; ++z) {
-        if (xload) {
-            GF_GLOBAL const double *b = u + (z + 1) * SZ + (y0 - 1) * SY + x;
-#pragma unroll
-            for (int r = 0; r < TY + 2; ++r)
-                if (r < ny + 2)
-                    pn[r] = b[r * SY];
-        }
-        if (xin) {
-            GF_GLOBAL const double *row = u + z * SZ + y0 * SY + x;
-            GF_GLOBAL double *out = w + z * SZ + y0 * SY + x;
-#pragma unroll
-            for (int r = 0; r < TY; ++r) {
-                if (r < ny) {
-                    const double xl = row[r * SY - 1];
-                    const double xr = row[r * SY + 1];
-                    const double v = (((xl + xr) + (pc[r] + pc[r + 2])) + (pm[r] + pn[r + 1])) * c6;
-                    __builtin_nontemporal_store(v, out + r * SY);
-                    if (want_red) {
-                        const double d = fabs(v - pc[r + 1]);
-                        mx = d > mx ? d : mx;
-                    }
-                }
-            }
-        }
-#pragma unroll
-        for (int r = 0; r < TY; ++r)
-            pm[r] = pc[r + 1];
-#pragma unroll
-        for (int r = 0; r < TY + 2; ++r)
-            pc[r] = pn[r];
-    }
-    return mx;
-}
-
 // Lane shifts across the whole wavefront (DPP wave_shr:1 / wave_shl:1):
 // lane i receives lane i-1's (shr) or lane i+1's (shl) value; the lane at
 // the wavefront edge receives 0 and is fixed up by the caller.
@@ -232,7 +146,7 @@ __device__ __forceinline__ double wave_shl1(double v)
 
 namespace gf {
 
-// 3D 7-point Jacobi for even n: each thread owns an x-pair (one 16-byte load
+// 3D 7-point Jacobi: each thread owns an x-pair (one 16-byte load
 // per row), a column of TY rows, and marches z. x-neighbours come from the
 // adjacent lanes by DPP shifts; the edge lanes of each wavefront swap their
 // values through LDS once per plane (which also keeps the workgroup's
@@ -244,14 +158,22 @@ namespace gf {
 // loaded with the streaming hint so they do not evict the halo rows that the
 // adjacent tile is about to read. FULL tiles (all TY rows present) run
 // without per-row guards; lanes past the row end load a clamped in-bounds
-// address and store nothing.
-template <int TY>
-__device__ __forceinline__ gf_d2 ld_row(GF_GLOBAL const double *p, int r)
+// address and store nothing. For odd n (ODD) the rows start on 8-byte
+// boundaries, which the 16-byte accesses take, and column n-1 falls to a
+// thread of its own, which loads the pair (n-2, n-1) and keeps the second.
+template <int TY, bool ODD>
+__device__ __forceinline__ gf_d2 ld_row(GF_GLOBAL const double *p, int r, bool lone)
 {
+    typedef typename std::conditional<ODD, gf_d2u, gf_d2>::type A;
+    gf_d2 v;
     // r indexes rows y0-1 .. y0+TY; rows y0-1, y0, y0+TY-1, y0+TY are shared
     if (r >= 2 && r <= TY - 1)
-        return __builtin_nontemporal_load((GF_GLOBAL const gf_d2 *)p);
-    return *(GF_GLOBAL const gf_d2 *)p;
+        v = __builtin_nontemporal_load((GF_GLOBAL const A *)p);
+    else
+        v = *(GF_GLOBAL const A *)p;
+    if constexpr (ODD)
+        v.x = lone ? v.y : v.x;
+    return v;
 }
 
 // One tile of planes [z0, z1). PF (1 or 2) planes ahead of the computed
@@ -259,7 +181,7 @@ __device__ __forceinline__ gf_d2 ld_row(GF_GLOBAL const double *p, int r)
 // for PF = 2, z+2, while the next plane is requested at the top of the step.
 // The two depths are written out separately: folding them into one ring
 // array cost a fifth of the bandwidth at depth 1 (measured).
-template <int TY, int PF, bool FULL>
+template <int TY, int PF, bool FULL, bool ODD>
 __device__ __forceinline__ double j3v2_tile(GF_GLOBAL const double *__restrict__ u, GF_GLOBAL double *__restrict__ w,
                                             int64_t n, int64_t x, int64_t y0, int ny, int64_t z0, int64_t z1,
                                             bool want_red)
@@ -270,8 +192,9 @@ __device__ __forceinline__ double j3v2_tile(GF_GLOBAL const double *__restrict__
     const int wv = threadIdx.x / kWave;
     const int nw = blockDim.x / kWave;
     const bool xload = x < n;
-    const int64_t xs = xload ? x : n - 2;          // clamped load column (even, in bounds)
-    const bool in0 = xload && x >= 1;              // column x is interior (x <= n-2 as x is even)
+    const int64_t xs = x <= n - 2 ? x : n - 2;     // clamped load column
+    const bool lone = ODD && x == n - 1;           // holds column n-1 alone
+    const bool in0 = x >= 1 && x <= n - 2;         // column x is interior
     const bool in1 = xload && x + 1 <= n - 2;      // column x+1 is interior
     const bool gather_l = wv == 0 && lane == 0 && xs >= 1;
     const bool gather_r = wv == nw - 1 && lane == kWave - 1 && xs + 2 <= n - 1;
@@ -285,26 +208,26 @@ __device__ __forceinline__ double j3v2_tile(GF_GLOBAL const double *__restrict__
     GF_GLOBAL const double *col = u + (y0 - 1) * SY + xs;  // row y0-1 of plane 0
 #pragma unroll
     for (int r = 0; r < TY; ++r)
-        pm[r] = (FULL || r < ny) ? ld_row<TY>(col + (z0 - 1) * SZ + (r + 1) * SY, r + 1) : zero2;
+        pm[r] = (FULL || r < ny) ? ld_row<TY, ODD>(col + (z0 - 1) * SZ + (r + 1) * SY, r + 1, lone) : zero2;
     // planes z0 and z0+1 exist (z0+1 <= z1 <= n-1); z0+2 may be past the grid
 #pragma unroll
     for (int r = 0; r < TY + 2; ++r) {
-        pc[r] = (FULL || r < ny + 2) ? ld_row<TY>(col + z0 * SZ + r * SY, r) : zero2;
-        pn[r] = (FULL || r < ny + 2) ? ld_row<TY>(col + (z0 + 1) * SZ + r * SY, r) : zero2;
+        pc[r] = (FULL || r < ny + 2) ? ld_row<TY, ODD>(col + z0 * SZ + r * SY, r, lone) : zero2;
+        pn[r] = (FULL || r < ny + 2) ? ld_row<TY, ODD>(col + (z0 + 1) * SZ + r * SY, r, lone) : zero2;
         pf[r] = zero2;
     }
     if constexpr (PF == 2) {
         const bool have = z0 + 2 <= z1;
 #pragma unroll
         for (int r = 0; r < TY + 2; ++r)
-            pa[r] = (have && (FULL || r < ny + 2)) ? ld_row<TY>(col + (z0 + 2) * SZ + r * SY, r) : zero2;
+            pa[r] = (have && (FULL || r < ny + 2)) ? ld_row<TY, ODD>(col + (z0 + 2) * SZ + r * SY, r, lone) : zero2;
     }
     for (int64_t z = z0; z < z1; ++z) {
         if (z + 1 + PF <= z1) {
 #pragma unroll
             for (int r = 0; r < TY + 2; ++r)
                 if (FULL || r < ny + 2)
-                    pf[r] = ld_row<TY>(col + (z + 1 + PF) * SZ + r * SY, r);
+                    pf[r] = ld_row<TY, ODD>(col + (z + 1 + PF) * SZ + r * SY, r, lone);
         }
         const int par = (int)(z & 1);
         if (lane == 0) {
@@ -349,7 +272,8 @@ __device__ __forceinline__ double j3v2_tile(GF_GLOBAL const double *__restrict__
                 v.x = (((xl + c.y) + (pc[r].x + pc[r + 2].x)) + (pm[r].x + pn[r + 1].x)) * c6;
                 v.y = (((c.x + xr) + (pc[r].y + pc[r + 2].y)) + (pm[r].y + pn[r + 1].y)) * c6;
                 if (in0 && in1) {
-                    __builtin_nontemporal_store(v, (GF_GLOBAL gf_d2 *)(out + r * SY));
+                    typedef typename std::conditional<ODD, gf_d2u, gf_d2>::type A;
+                    __builtin_nontemporal_store(v, (GF_GLOBAL A *)(out + r * SY));
                 } else if (in0) {
                     out[r * SY] = v.x;
                 } else if (in1) {
@@ -384,7 +308,7 @@ template <int TY, int PF>
 __device__ __forceinline__ double j3v2_item(const double *u_, double *w_, int64_t n, int64_t item, const Tiling &t,
                                             bool want_red)
 {
-    const StencilGeom g = j3v2_geom(n, t);
+    const StencilGeom g = j3_geom(n, t);
     const int64_t xc = item % g.nxc;
     const int64_t rest = item / g.nxc;
     const int64_t yt = rest % g.nyt;
@@ -394,9 +318,14 @@ __device__ __forceinline__ double j3v2_item(const double *u_, double *w_, int64_
     const int ny = (int)(n - 1 - y0 < TY ? n - 1 - y0 : TY);
     const int64_t z0 = 1 + zs * t.tile_z;
     const int64_t z1 = (z0 + t.tile_z < n - 1) ? z0 + t.tile_z : n - 1;
+    if (n & 1) {
+        if (ny == TY)
+            return j3v2_tile<TY, PF, true, true>(gptr(u_), gptr(w_), n, x, y0, ny, z0, z1, want_red);
+        return j3v2_tile<TY, PF, false, true>(gptr(u_), gptr(w_), n, x, y0, ny, z0, z1, want_red);
+    }
     if (ny == TY)
-        return j3v2_tile<TY, PF, true>(gptr(u_), gptr(w_), n, x, y0, ny, z0, z1, want_red);
-    return j3v2_tile<TY, PF, false>(gptr(u_), gptr(w_), n, x, y0, ny, z0, z1, want_red);
+        return j3v2_tile<TY, PF, true, false>(gptr(u_), gptr(w_), n, x, y0, ny, z0, z1, want_red);
+    return j3v2_tile<TY, PF, false, false>(gptr(u_), gptr(w_), n, x, y0, ny, z0, z1, want_red);
 }
 
 // 2D 5-point Jacobi. The workgroup owns a chunk of columns and marches down
@@ -1016,9 +945,7 @@ __device__ __forceinline__ double region_item(const DStep &st, void *const *op, 
     switch (st.kind) {
     case GF_R_JACOBI3D:
         if constexpr ((KMASK >> GF_R_JACOBI3D) & 1u) {
-            if ((n & 1) == 0)
-                return j3v2_item<TY, PF>((const double *)op[0], (double *)op[1], n, item, t, red);
-            return j3_item<TY>((const double *)op[0], (double *)op[1], n, item, t, red);
+            return j3v2_item<TY, PF>((const double *)op[0], (double *)op[1], n, item, t, red);
         }
         break;
     case GF_R_JACOBI2D:
