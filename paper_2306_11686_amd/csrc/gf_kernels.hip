@@ -50,7 +50,7 @@ __host__ __device__ inline StencilGeom j2_geom(int64_t n, const Tiling &t)
 __host__ __device__ inline int64_t chunk_elems(const Tiling &t) { return (int64_t)t.wg_size * t.items; }
 
 // SpMV rows per work item: half the workgroup, so a block of a stencil-like
-// matrix (<= 30 nonzeros per row) fits the LDS product tile.
+// matrix (<= 30 nonzeros per row) fits the LDS product slots.
 __host__ __device__ inline int64_t spmv_rows(const Tiling &t) { return t.wg_size / 2; }
 
 // Histogram work: chunks of wg_size * items * 4 keys (each thread reads
@@ -444,31 +444,37 @@ __device__ __forceinline__ double j2_item(const double *u_, double *w_, int64_t 
     return j2m_seg<false>(gptr(u_), gptr(w_), n, x, y0, y1, want_red);
 }
 
-// CSR SpMV over a block of wg_size/2 rows (CSR-stream): the block's products
-// val[k] * x[col[k]] are formed by a coalesced pass over its nonzeros into
-// LDS (eight gathers in flight per thread), then each of the first R threads
-// sums its own row serially in stored column order, exactly as the legacy
-// loop does (same products, same order, no contraction). Blocks with more
-// nonzeros than the LDS tile fall back to one thread per row.
-// 30 KiB of products per workgroup (960 per wavefront: 32 rows of up to 30
-// nonzeros): with the kernel's other LDS a workgroup stays under 32 KiB in
-// whole allocation granules, so five 256-thread workgroups fit a CU's 160 KiB.
-// At 32 KiB only four fit, and the latency-bound SpMV ran 5 % slower.
-constexpr int kSpmvLds = 3840;
-constexpr int kSpmvWaveRows = 32;     // rows per wavefront
-constexpr int kSpmvWaveLds = kSpmvLds / (kMaxWg / kWave);  // product slots per wavefront
-constexpr int kSpmvUnroll = 8;
+// CSR SpMV. A work item is wg_size / 2 consecutive rows, split into 32-row
+// slices: one slice per wavefront. The slice's nonzeros are read coalesced,
+// four adjacent ones per lane, their products go to the wavefront's own part
+// of the LDS, and one lane per row adds them serially in stored column order,
+// exactly as the legacy loop does (same products, same order, no
+// contraction). Wavefronts share no LDS and never wait for each other. A
+// slice with more nonzeros than its 960 slots (30 per row) takes the direct
+// row loop (same order).
+constexpr int kSpmvLds = 3840;        // products per workgroup (30 KiB, five of them fit a CU)
+constexpr int kSpmvWaveRows = 32;
+constexpr int kSpmvWaveLds = kSpmvLds / (kMaxWg / kWave);
+constexpr int kSpmvVec = 4;           // nonzeros a lane loads per round
+constexpr int kSpmvRound = kSpmvVec * kWave;
+constexpr int kSpmvRounds = (kSpmvWaveLds + kSpmvRound - 1) / kSpmvRound;
 
-// CSR SpMV, one work item = wg_size / 2 consecutive rows, split into
-// 32-row slices, one per wavefront. A wavefront streams its slice's
-// nonzeros (coalesced col/val loads, eight in flight per lane, then the x
-// gathers) into its own LDS slice as products val * x[col]; then lane r sums
-// row r's products serially in column order (the serial loop's order, so y
-// is bit-exact). Wavefronts share no LDS and never wait for each other. A
-// slice whose nonzeros exceed its LDS share takes the direct row loop (same
-// order).
-__device__ __forceinline__ void spmv_item(const int32_t *rowptr_, const int32_t *col_, const double *val_,
-                                          const double *x_, double *y_, int64_t n, int64_t item, int64_t R)
+typedef int32_t gf_i4u __attribute__((ext_vector_type(4), aligned(4)));
+
+// This worker's items worker, worker + G, .. of the region, pipelined: the
+// next slice's columns and values are requested once this slice's products
+// are in LDS, so that they arrive while its rows are added up; its row
+// extents a step earlier, and all gathers of x go out together. The lanes at
+// a slice's end load its last four nonzeros again, so that every load is
+// inside the slice and none is conditional.
+// Bound by the unit that makes the gathers' addresses (95 % busy): the 27-point
+// matrix of a 128^3 grid (56 million gathers) took 197 us when a slice's loads followed the previous slice's sum, and takes
+// 159. One nonzero per lane and round took 162 (fewer bank conflicts, more
+// instructions); columns and values through LDS with the gathers by rows
+// took 162 to 168 (fewer cache lines per gather, twice the LDS traffic).
+__device__ __forceinline__ void spmv_region(const int32_t *rowptr_, const int32_t *col_, const double *val_,
+                                            const double *x_, double *y_, int64_t n, int64_t worker, int64_t G,
+                                            int64_t nitems, int64_t R)
 {
     __shared__ double s_prod[kSpmvLds];
     GF_GLOBAL const int32_t *__restrict__ rowptr = gptr(rowptr_);
@@ -477,67 +483,115 @@ __device__ __forceinline__ void spmv_item(const int32_t *rowptr_, const int32_t 
     GF_GLOBAL const double *__restrict__ x = gptr(x_);
     GF_GLOBAL double *__restrict__ y = gptr(y_);
     const int lane = threadIdx.x & (kWave - 1);
-    const int wv = threadIdx.x / kWave;
+    const int wv = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
     double *slot = s_prod + wv * kSpmvWaveLds;
-    const int64_t blk = item * R;
-    const int64_t blk_end = blk + R < n ? blk + R : n;
-    const int64_t a = blk + (int64_t)wv * kSpmvWaveRows;
-    if (a >= blk_end)
-        return;
-    const int64_t b = a + kSpmvWaveRows < blk_end ? a + kSpmvWaveRows : blk_end;
-    const int64_t row = a + lane;
-    const bool mine = row < b;
-    // the slice's extent and this lane's row extent, requested together
-    const int32_t k0 = rowptr[a];
-    const int32_t nnz = rowptr[b] - k0;
-    const int32_t rb = mine ? rowptr[row] : 0;
-    const int32_t re = mine ? rowptr[row + 1] : 0;
-    if (nnz <= kSpmvWaveLds) {
-        for (int32_t base = lane; base < nnz; base += kSpmvUnroll * kWave) {
-            int32_t c[kSpmvUnroll];
-            double v[kSpmvUnroll], xv[kSpmvUnroll];
+    // first row of the wavefront's slice of item it, and its rows (<= 0: none)
+    auto first_row = [&](int64_t it) -> int64_t { return it * R + (int64_t)wv * kSpmvWaveRows; };
+    auto rows_of = [&](int64_t it) -> int {
+        if (it >= nitems)
+            return 0;
+        const int64_t end = (it + 1) * R < n ? (it + 1) * R : n;
+        const int64_t m = end - first_row(it);
+        return (int)(m < kSpmvWaveRows ? m : kSpmvWaveRows);
+    };
+    // row extents: lane l holds rowptr of the slice's row l (of its end from
+    // there on)
+    auto extents = [&](int64_t it) -> int32_t {
+        const int rows = rows_of(it);
+        return rows > 0 ? rowptr[first_row(it) + (lane < rows ? lane : rows)] : 0;
+    };
+    gf_i4u c[kSpmvRounds];
+    gf_d2u v[kSpmvRounds][2];
+    // where in the slice the lane's four nonzeros of round j start
+    auto at = [&](int j, int32_t nnz) -> uint32_t {
+        const int32_t k = j * kSpmvRound + kSpmvVec * lane;
+        return (uint32_t)(k < nnz - kSpmvVec ? k : nnz - kSpmvVec);
+    };
+    auto in_lds = [](int rows, int32_t nnz) -> bool { return rows > 0 && nnz <= kSpmvWaveLds && nnz >= kSpmvVec; };
+    // one turn sums slice `it` (extents rp) while slice `nit` is requested;
+    // the first turn has nothing to sum
+    int32_t rp = 0;
+    int rows = 0;
+    int64_t it = worker - G;
+    for (;;) {
+        const int64_t nit = it + G;
+        const int nrows = rows_of(nit);
+        const int32_t rpn = extents(nit);
+        const int32_t k0 = __builtin_amdgcn_readfirstlane(rp);
+        const int32_t nnz = __builtin_amdgcn_readlane(rp, rows > 0 ? rows : 0) - k0;
+        const bool lds = in_lds(rows, nnz);
+        if (lds) {
+            double xv[kSpmvRounds][kSpmvVec];
 #pragma unroll
-            for (int j = 0; j < kSpmvUnroll; ++j) {
-                const int32_t kk = base + j * kWave;
-                c[j] = kk < nnz ? col[k0 + kk] : 0;
-                v[j] = kk < nnz ? val[k0 + kk] : 0.0;
-            }
+            for (int j = 0; j < kSpmvRounds; ++j)
+                if (j * kSpmvRound < nnz)
 #pragma unroll
-            for (int j = 0; j < kSpmvUnroll; ++j)
-                xv[j] = base + j * kWave < nnz ? x[c[j]] : 0.0;
+                    for (int q = 0; q < kSpmvVec; ++q)
+                        xv[j][q] = x[c[j][q]];
 #pragma unroll
-            for (int j = 0; j < kSpmvUnroll; ++j)
-                if (base + j * kWave < nnz)
-                    slot[base + j * kWave] = v[j] * xv[j];
+            for (int j = 0; j < kSpmvRounds; ++j)
+                if (j * kSpmvRound < nnz) {
+                    double *d = slot + at(j, nnz);
+                    d[0] = v[j][0].x * xv[j][0];
+                    d[1] = v[j][0].y * xv[j][1];
+                    d[2] = v[j][1].x * xv[j][2];
+                    d[3] = v[j][1].y * xv[j][3];
+                }
         }
-        // the wavefront's LDS writes complete before its lanes read them
-        __builtin_amdgcn_s_waitcnt(0xC07F);  // lgkmcnt(0)
-        __builtin_amdgcn_wave_barrier();
-        if (mine) {
-            const int32_t e = re - k0;
+        const int32_t kn = __builtin_amdgcn_readfirstlane(rpn);
+        const int32_t nnzn = __builtin_amdgcn_readlane(rpn, nrows > 0 ? nrows : 0) - kn;
+        if (in_lds(nrows, nnzn)) {
+#pragma unroll
+            for (int j = 0; j < kSpmvRounds; ++j)
+                if (j * kSpmvRound < nnzn)
+                    c[j] = *(GF_GLOBAL const gf_i4u *)(col + kn + at(j, nnzn));
+#pragma unroll
+            for (int j = 0; j < kSpmvRounds; ++j)
+                if (j * kSpmvRound < nnzn) {
+                    GF_GLOBAL const double *p = val + kn + at(j, nnzn);
+                    v[j][0] = *(GF_GLOBAL const gf_d2u *)p;
+                    v[j][1] = *(GF_GLOBAL const gf_d2u *)(p + 2);
+                }
+        }
+        if (rows > 0) {
+            const int32_t rb = rp - k0;
+            const int32_t re = __builtin_amdgcn_mov_dpp(rp, 0x130, 0xf, 0xf, true) - k0;  // lane l + 1's
             double acc = 0.0;
-            int32_t k = rb - k0;
-            for (; k + 8 <= e; k += 8) {
-                double p[8];
+            if (lds) {
+                __builtin_amdgcn_s_waitcnt(0xC07F);  // lgkmcnt(0): this wavefront's products are in LDS
+                __builtin_amdgcn_wave_barrier();
+                if (lane < rows) {
+                    int32_t k = rb;
+                    for (; k + 9 <= re; k += 9) {
+                        double p[9];
 #pragma unroll
-                for (int j = 0; j < 8; ++j)
-                    p[j] = slot[k + j];
+                        for (int q = 0; q < 9; ++q)
+                            p[q] = slot[k + q];
 #pragma unroll
-                for (int j = 0; j < 8; ++j)
-                    acc = acc + p[j];
+                        for (int q = 0; q < 9; ++q)
+                            acc += p[q];
+                    }
+#pragma unroll 1
+                    for (; k < re; ++k)
+                        acc += slot[k];
+                }
+                // the next slice's products may not overwrite the slots before
+                // these reads are done
+                __builtin_amdgcn_s_waitcnt(0xC07F);
+                __builtin_amdgcn_wave_barrier();
+            } else if (lane < rows) {
+#pragma unroll 1
+                for (int32_t k = rb + k0; k < re + k0; ++k)
+                    acc = acc + val[k] * x[col[k]];
             }
-            for (; k < e; ++k)
-                acc = acc + slot[k];
-            y[row] = acc;
+            if (lane < rows)
+                y[first_row(it) + lane] = acc;
         }
-        // the next item's writes to this slice wait for these reads
-        __builtin_amdgcn_s_waitcnt(0xC07F);
-        __builtin_amdgcn_wave_barrier();
-    } else if (mine) {
-        double acc = 0.0;
-        for (int32_t k = rb; k < re; ++k)
-            acc = acc + val[k] * x[col[k]];
-        y[row] = acc;
+        if (nit >= nitems)
+            break;
+        it = nit;
+        rp = rpn;
+        rows = nrows;
     }
 }
 
@@ -952,13 +1006,6 @@ __device__ __forceinline__ double region_item(const DStep &st, void *const *op, 
         if constexpr ((KMASK >> GF_R_JACOBI2D) & 1u)
             return j2_item((const double *)op[0], (double *)op[1], n, item, t, red);
         break;
-    case GF_R_SPMV:
-        if constexpr ((KMASK >> GF_R_SPMV) & 1u) {
-            spmv_item((const int32_t *)op[0], (const int32_t *)op[1], (const double *)op[2], (const double *)op[3],
-                      (double *)op[4], n, item, spmv_rows(t));
-            return 0.0;
-        }
-        break;
     case GF_R_DOT:
         if constexpr ((KMASK >> GF_R_DOT) & 1u)
             return dot_item((const double *)op[0], (const double *)op[1], n, item, t);
@@ -1245,6 +1292,8 @@ constexpr int persistent_min_waves()
         return 3;
     if (KMASK == kFamFused3)
         return 2;
+    if (((KMASK >> GF_R_SPMV) & 1u) && !((KMASK >> GF_R_JACOBI3D) & 1u))
+        return 4;
     return 1;
 }
 
@@ -1621,6 +1670,11 @@ __global__ void __launch_bounds__(family_max_threads<KMASK>())
                     hist_merge((uint32_t *)op[1], scr.hist_rows, st.mask, G, worker * blockDim.x + threadIdx.x,
                                G * blockDim.x);
                 }
+            } else if (st.kind == GF_R_SPMV) {
+                if constexpr ((KMASK >> GF_R_SPMV) & 1u)
+                    spmv_region((const int32_t *)op[0], (const int32_t *)op[1], (const double *)op[2],
+                                (const double *)op[3], (double *)op[4], n, worker, G, region_items_dev(st, n, t),
+                                spmv_rows(t));
             } else {
                 const int64_t nitems = region_items_dev(st, n, t);
                 // fold: this workgroup's max over its items, then one atomic
@@ -1751,8 +1805,15 @@ __device__ inline void run_glue(const RegionLaunch &rl, const RpcRing &rpc, int3
     }
 }
 
+template <unsigned KMASK>
+constexpr int region_min_waves()
+{
+    return (KMASK >> GF_R_SPMV) & 1u ? 4 : 1;
+}
+
 template <unsigned KMASK, int TY, int PF>
-__global__ void __launch_bounds__(family_max_threads<KMASK>()) k_region(RegionLaunch rl, Tiling t, Scratch scr,
+__global__ void __launch_bounds__(family_max_threads<KMASK>())
+    __attribute__((amdgpu_waves_per_eu(region_min_waves<KMASK>()))) k_region(RegionLaunch rl, Tiling t, Scratch scr,
                                                                          RpcRing rpc)
 {
     __shared__ double s_red[kLdsRed];
@@ -1770,6 +1831,11 @@ __global__ void __launch_bounds__(family_max_threads<KMASK>()) k_region(RegionLa
             hist_phase1((const uint32_t *)rl.arr[0], (uint32_t *)rl.arr[1], scr.hist_rows, st.mask, rl.n,
                         worker_id(blockIdx.x, G, t.xcd_remap), G, t);
         return;
+    } else if (st.kind == GF_R_SPMV) {
+        if constexpr ((KMASK >> GF_R_SPMV) & 1u)
+            spmv_region((const int32_t *)rl.arr[0], (const int32_t *)rl.arr[1], (const double *)rl.arr[2],
+                        (const double *)rl.arr[3], (double *)rl.arr[4], rl.n, worker_id(blockIdx.x, G, t.xcd_remap), G,
+                        rl.n_items, spmv_rows(t));
     } else if (st.kind < 32) {
         const double coef = (st.kind == GF_R_AXPBY) ? rl.scal[st.sc[1]] * st.c : 0.0;
         const int64_t worker = worker_id(blockIdx.x, G, t.xcd_remap);
