@@ -3165,28 +3165,20 @@ gf_status gf_train_predictor(gf_ctx *ctx, float *d_params, float *d_m, float *d_
         epochs < 0)
         return fail(ctx, GF_EINVAL, "bad training arguments");
     hipSetDevice(ctx->device);
-    // scratch: gradient partials | grads | z1 | z2 | y | loss partials
+    // scratch: gradient partials | y | loss partials
     const size_t part = mlp_part_floats(batch);
-    const size_t zsz = (size_t)batch * GF_MLP_HIDDEN, ysz = (size_t)batch * GF_MLP_OUT;
+    const size_t ysz = (size_t)batch * GF_MLP_OUT;
     gf_status st = order_before(ctx, (hipStream_t)hip_stream);
     if (st == GF_OK)
-        st = mlp_scratch(ctx, part + GF_MLP_NPARAMS + 2 * zsz + ysz + 64);
+        st = mlp_scratch(ctx, part + ysz + 64);
     if (st != GF_OK)
         return st;
-    float *dpart = ctx->d_mlp, *dg = dpart + part, *z1 = dg + GF_MLP_NPARAMS, *z2 = z1 + zsz, *y = z2 + zsz,
-          *lpart = y + ysz;
+    float *dpart = ctx->d_mlp, *y = dpart + part, *lpart = y + ysz;
     hipStream_t s = (hipStream_t)hip_stream;
-    for (int32_t e = 0; e < epochs; ++e) {
-        hipError_t r = launch_mlp_forward(d_params, d_feats, batch, y, z1, z2, s);
-        if (r == hipSuccess && d_loss_hist)
-            r = launch_mlp_loss(y, d_target, d_mask, (int64_t)ysz, inv_norm, lpart, d_loss_hist + e, s);
-        if (r == hipSuccess)
-            r = launch_mlp_backward(d_params, d_feats, z1, z2, y, d_target, d_mask, batch, inv_norm, dpart, dg, s);
-        if (r == hipSuccess)
-            r = launch_adam(d_params, dg, d_m, d_v, GF_MLP_NPARAMS, lr, 0.9f, 0.999f, 1e-8f, e + 1, s);
-        if (r != hipSuccess)
-            return hipfail(ctx, r, "training step");
-    }
+    const hipError_t r = launch_mlp_train(d_params, d_m, d_v, d_feats, d_target, d_mask, batch, inv_norm, epochs, lr,
+                                          dpart, y, lpart, d_loss_hist, s);
+    if (r != hipSuccess)
+        return hipfail(ctx, r, "training step");
     mark_after(ctx, s);
     return GF_OK;
 }

@@ -282,6 +282,9 @@ hipError_t launch_mlp_backward(const float *P, const float *feats, const float *
                                float *grads, hipStream_t s);
 hipError_t launch_mlp_loss(const float *y, const float *tgt, const float *mask, int64_t count, float inv_norm,
                            float *part, float *loss, hipStream_t s);
+hipError_t launch_mlp_train(float *P, float *m, float *v, const float *feats, const float *tgt, const float *mask,
+                            int32_t batch, float inv_norm, int32_t epochs, float lr, float *part, float *y,
+                            float *lpart, float *loss_hist, hipStream_t s);
 hipError_t launch_adam(float *p, const float *g, float *m, float *v, int32_t n, float lr, float b1, float b2,
                        float eps, int32_t t, hipStream_t s);
 int mlp_blocks(int32_t batch);
