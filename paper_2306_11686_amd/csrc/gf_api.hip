@@ -1086,16 +1086,23 @@ unsigned program_region_mask(const DProg &p)
     return m;
 }
 
-// Largest grid side of the program's stencil regions over the instances (0:
-// no stencil or no instance given).
-int64_t stencil_side(const DProg &p, const gf_instance *inst, int n_inst)
+// Largest length of the program's regions of the kinds in `kinds` over the
+// instances (0: none, or no instance given).
+int64_t region_length(const DProg &p, unsigned kinds, const gf_instance *inst, int n_inst)
 {
     int64_t n = 0;
     for (int k = 0; k < p.n_steps; ++k)
-        if (p.steps[k].kind == GF_R_JACOBI2D || p.steps[k].kind == GF_R_JACOBI3D)
+        if (p.steps[k].kind < 32 && ((kinds >> p.steps[k].kind) & 1u))
             for (int i = 0; inst && i < n_inst; ++i)
-                n = std::max<int64_t>(n, std::min<int64_t>(inst[i].ip[p.steps[k].np], 1 << 20));
+                n = std::max<int64_t>(n, inst[i].ip[p.steps[k].np]);
     return n;
+}
+
+// Largest grid side of the program's stencil regions.
+int64_t stencil_side(const DProg &p, const gf_instance *inst, int n_inst)
+{
+    return std::min<int64_t>(
+        region_length(p, (1u << GF_R_JACOBI3D) | (1u << GF_R_JACOBI2D), inst, n_inst), 1 << 20);
 }
 
 // Defaults. Streaming regions: 4 elements per thread. Stencils follow the
@@ -1127,8 +1134,12 @@ Tiling choose_tiling(const DProg &p, const gf_launch *l, const gf_instance *inst
     t.wg_size = program_is_hist_family(p) ? 1024 : 256;
     if (n > 0 && (m & ~((1u << GF_R_JACOBI3D) | (1u << GF_R_JACOBI2D))) == 0)
         t.wg_size = (int32_t)std::min<int64_t>(256, std::max<int64_t>(64, ((n + 1) / 2 + 63) / 64 * 64));
-    if (program_is_hist_family(p))
-        t.items = 8;
+    if (program_is_hist_family(p)) {
+        // four groups per thread, whose next four are requested ahead; fewer
+        // where the chunks would not reach every CU
+        const int64_t keys = named ? 0 : region_length(p, 1u << GF_R_HIST, inst, n_inst);
+        t.items = keys > 0 && keys < (1 << 21) ? 1 : (keys > 0 && keys < (1 << 22) ? 2 : 4);
+    }
     const bool tall = n >= 416 && n % 64 != 0;
     t.tile_y = is3 ? 8 : (is2 ? 16 : 1);
     if (n > 0)
@@ -1366,7 +1377,7 @@ int region_grid(gf_ctx *ctx, const DStep &s, int64_t items, const Tiling &t)
     if (s.kind == GF_R_PHASES)
         return std::max(1, std::min(ctx->num_cu, phases_capacity(t.wg_size, ctx->num_cu)));
     if (s.kind == GF_R_HIST)
-        return hist_grid(std::min<int64_t>(std::max<int64_t>(items, 1), (int64_t)ctx->num_cu * 2), s.mask);
+        return hist_grid(std::min<int64_t>(std::max<int64_t>(items, 1), (int64_t)ctx->num_cu), s.mask);
     int64_t cap = (int64_t)ctx->num_cu * 16;
     if (s.kind == GF_R_SPMV) {
         const std::array<int, 4> key{s.kind, t.wg_size, t.tile_y, t.prefetch};
@@ -1409,7 +1420,7 @@ gf_status launch_one(gf_ctx *ctx, const RegionLaunch &cur, const Tiling &t, cons
         p1.n_glue = 0;
         hipError_t e = launch_region(p1, t, grid, ctx->scr, rpc, stream);
         if (e == hipSuccess)
-            e = launch_hist_merge(cur, grid, ctx->scr, rpc, ctx->num_cu, stream);
+            e = launch_hist_merge(cur, std::min<int64_t>(grid, cur.n_items), ctx->scr, rpc, ctx->num_cu, stream);
         if (e != hipSuccess)
             return hipfail(ctx, e, "histogram launch");
         *launches += 2;

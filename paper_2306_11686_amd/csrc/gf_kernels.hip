@@ -684,42 +684,64 @@ __device__ __forceinline__ void axpby_item(double *out_, const double *x_, doubl
 // falls in its part (all of a worker's items share one part because the
 // worker stride is a multiple of the part count) into 16-bit counters packed
 // two per 32-bit LDS word, with non-returning LDS atomics, then writes them
-// as its partial row of 16-bit counts. Once per 32768 keys at most (every
-// chunk, or every few when chunks are smaller; a chunk is at most 32768
-// keys, checked on the host) the workgroup moves 0x8000 of every counter
-// that reached 0x8000 into the global bin: a counter is below 0x8000 after a
-// scan and grows by at most 32768 before the next one, so it never wraps and
-// no carry crosses into the neighbouring counter; the final counters fit in
-// 16 bits. Integer counts are exact in any order.
-__device__ __forceinline__ void hist_count(uint32_t *s_h, uint32_t key, uint32_t mask, uint32_t lo, uint32_t span)
+// as its partial row of 16-bit counts.
+// The LDS holds kHistPart counters whatever the bins: with fewer bins there
+// are R = 2^lr copies of each, up to 64, and lane l counts in copy l % R,
+// which lie next to each other. Skewed keys then meet in fewer lanes of a
+// wavefront on one counter (none at 64 copies, where every lane has a bank
+// of its own).
+// A scan moves every counter that reached 0x8000 into the global bin. It
+// leaves counters below 0x8000, and a chunk adds at most chunk_keys / R to a
+// counter, so a scan every `every` chunks, every * chunk_keys / R <= 0x8000,
+// keeps them within 16 bits: none wraps and no carry crosses into the
+// neighbouring counter (moving at 0x1000 saves a third of the scans, but the
+// workgroups' additions to a few hot bins then cost more: 2^28 skewed keys in
+// 4,096 bins 300 us against 226). Integer counts are exact in any order.
+struct HistPlan {
+    uint32_t mask, lo;      // the part's first bin
+    uint32_t words;         // LDS words in use
+    int lr;                 // log2 of the copies
+    bool one;               // one part: every key counts
+};
+
+__device__ __forceinline__ void hist_count(uint32_t *s_copy, uint32_t key, const HistPlan &h, bool one)
 {
-    const uint32_t b = (key & mask) - lo;
-    if (b < span)
-        __hip_atomic_fetch_add(&s_h[b >> 1], 1u << ((b & 1u) * 16u), __ATOMIC_RELAXED,
-                               __HIP_MEMORY_SCOPE_WORKGROUP);
+    uint32_t b = key & h.mask;
+    if (!one) {
+        b -= h.lo;
+        if (b >= (uint32_t)kHistPart)
+            return;
+    }
+    // odd bins count in the word's upper half
+    __hip_atomic_fetch_add(&s_copy[(b >> 1) << h.lr], 1u << ((b << 4) & 31u), __ATOMIC_RELAXED,
+                           __HIP_MEMORY_SCOPE_WORKGROUP);
 }
 
-__device__ __forceinline__ void hist_escape(uint32_t *s_h, GF_GLOBAL uint32_t *bins, uint32_t lo, uint32_t span)
+typedef uint32_t gf_u4 __attribute__((ext_vector_type(4)));
+
+__device__ __forceinline__ void hist_escape(uint32_t *s_h, GF_GLOBAL uint32_t *bins, const HistPlan &h)
 {
     __syncthreads();
-    for (uint32_t wd = threadIdx.x; wd < (span + 1) / 2; wd += blockDim.x) {
-        uint32_t v = s_h[wd];
-        if (v & 0x80008000u) {
-            if (v & 0x8000u) {
-                __hip_atomic_fetch_add(&bins[lo + 2 * wd], 0x8000u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-                v -= 0x8000u;
+    for (uint32_t q = threadIdx.x * 4; q < h.words; q += blockDim.x * 4) {
+        gf_u4 v = *(gf_u4 *)(s_h + q);
+        if ((v.x | v.y | v.z | v.w) & 0x80008000u) {
+#pragma unroll
+            for (int j = 0; j < 4; ++j) {
+                GF_GLOBAL uint32_t *b = bins + h.lo + 2 * ((q + j) >> h.lr);
+                if (v[j] & 0x8000u) {
+                    __hip_atomic_fetch_add(b, v[j] & 0xFFFFu, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                    v[j] &= 0xFFFF0000u;
+                }
+                if (v[j] & 0x80000000u) {
+                    __hip_atomic_fetch_add(b + 1, v[j] >> 16, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                    v[j] &= 0xFFFFu;
+                }
             }
-            if (v & 0x80000000u) {
-                __hip_atomic_fetch_add(&bins[lo + 2 * wd + 1], 0x8000u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-                v -= 0x80000000u;
-            }
-            s_h[wd] = v;
+            *(gf_u4 *)(s_h + q) = v;
         }
     }
     __syncthreads();
 }
-
-typedef uint32_t gf_u4 __attribute__((ext_vector_type(4)));
 
 // The keys of one chunk for this thread: ITEMS groups of four consecutive
 // keys, group k at base + (k * blockDim.x + threadIdx.x) * 4. Every chunk
@@ -750,33 +772,42 @@ __device__ __forceinline__ void hist_load(GF_GLOBAL const uint32_t *keys, int64_
 }
 
 template <int ITEMS>
-__device__ __forceinline__ void hist_count_all(uint32_t *s_h, const gf_u4 (&v)[ITEMS], int64_t n, int64_t base,
-                                               uint32_t mask, uint32_t lo, uint32_t span)
+__device__ __forceinline__ void hist_count_all(uint32_t *s_copy, const gf_u4 (&v)[ITEMS], int64_t n, int64_t base,
+                                               const HistPlan &h)
 {
     const uint32_t B4 = blockDim.x * 4u;
     if (base + (int64_t)ITEMS * B4 <= n) {
+        if (h.one) {
 #pragma unroll
-        for (int k = 0; k < ITEMS; ++k) {
-            hist_count(s_h, v[k].x, mask, lo, span);
-            hist_count(s_h, v[k].y, mask, lo, span);
-            hist_count(s_h, v[k].z, mask, lo, span);
-            hist_count(s_h, v[k].w, mask, lo, span);
+            for (int k = 0; k < ITEMS; ++k)
+#pragma unroll
+                for (int j = 0; j < 4; ++j)
+                    hist_count(s_copy, v[k][j], h, true);
+        } else {
+#pragma unroll
+            for (int k = 0; k < ITEMS; ++k)
+#pragma unroll
+                for (int j = 0; j < 4; ++j)
+                    hist_count(s_copy, v[k][j], h, false);
         }
         return;
     }
     const int64_t left0 = n - base - threadIdx.x * 4;
+#pragma unroll
     for (int k = 0; k < ITEMS; ++k) {
         const int64_t left = left0 - (int64_t)k * B4;
-        for (int j = 0; j < 4 && j < left; ++j)
-            hist_count(s_h, v[k][j], mask, lo, span);
+#pragma unroll
+        for (int j = 0; j < 4; ++j)
+            if (j < left)
+                hist_count(s_copy, v[k][j], h, false);
     }
 }
 
 // Up to four groups per thread, the next chunk's keys are requested before
 // this chunk is counted, so their latency hides behind the LDS atomics and
-// the escape scan (eight groups double-buffered would not fit the 128
-// registers of a 1024-thread workgroup). s_h: the workgroup's
-// kHistPart / 2 LDS words.
+// the scan (eight groups double-buffered would not fit the 128 registers of a
+// 1024-thread workgroup). A worker without a chunk does nothing, and has no
+// row. s_h: the workgroup's kHistPart / 2 LDS words.
 template <int ITEMS>
 __device__ __forceinline__ void hist_phase1_t(uint32_t *s_h, const uint32_t *keys_, uint32_t *bins_,
                                               uint32_t *rows_, uint32_t mask, int64_t n, int64_t worker, int64_t G,
@@ -785,34 +816,39 @@ __device__ __forceinline__ void hist_phase1_t(uint32_t *s_h, const uint32_t *key
     GF_GLOBAL const uint32_t *__restrict__ keys = gptr(keys_);
     GF_GLOBAL uint32_t *bins = gptr(bins_);
     const HistGeom g = hist_geom(n, mask, t);
-    const int64_t part = worker % g.parts;
-    const uint32_t lo = (uint32_t)(part * kHistPart);
-    const int64_t span64 = g.nbins - (int64_t)lo < kHistPart ? g.nbins - (int64_t)lo : kHistPart;
-    const uint32_t span = (uint32_t)span64;
-    for (int i = threadIdx.x; i < kHistPart / 2; i += blockDim.x)
-        s_h[i] = 0u;
+    if (worker >= g.nitems)
+        return;
+    const int lbins = __builtin_popcount(mask);             // 2^lbins bins
+    const int lparts = lbins > 16 ? lbins - 16 : 0;
+    HistPlan h;
+    h.mask = mask;
+    h.one = lparts == 0;
+    h.lr = lbins >= 16 ? 0 : (lbins > 10 ? 16 - lbins : 6);
+    h.lo = (uint32_t)((worker & ((1 << lparts) - 1)) * kHistPart);
+    h.words = h.one ? (uint32_t)((g.nbins + 1) / 2) << h.lr : (uint32_t)kHistPart / 2;
+    for (uint32_t i = threadIdx.x * 4; i < h.words; i += blockDim.x * 4)
+        *(gf_u4 *)(s_h + i) = gf_u4{0u, 0u, 0u, 0u};
     __syncthreads();
+    uint32_t *s_copy = s_h + (threadIdx.x & ((1u << h.lr) - 1));
     constexpr bool kAhead = ITEMS <= 4;
-    // A chunk adds at most chunk_keys to a counter, so escaping after every
-    // `every` chunks, every * chunk_keys <= 0x8000, keeps each counter (below
-    // 0x8000 after an escape) within 16 bits; small chunks share one scan.
-    const int64_t every = g.chunk_keys >= 0x8000 ? 1 : 0x8000 / g.chunk_keys;
-    int64_t since = 0;
+    const int every = (int)(0x8000 / (g.chunk_keys >> h.lr));
+    int since = 0;
+    const int64_t step = (G >> lparts) * g.chunk_keys;
     gf_u4 cur[ITEMS], nxt[kAhead ? ITEMS : 1];
-    if (kAhead && worker < g.nitems)
-        hist_load<ITEMS>(keys, n, (worker / g.parts) * g.chunk_keys, cur);
-    for (int64_t it = worker; it < g.nitems; it += G) {
-        const int64_t base = (it / g.parts) * g.chunk_keys;
+    int64_t base = (worker >> lparts) * g.chunk_keys;
+    if (kAhead)
+        hist_load<ITEMS>(keys, n, base, cur);
+    for (; base < n; base += step) {
         const bool scan = ++since == every;
         if (scan)
             since = 0;
         if constexpr (kAhead) {
-            const bool more = it + G < g.nitems;
+            const bool more = base + step < n;
             if (more)
-                hist_load<ITEMS>(keys, n, ((it + G) / g.parts) * g.chunk_keys, nxt);
-            hist_count_all<ITEMS>(s_h, cur, n, base, mask, lo, span);
+                hist_load<ITEMS>(keys, n, base + step, nxt);
+            hist_count_all<ITEMS>(s_copy, cur, n, base, h);
             if (scan)
-                hist_escape(s_h, bins, lo, span);
+                hist_escape(s_h, bins, h);
             if (more) {
 #pragma unroll
                 for (int k = 0; k < ITEMS; ++k)
@@ -820,20 +856,37 @@ __device__ __forceinline__ void hist_phase1_t(uint32_t *s_h, const uint32_t *key
             }
         } else {
             hist_load<ITEMS>(keys, n, base, cur);
-            hist_count_all<ITEMS>(s_h, cur, n, base, mask, lo, span);
+            hist_count_all<ITEMS>(s_copy, cur, n, base, h);
             if (scan)
-                hist_escape(s_h, bins, lo, span);
+                hist_escape(s_h, bins, h);
         }
     }
-    // the rows below hold the counters as 16-bit entries: every counter is
-    // at most 0x7FFF plus the keys of the chunks since the last escape; the
-    // workgroup's counting is complete before they are read
     __syncthreads();
     // the packed LDS word holds bins 2w (low half) and 2w+1 (high half): as
-    // a 32-bit store it lays down the two 16-bit row entries in order
+    // a 32-bit store it lays down the two 16-bit row entries in order. Copies
+    // are added; what exceeds a 16-bit entry goes to the bin itself.
     GF_GLOBAL uint32_t *row = gptr(rows_) + worker * (kHistPart / 2);
-    for (uint32_t wd = threadIdx.x; wd < (span + 1) / 2; wd += blockDim.x)
-        row[wd] = s_h[wd];
+    if (h.lr == 0) {
+        for (uint32_t i = threadIdx.x * 4; i < h.words; i += blockDim.x * 4)
+            *(GF_GLOBAL gf_u4 *)(row + i) = *(const gf_u4 *)(s_h + i);
+        return;
+    }
+    const uint32_t R = 1u << h.lr;
+    for (uint32_t wd = threadIdx.x; wd < h.words >> h.lr; wd += blockDim.x) {
+        uint32_t a = 0, b = 0;
+        // every lane starts at another copy, another bank
+#pragma unroll 8
+        for (uint32_t c = 0; c < R; ++c) {
+            const uint32_t v = s_h[(wd << h.lr) + ((c + threadIdx.x) & (R - 1))];
+            a += v & 0xFFFFu;
+            b += v >> 16;
+        }
+        row[wd] = (a & 0xFFFFu) | (b << 16);
+        if (a >> 16)
+            __hip_atomic_fetch_add(&bins[2 * wd], a & 0xFFFF0000u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        if (b >> 16)
+            __hip_atomic_fetch_add(&bins[2 * wd + 1], b & 0xFFFF0000u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    }
 }
 
 __device__ __forceinline__ void hist_phase1(const uint32_t *keys, uint32_t *bins, uint32_t *rows, uint32_t mask,
@@ -849,49 +902,55 @@ __device__ __forceinline__ void hist_phase1(const uint32_t *keys, uint32_t *bins
 }
 
 // Histogram, phase 2: bins[b] += the sum of b's entries over the `rows_used`
-// partial rows (row w holds part w % parts). A work unit is four adjacent
-// bins times one slice of the rows (every S-th row of the part, S chosen so
-// the units cover the threads); its four sums go to the bins with integer
-// atomics, exact in any order. Threads [first, first + stride) share the
-// units.
+// partial rows (row w holds part w % parts). A workgroup takes tiles of
+// blockDim / 4 bins: eight adjacent bins per thread, 32 threads each with
+// every 32nd row of the part, their sums added in LDS, so that a bin gets one
+// atomic. Bound by the latency of the rows. 256 rows of 65,536 bins took 21
+// us with slices of 16 rows that each added to the bins, and take 8.
+constexpr int kHistSlices = 32;
+
 __device__ __forceinline__ void hist_merge(uint32_t *bins_, const uint32_t *rows_, uint32_t mask, int64_t rows_used,
-                                           int64_t first, int64_t stride)
+                                           int64_t block, int64_t nblocks)
 {
+    __shared__ uint32_t s_sum[kMaxWgHist / 4];
+    typedef uint16_t gf_h8 __attribute__((ext_vector_type(8)));
     GF_GLOBAL uint32_t *bins = gptr(bins_);
     GF_GLOBAL const uint16_t *rows = (GF_GLOBAL const uint16_t *)gptr(rows_);
     const int64_t nbins = (int64_t)mask + 1;
-    const int64_t parts = cdiv(nbins, kHistPart);
-    const int64_t quads = cdiv(nbins, 4);
-    const int64_t per_part = rows_used / parts;  // rows of each part
-    int64_t S = stride / quads;
-    S = S < 1 ? 1 : (S > per_part ? per_part : S);
-    for (int64_t u = first; u < quads * S; u += stride) {
-        const int64_t q = u % quads;
-        const int64_t sl = u / quads;
-        const int64_t b0 = q * 4;
-        const int64_t part = b0 / kHistPart;
-        const int64_t off = b0 - part * kHistPart;
-        uint32_t s0 = 0, s1 = 0, s2 = 0, s3 = 0;
-        // unrolled so that several row loads are in flight per thread (the
-        // persistent kernel runs this with one workgroup per CU)
+    const int lbins = __builtin_popcount(mask);
+    const int lparts = lbins > 16 ? lbins - 16 : 0;
+    const int64_t per_part = rows_used >> lparts;  // rows of each part
+    const int octs = blockDim.x / kHistSlices;
+    const int o = threadIdx.x % octs, sl = threadIdx.x / octs;
+    const int span = octs * 8;
+    for (int64_t first = block * span; first < nbins; first += nblocks * span) {
+        if ((int)threadIdx.x < span)
+            s_sum[threadIdx.x] = 0u;
+        __syncthreads();
+        const int64_t b0 = first + o * 8;
+        if (b0 < nbins) {
+            GF_GLOBAL const uint16_t *p = rows + (b0 / kHistPart) * kHistPart + b0 % kHistPart;
+            uint32_t sum[8] = {};
 #pragma unroll 8
-        for (int64_t j = sl; j < per_part; j += S) {
-            const int64_t w = part + j * parts;
-            typedef uint16_t gf_h4 __attribute__((ext_vector_type(4)));
-            const gf_h4 r = *(GF_GLOBAL const gf_h4 *)(rows + w * kHistPart + off);
-            s0 += r.x;
-            s1 += r.y;
-            s2 += r.z;
-            s3 += r.w;
+            for (int64_t j = sl; j < per_part; j += kHistSlices) {
+                const gf_h8 r = *(GF_GLOBAL const gf_h8 *)(p + (j << lparts) * kHistPart);
+#pragma unroll
+                for (int q = 0; q < 8; ++q)
+                    sum[q] += r[q];
+            }
+#pragma unroll
+            for (int q = 0; q < 8; ++q)
+                if (sum[q])
+                    __hip_atomic_fetch_add(&s_sum[q * octs + o], sum[q], __ATOMIC_RELAXED,
+                                           __HIP_MEMORY_SCOPE_WORKGROUP);
         }
-        if (s0)
-            __hip_atomic_fetch_add(&bins[b0], s0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        if (s1 && b0 + 1 < nbins)
-            __hip_atomic_fetch_add(&bins[b0 + 1], s1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        if (s2 && b0 + 2 < nbins)
-            __hip_atomic_fetch_add(&bins[b0 + 2], s2, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        if (s3 && b0 + 3 < nbins)
-            __hip_atomic_fetch_add(&bins[b0 + 3], s3, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        __syncthreads();
+        if ((int)threadIdx.x < span && first + threadIdx.x < nbins) {
+            const uint32_t v = s_sum[threadIdx.x % 8 * octs + threadIdx.x / 8];
+            if (v)
+                __hip_atomic_fetch_add(&bins[first + threadIdx.x], v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        }
+        __syncthreads();
     }
 }
 
@@ -1667,8 +1726,8 @@ __global__ void __launch_bounds__(family_max_threads<KMASK>())
                     hist_phase1((const uint32_t *)op[0], (uint32_t *)op[1], scr.hist_rows, st.mask, n, worker, G, t);
                     if (!barrier())
                         return;
-                    hist_merge((uint32_t *)op[1], scr.hist_rows, st.mask, G, worker * blockDim.x + threadIdx.x,
-                               G * blockDim.x);
+                    const int64_t rows = region_items_dev(st, n, t);
+                    hist_merge((uint32_t *)op[1], scr.hist_rows, st.mask, rows < G ? rows : G, worker, G);
                 }
             } else if (st.kind == GF_R_SPMV) {
                 if constexpr ((KMASK >> GF_R_SPMV) & 1u)
@@ -1988,8 +2047,7 @@ __global__ void __launch_bounds__(kMaxWg) k_hist_merge(RegionLaunch rl, int64_t 
 {
     __shared__ int s_last;
     const int64_t G = gridDim.x;
-    hist_merge((uint32_t *)rl.arr[1], scr.hist_rows, rl.step.mask, rows_used,
-               (int64_t)blockIdx.x * blockDim.x + threadIdx.x, G * blockDim.x);
+    hist_merge((uint32_t *)rl.arr[1], scr.hist_rows, rl.step.mask, rows_used, blockIdx.x, G);
     if (rl.n_glue == 0)
         return;
     uint32_t *cnt = scr.lines + (int64_t)(kFinalizeLine0 + rl.inst) * kLineWords;
@@ -2214,11 +2272,7 @@ int64_t hist_parts(uint32_t mask) { return cdiv((int64_t)mask + 1, kHistPart); }
 hipError_t launch_hist_merge(const RegionLaunch &rl, int64_t rows_used, const Scratch &scr, const RpcRing &rpc,
                              int num_cu, hipStream_t s)
 {
-    // one thread per (four bins, slice of up to 16 rows of the part)
-    const int64_t nbins = (int64_t)rl.step.mask + 1;
-    const int64_t per_part = rows_used / cdiv(nbins, kHistPart);
-    const int64_t slices = per_part < 16 ? (per_part < 1 ? 1 : per_part) : 16;
-    int64_t g = cdiv(cdiv(nbins, 4) * slices, kMaxWg);
+    int64_t g = cdiv((int64_t)rl.step.mask + 1, kMaxWg / 4);
     if (g > (int64_t)num_cu * 16)
         g = (int64_t)num_cu * 16;
     hipLaunchKernelGGL(k_hist_merge, dim3((unsigned)g), dim3(kMaxWg), 0, s, rl, rows_used, scr, rpc);
