@@ -2181,12 +2181,19 @@ static gf_status region_run(gf_ctx *ctx, const gf_program *prog, const gf_instan
                                fused_rs);
         for (int i = 0; i < n_inst; ++i) {
             // default grid: at most two workgroups per CU (the grid barrier's
-            // cost grows with the number of members), sized so that every
+            // cost grows with the number of members: each invalidates its
+            // XCD's L2, 60 to 80 ns one after the other), sized so that every
             // workgroup gets the same number of work items (balanced rounds)
             int64_t gmax = std::min<int64_t>(cap, 2 * (int64_t)ctx->num_cu);
             int64_t items = 0;
             if (fused_rs < 0) {
                 items = max_items(p, inst[i], t);
+                // SpMV programs spend their time in barriers up to some eight
+                // items per CU: one workgroup per CU (50 iterations of CG, one
+                // against two, m^3 rows, m = 40 / 50 / 64 / 80: 1.89 / 2.24 /
+                // 2.83 / 4.03 ms and 2.34 / 2.56 / 3.09 / 4.00)
+                if ((program_region_mask(p) & (1u << GF_R_SPMV)) && items <= 8 * (int64_t)ctx->num_cu)
+                    gmax = std::min<int64_t>(cap, ctx->num_cu);
             } else {
                 const DStep &st = p.steps[fused_rs];
                 gmax = fcap;

@@ -205,6 +205,10 @@ constexpr int kXcdBarrierMinWg = 96;
 // registration costs one tree barrier).
 constexpr int64_t kXcdBarrierMinBarriers = 8;
 
+// Partials of a reduction that every workgroup of the persistent kernel sums
+// itself.
+constexpr int64_t kFinItems = 1024;
+
 constexpr int kHistRowsMax = 512;
 
 constexpr int kLineWords = 32;  // uint32 words per 128-byte line

@@ -1752,11 +1752,16 @@ __global__ void __launch_bounds__(family_max_threads<KMASK>())
                 }
                 if (fold && threadIdx.x == 0 && worker < nitems)
                     __hip_atomic_fetch_max(slot, max_key(wmax), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-                if (red && !fold && xmode && s_xcd.use && G > 1) {
-                    // Other reductions under the XCD barrier: the last
-                    // workgroup to arrive reduces the partials once (the same
-                    // fixed order as below) and publishes the value; the
-                    // others read one word instead of every partial.
+                if (red && !fold && xmode && s_xcd.use && nitems > kFinItems) {
+                    // Other reductions of many items under the XCD barrier:
+                    // the last workgroup to arrive reduces the partials once
+                    // (the same fixed order as below) and publishes the
+                    // value; the others read one word instead of every
+                    // partial. Up to kFinItems partials, four loads per
+                    // thread, are read by every workgroup after the barrier
+                    // instead: its release does not wait for the sum (96 /
+                    // 256 / 1,024 workgroups with a dot item each: 7.0 / 8.5
+                    // / 16.1 us a dot against 6.4 / 7.8 / 15.8).
                     uint64_t *sum_slot = (uint64_t *)(scr.lines + (int64_t)kRedSlotLine * kLineWords);
                     if (!xcd_barrier_fin(scr.lines, s_xcd, &s_bar, scr.error, scr.barrier_timeout_ticks, [&]() {
                             const double v = reduce_partials(st.red_op, part, nitems, s_red);
