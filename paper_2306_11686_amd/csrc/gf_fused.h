@@ -328,23 +328,33 @@ __device__ __forceinline__ void j2f_item(const double *u_, double *w_, int64_t n
 }
 
 // ---------------------------------------------------------------------------
-// 3D. A wavefront owns 128 columns (two per lane) by kJ3fRows output rows and
-// marches z; the four wavefronts of a workgroup sit above each other in y.
-// When plane z arrives, stage s computes plane z - s of sweep k + s for the
-// output rows and M - s rows on each side, from stage s-1's planes z-s-1,
-// z-s, z-s+1, all in registers. The rows a neighbouring wavefront also reads
-// come from the CU's L1. A plane's rows are requested as soon as the
-// registers of the plane three before are free, one step ahead of their use.
+// 3D. A workgroup owns 128 columns (two per lane) by 32 rows, four per
+// wavefront, and marches z. When plane z arrives, stage s computes plane
+// z - s of sweep k + s from stage s-1's planes z-s-1, z-s, z-s+1, all in
+// registers. The rows above and below a wavefront's own are the neighbouring
+// wavefronts': each lays the edge rows of every stage's newest plane in LDS
+// at the end of a step, and they are read a step later, when that plane is
+// the middle one, so that one barrier per step is enough. The tile's outermost
+// rows go wrong one per stage, like the columns: it writes 32 - 2 M rows. A
+// plane's rows are requested as soon as the registers of the plane three
+// before are free, one step ahead of their use.
+// 512^3, 100 sweeps: 44.9 ms a sweep at a time; 20.6 with every wavefront
+// computing the rows around its three output rows itself (5 rows of work for
+// one output row and three sweeps); 16.3 so (3.7). About 480 us a pass of
+// three sweeps, 2.4 GB (an eighth of it halos) at 5 TB/s, with the vector
+// units half busy: bound by HBM and by the steps' latency at two wavefronts
+// per SIMD.
 // Only run when the two buffers' outer layers agree (the kernel compares
 // them first), so a point of the outer layer keeps its value at every stage.
 // ---------------------------------------------------------------------------
 
-constexpr int kJ3fRows = 3;    // output rows per wavefront
-constexpr int kJ3fWaves = 4;   // wavefronts of a workgroup, along y
+constexpr int kJ3fRows = 4;    // rows per wavefront
+constexpr int kJ3fWaves = 8;   // wavefronts of a workgroup, along y
+constexpr int kJ3fTile = kJ3fRows * kJ3fWaves;
 
 struct J3fGeom {
     int32_t chunks, width;  // items across a row, output columns of one (even)
-    int32_t yt;             // workgroup tiles along y
+    int32_t yt, height;     // workgroup tiles along y, output rows of one
     int32_t zlen, zs;       // planes per segment, segments
     int64_t items;          // workgroup items
 };
@@ -353,8 +363,10 @@ __host__ __device__ inline J3fGeom j3f_geom(int64_t n, int M, int32_t zlen)
 {
     J3fGeom g;
     j2f_chunks(n, M, &g.chunks, &g.width);
-    const int64_t in = n > 2 ? n - 2 : 0;
-    g.yt = (int32_t)((in + kJ3fRows * kJ3fWaves - 1) / (kJ3fRows * kJ3fWaves));
+    const int32_t in = n > 2 ? (int32_t)(n - 2) : 0, most = kJ3fTile - 2 * M;
+    const int32_t tiles = in > 0 ? (in + most - 1) / most : 1;
+    g.height = in > 0 ? (in + tiles - 1) / tiles : 1;
+    g.yt = (in + g.height - 1) / g.height;
     g.zlen = zlen;
     g.zs = (int32_t)((in + zlen - 1) / zlen);
     g.items = (int64_t)g.chunks * g.yt * g.zs;
@@ -399,18 +411,22 @@ __device__ __forceinline__ bool outer3_agrees(GF_GLOBAL const double *a_, GF_GLO
     return diff == 0;
 }
 
-// Planes [z0, z1), rows [y0, y0 + kJ3fRows) of u^(k+M). EDGE: the tile or the
-// rows, columns and planes around it that it computes touch the outer layer.
-// valid: false for a wavefront past the last row (it keeps step with the
-// others and stores nothing). acc[s]: the lane's max |difference| of sweep
-// k + s + 1.
+// Edge rows of the planes that the stages of a workgroup's wavefronts read
+// next: [parity of the step][stage][wavefront][first, last row][lane].
+template <int M>
+struct J3fEdges {
+    gf_d2 row[2][M][kJ3fWaves][2][kWave];
+};
+
+// Planes [z0, z1), rows [ylo, yhi) of u^(k+M), by a wavefront that holds rows
+// [r0, r0 + kJ3fRows). EDGE: these rows or the columns touch the outer layer. acc[s]: the lane's max |difference| of
+// sweep k + s + 1.
 template <int M, bool EDGE>
 __device__ __forceinline__ void j3f_tile(GF_GLOBAL const double *__restrict__ u, GF_GLOBAL double *__restrict__ w,
-                                         int32_t n, int32_t x0, int32_t xa, int32_t xb, int32_t y0, bool valid,
-                                         int32_t z0, int32_t z1, double (&acc)[M])
+                                         J3fEdges<M> &edges, int32_t n, int32_t x0, int32_t xa, int32_t xb, int32_t r0,
+                                         int32_t ylo, int32_t yhi, int32_t z0, int32_t z1, int wv, double (&acc)[M])
 {
     constexpr int TY = kJ3fRows;
-    constexpr int R0 = TY + 2 * M;
     const int lane = threadIdx.x & (kWave - 1);
     const int32_t x = x0 + 2 * lane;
     const uint32_t xs = 8u * (uint32_t)(EDGE && x > n - 2 ? n - 2 : x);
@@ -418,63 +434,68 @@ __device__ __forceinline__ void j3f_tile(GF_GLOBAL const double *__restrict__ u,
     const bool bx = EDGE && (x == 0 || x == n - 1);
     const bool by = EDGE && x + 1 == n - 1;
     const bool zy = by || lone;
-    const bool mine = valid && x >= xa && x < xb && x < n;
+    const bool mine = x >= xa && x < xb && x < n;
     const int64_t pitch = n, plane = (int64_t)n * n;
     const int32_t za = z0 - M > 0 ? z0 - M : 0;                    // first plane read
     const int32_t zb = z1 - 1 + M < n - 1 ? z1 - 1 + M : n - 1;    // last plane read
     const int32_t ze = z1 - 1 + M;                                 // last step
+    // the wavefronts above and below (at the tile's ends: any row, never used)
+    const int wu = wv > 0 ? wv - 1 : 0, wd = wv + 1 < kJ3fWaves ? wv + 1 : wv;
     auto ld = [&](int32_t z, int j) -> gf_d2 {
-        int32_t y = y0 - M + j;
+        int32_t y = r0 + j;
         if constexpr (EDGE)
-            y = y < 0 ? 0 : (y > n - 1 ? n - 1 : y);
+            y = y > n - 1 ? n - 1 : y;
         const gf_d2 v = *row_at<const gf_d2u>(u + (z < zb ? z : zb) * plane + y * pitch, xs);
         if constexpr (EDGE)
             return gf_d2{lone ? v.y : v.x, v.y};
         return v;
     };
     const gf_d2 zero2 = {0.0, 0.0};
-    // q[s][slot][row]: stage s's planes, row j of stage s is y0 - (M - s) + j
-    gf_d2 q[M][3][R0];
+    // q[s][slot][row]: stage s's planes
+    gf_d2 q[M][3][TY];
 #pragma unroll
     for (int s = 0; s < M; ++s)
 #pragma unroll
         for (int k = 0; k < 3; ++k)
 #pragma unroll
-            for (int j = 0; j < R0 - 2 * s; ++j)
+            for (int j = 0; j < TY; ++j)
                 q[s][k][j] = zero2;
 #pragma unroll
-    for (int j = 0; j < R0; ++j)
+    for (int j = 0; j < TY; ++j)
         q[0][0][j] = ld(za, j);
     const double c6 = 1.0 / 6.0;
-    gf_d2 fin[TY];  // the last stage's rows
-#pragma unroll
-    for (int j = 0; j < TY; ++j)
-        fin[j] = zero2;
-    // one step: plane z is in slot k of stage 0
-    auto step = [&](auto kc, int32_t z) {
+    // one step: plane z is in slot k of stage 0. ENDS: a stage may be at the
+    // first or the last plane
+    auto step = [&](auto kc, auto ends, int32_t plane_in) {
+        const int32_t z = __builtin_amdgcn_readfirstlane(plane_in);
         constexpr int k = decltype(kc)::value;
+        constexpr bool ENDS = decltype(ends)::value;
         constexpr int kc1 = (k + 2) % 3, km = (k + 1) % 3;  // the planes one and two before
-        __syncthreads();
-        // stage 0's plane z-2 is read for its middle rows only
-        q[0][km][0] = ld(z + 1, 0);
+        __syncthreads();  // the edge rows of the step before are in LDS, those of the one before that free
+        gf_d2 nu[M], nd[M];
 #pragma unroll
-        for (int j = 0; j < R0 - 2 + M - 1; ++j) {
-            // row j of stage 1, then row j-1 of stage 2, j-2 of stage 3
+        for (int s = 0; s < M; ++s) {
+            nu[s] = edges.row[(z + 1) & 1][s][wu][1][lane];
+            nd[s] = edges.row[(z + 1) & 1][s][wd][0][lane];
+        }
+        gf_d2 fin[TY];
 #pragma unroll
-            for (int s = 1; s <= M; ++s) {
-                const int i = j - (s - 1);
-                if (i < 0 || i >= R0 - 2 * s)
-                    continue;
-                const gf_d2 c = q[s - 1][kc1][i + 1];
-                const gf_d2 up = q[s - 1][kc1][i], dn = q[s - 1][kc1][i + 2];
-                const gf_d2 zm = q[s - 1][km][i + 1], zp = q[s - 1][k][i + 1];
+        for (int s = 1; s <= M; ++s)
+#pragma unroll
+            for (int i = 0; i < TY; ++i) {
+                // the rows that need the neighbours' last
+                const int j = i < TY - 2 ? i + 1 : (i == TY - 2 ? 0 : TY - 1);
+                const gf_d2 c = q[s - 1][kc1][j];
+                const gf_d2 up = j > 0 ? q[s - 1][kc1][j > 0 ? j - 1 : 0] : nu[s - 1];
+                const gf_d2 dn = j + 1 < TY ? q[s - 1][kc1][j + 1 < TY ? j + 1 : 0] : nd[s - 1];
+                const gf_d2 zm = q[s - 1][km][j], zp = q[s - 1][k][j];
                 const double xl = lane_left(c.y);
                 const double xr = lane_right(c.x);
                 gf_d2 out;
                 out.x = (((xl + c.y) + (up.x + dn.x)) + (zm.x + zp.x)) * c6;
                 out.y = (((c.x + xr) + (up.y + dn.y)) + (zm.y + zp.y)) * c6;
-                if constexpr (EDGE) {
-                    const int32_t y = y0 - (M - s) + i;
+                if constexpr (EDGE || ENDS) {
+                    const int32_t y = r0 + j;
                     const bool flat = y <= 0 || y >= n - 1 || z - s <= 0 || z - s >= n - 1;
                     out.x = (bx || flat) ? c.x : out.x;
                     out.y = (by || flat) ? c.y : out.y;
@@ -483,24 +504,28 @@ __device__ __forceinline__ void j3f_tile(GF_GLOBAL const double *__restrict__ u,
                 // value keeps all of its inputs in registers
                 asm volatile("" : "+v"(out.x), "+v"(out.y));
                 if (s < M)
-                    q[s < M ? s : 0][k][i] = out;
+                    q[s < M ? s : 0][k][j] = out;
                 else
-                    fin[i < TY ? i : 0] = out;
+                    fin[j] = out;
+                // stage 0's plane z-2 is done with
                 if (s == 1)
-                    q[0][km][i + 1] = ld(z + 1, i + 1);
+                    q[0][km][j] = ld(z + 1, j);
             }
+#pragma unroll
+        for (int s = 0; s < M; ++s) {
+            edges.row[z & 1][s][wv][0][lane] = q[s][k][0];
+            edges.row[z & 1][s][wv][1][lane] = q[s][k][TY - 1];
         }
-        q[0][km][R0 - 1] = ld(z + 1, R0 - 1);
         // the output rows' differences, planes of this segment
 #pragma unroll
         for (int s = 1; s <= M; ++s)
             if (z - s >= z0 && z - s < z1) {
 #pragma unroll
-                for (int t = 0; t < TY; ++t) {
-                    if (EDGE && y0 + t > n - 2)
+                for (int j = 0; j < TY; ++j) {
+                    if (r0 + j < ylo || r0 + j >= yhi)
                         continue;
-                    const gf_d2 o = s < M ? q[s < M ? s : 0][k][t + M - s] : fin[t];
-                    const gf_d2 c = q[s - 1][kc1][t + M - s + 1];
+                    const gf_d2 o = s < M ? q[s < M ? s : 0][k][j] : fin[j];
+                    const gf_d2 c = q[s - 1][kc1][j];
                     double dx = __builtin_fabs(o.x - c.x), dy = __builtin_fabs(o.y - c.y);
                     if constexpr (EDGE) {
                         dx = bx ? -INFINITY : dx;
@@ -508,7 +533,7 @@ __device__ __forceinline__ void j3f_tile(GF_GLOBAL const double *__restrict__ u,
                     }
                     acc[s - 1] = __builtin_fmax(acc[s - 1], __builtin_fmax(dx, dy));
                     if (s == M && mine) {
-                        GF_GLOBAL double *p = row_at<double>(w + (z - M) * plane + (y0 + t) * pitch, xs);
+                        GF_GLOBAL double *p = row_at<double>(w + (z - M) * plane + (r0 + j) * pitch, xs);
                         if (!EDGE || (!bx && !by))
                             __builtin_nontemporal_store(o, (GF_GLOBAL gf_d2u *)p);
                         else if (!bx)
@@ -519,14 +544,20 @@ __device__ __forceinline__ void j3f_tile(GF_GLOBAL const double *__restrict__ u,
                 }
             }
     };
+    auto any_step = [&](auto kc, int32_t z) {
+        if (EDGE || z <= M || z >= n)
+            step(kc, std::true_type{}, z);
+        else
+            step(kc, std::false_type{}, z);
+    };
     for (int32_t z = za;;) {
-        step(std::integral_constant<int, 0>{}, z);
+        any_step(std::integral_constant<int, 0>{}, z);
         if (++z > ze)
             break;
-        step(std::integral_constant<int, 1>{}, z);
+        any_step(std::integral_constant<int, 1>{}, z);
         if (++z > ze)
             break;
-        step(std::integral_constant<int, 2>{}, z);
+        any_step(std::integral_constant<int, 2>{}, z);
         if (++z > ze)
             break;
     }
@@ -537,8 +568,8 @@ __device__ __forceinline__ void j3f_tile(GF_GLOBAL const double *__restrict__ u,
 
 // One workgroup item: wavefront wv's rows.
 template <int M>
-__device__ __forceinline__ void j3f_item(const double *u_, double *w_, int64_t n, int32_t zlen, int64_t item, int wv,
-                                         double (&acc)[M])
+__device__ __forceinline__ void j3f_item(const double *u_, double *w_, J3fEdges<M> &edges, int64_t n, int32_t zlen,
+                                         int64_t item, int wv, double (&acc)[M])
 {
     const J3fGeom g = j3f_geom(n, M, zlen);
     const int64_t c = item % g.chunks;
@@ -547,9 +578,11 @@ __device__ __forceinline__ void j3f_item(const double *u_, double *w_, int64_t n
     const int64_t zi = rest / g.yt;
     const int64_t z0 = 1 + zi * g.zlen;
     const int64_t z1 = z0 + g.zlen < n - 1 ? z0 + g.zlen : n - 1;
-    int64_t y0 = 1 + (yt * kJ3fWaves + wv) * kJ3fRows;
-    const bool valid = y0 <= n - 2;
-    y0 = valid ? y0 : 1;
+    const int64_t ylo = 1 + yt * g.height;
+    const int64_t yhi = ylo + g.height < n - 1 ? ylo + g.height : n - 1;
+    const int64_t ymax = n > kJ3fTile ? n - kJ3fTile : 0;
+    int64_t r0 = ylo - M > 0 ? ylo - M : 0;
+    r0 = (r0 < ymax ? r0 : ymax) + wv * kJ3fRows;
     const int64_t halo = (M + 1) & ~1;
     const int64_t cols = (n + 1) & ~(int64_t)1;
     const int64_t xa = c * g.width;
@@ -559,15 +592,16 @@ __device__ __forceinline__ void j3f_item(const double *u_, double *w_, int64_t n
 #pragma unroll
     for (int s = 0; s < M; ++s)
         acc[s] = -INFINITY;
-    // rows and planes the stages compute, and the columns they load
-    const bool edge = x0 == 0 || x0 + 128 >= n || y0 - M < 0 || y0 + kJ3fRows + M > n || z0 - (M - 1) <= 0 ||
-                      z1 - 1 + (M - 1) >= n - 1;
-    if (edge)
-        j3f_tile<M, true>(gptr(u_), gptr(w_), (int32_t)n, (int32_t)x0, (int32_t)xa, (int32_t)(xa + g.width),
-                          (int32_t)y0, valid, (int32_t)z0, (int32_t)z1, acc);
+    // the rows the stages compute, and the columns they load
+    const bool edge = x0 == 0 || x0 + 128 >= n || r0 == 0 || r0 + kJ3fRows >= n;
+    // uniform: kept in scalar registers
+    auto uni = [](int64_t v) -> int32_t { return __builtin_amdgcn_readfirstlane((int32_t)v); };
+    const int32_t side = uni(n), xs = uni(x0), xl = uni(xa), xh = uni(xa + g.width), rs = uni(r0), yl = uni(ylo),
+                  yh = uni(yhi), zl = uni(z0), zh = uni(z1);
+    if (__builtin_amdgcn_readfirstlane(edge))
+        j3f_tile<M, true>(gptr(u_), gptr(w_), edges, side, xs, xl, xh, rs, yl, yh, zl, zh, wv, acc);
     else
-        j3f_tile<M, false>(gptr(u_), gptr(w_), (int32_t)n, (int32_t)x0, (int32_t)xa, (int32_t)(xa + g.width),
-                           (int32_t)y0, valid, (int32_t)z0, (int32_t)z1, acc);
+        j3f_tile<M, false>(gptr(u_), gptr(w_), edges, side, xs, xl, xh, rs, yl, yh, zl, zh, wv, acc);
 }
 
 }  // namespace gf

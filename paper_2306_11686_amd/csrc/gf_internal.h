@@ -24,9 +24,10 @@ constexpr int kFusedMax2 = 7;
 constexpr int kFusedMax3 = 3;
 // Threads per workgroup. 2D: two wavefronts, so that the groups of a batched
 // run divide its items finely (256 uneven instances: the slowest group takes
-// 10 % less than with four); 3D: four, which share the rows between them.
+// 10 % less than with four); 3D: eight, as many as the registers allow, which
+// share a tile's rows.
 constexpr int kFusedWg2 = 128;
-constexpr int kFusedWg3 = 256;
+constexpr int kFusedWg3 = 512;
 constexpr int kFusedMinIters = 4;  // fewer sweeps: nothing to fuse (the last is a pass of its own)
 constexpr int kFusedMinSide2 = 16;  // smaller 2D grids: one sweep per pass
 

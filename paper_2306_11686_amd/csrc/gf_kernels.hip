@@ -1328,7 +1328,7 @@ constexpr unsigned kFamFused3 = kFusedBit | (1u << GF_R_JACOBI3D);
 template <unsigned KMASK>
 constexpr int family_max_threads()
 {
-    return KMASK == kFamHist ? kMaxWgHist : kMaxWg;
+    return KMASK == kFamHist ? kMaxWgHist : (KMASK == kFamFused3 ? kFusedWg3 : kMaxWg);
 }
 
 // Waves per SIMD the persistent kernel is compiled to fit (168 VGPRs for
@@ -1374,10 +1374,12 @@ __device__ __forceinline__ bool fused_pass(const double *src, double *dst, int64
     const int64_t items = k3D ? j3f_geom(n, M, zlen).items * kJ3fWaves : j2f_geom(n, M).items;
     for (int64_t it = worker * nw + wv; it < items; it += G * nw) {
         double acc[M];
-        if constexpr (k3D)
-            j3f_item<M>(src, dst, n, zlen, uniform_i64(it) / kJ3fWaves, wv, acc);
-        else
+        if constexpr (k3D) {
+            __shared__ J3fEdges<M> s_edges;
+            j3f_item<M>(src, dst, s_edges, n, zlen, uniform_i64(it) / kJ3fWaves, wv, acc);
+        } else {
             j2f_item<M>(src, dst, n, uniform_i64(it), acc);
+        }
         if (red) {
             wave_reduce_m<OP, M>(acc);
             if ((threadIdx.x & (kWave - 1)) == 0)
@@ -1478,7 +1480,7 @@ __device__ __forceinline__ void fused_program(const DProg &prog, const DInst &in
 {
     constexpr bool k3D = KMASK == kFamFused3;
     constexpr int kMax = k3D ? kFusedMax3 : kFusedMax2;
-    __shared__ double s_redw[kMax * (kMaxWg / kWave)];
+    __shared__ double s_redw[kMax * (family_max_threads<KMASK>() / kWave)];
     __shared__ double s_redv[kMax];
     const bool first = worker == G - 1;
     int rs = prog.n_pro;
