@@ -201,3 +201,20 @@ def test_fused_3d_grid_sizes_no_reduction_and_batch(gfx):
     for i in range(len(sides)):
         assert np.array_equal(host(us[i]), ref[i][0]) and np.array_equal(host(ws[i]), ref[i][1])
         assert np.array_equal(host(rs[i]), ref[i][2])
+
+
+@pytest.mark.parametrize("n", [27, 28, 29, 31, 33, 34, 54, 55, 124, 125])
+@pytest.mark.parametrize("num_wg", [0, 5])
+def test_fused_3d_tile_edges(gfx, n, num_wg):
+    """Sides where a workgroup's tile of 32 rows (26 of them written in a full
+    pass, 30 in a pass of one sweep) just fits or spills over, and where the
+    last tile is moved up to end at the last row; few workgroups give several
+    tiles to each."""
+    import paper_2306_11686_amd as gf
+    from paper_2306_11686_amd import programs
+    u0 = gi.grid3d(n, seed=n)
+    prog, w0 = programs.jacobi3d(8), u0.copy()
+    a = _run(gfx, prog, u0, w0, 8, gf.Launch.make(num_wg=num_wg) if num_wg else None)
+    b = _run(gfx, prog, u0, w0, 8, gf.Launch.make(tile_y=4, tile_z=8))
+    for x, y in zip(a[:3], b[:3]):
+        assert np.array_equal(x, y)
