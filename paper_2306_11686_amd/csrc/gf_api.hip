@@ -1128,8 +1128,10 @@ Tiling choose_tiling(const DProg &p, const gf_launch *l, const gf_instance *inst
     const unsigned m = program_region_mask(p);
     const bool is3 = m & (1u << GF_R_JACOBI3D), is2 = m & (1u << GF_R_JACOBI2D);
     // a launch that names a tile keeps the fixed defaults for what it leaves
-    // out (the tuner's and the predictor's shapes are meant that way)
-    const bool named = l && (l->wg_size || l->tile_y || l->tile_z);
+    // out (the tuner's and the predictor's shapes are meant that way); so does
+    // a program that records thread ids, whose grid is sized from the tiles
+    const bool named = (l && (l->wg_size || l->tile_y || l->tile_z)) ||
+                       (m & ((1u << GF_R_OWNER) | (1u << GF_R_PHASES)));
     const int64_t n = named ? 0 : stencil_side(p, inst, n_inst);
     t.wg_size = program_is_hist_family(p) ? 1024 : 256;
     if (n > 0 && (m & ~((1u << GF_R_JACOBI3D) | (1u << GF_R_JACOBI2D))) == 0)
@@ -2192,7 +2194,9 @@ static gf_status region_run(gf_ctx *ctx, const gf_program *prog, const gf_instan
                 // items per CU: one workgroup per CU (50 iterations of CG, one
                 // against two, m^3 rows, m = 40 / 50 / 64 / 80: 1.89 / 2.24 /
                 // 2.83 / 4.03 ms and 2.34 / 2.56 / 3.09 / 4.00)
-                if ((program_region_mask(p) & (1u << GF_R_SPMV)) && items <= 8 * (int64_t)ctx->num_cu)
+                const unsigned kinds = program_region_mask(p);
+                if ((kinds & (1u << GF_R_SPMV)) && !(kinds & ((1u << GF_R_OWNER) | (1u << GF_R_PHASES))) &&
+                    items <= 8 * (int64_t)ctx->num_cu)
                     gmax = std::min<int64_t>(cap, ctx->num_cu);
             } else {
                 const DStep &st = p.steps[fused_rs];
@@ -2214,7 +2218,14 @@ static gf_status region_run(gf_ctx *ctx, const gf_program *prog, const gf_instan
                 for (int k = 0; k < p.n_steps; ++k)
                     if (p.steps[k].kind == GF_R_HIST)
                         mask = std::max(mask, p.steps[k].mask);
-                const int want = (launch && launch->num_wg > 0) ? launch->num_wg : cap;
+                // no more workgroups than have a chunk to count or bins to
+                // merge (the barrier's cost grows with its members); a
+                // program that records owners keeps its thread count
+                int64_t want = cap;
+                if (!(program_region_mask(p) & (1u << GF_R_OWNER)))
+                    want = std::min<int64_t>(cap, std::max<int64_t>(items, ((int64_t)mask + 256) / 256));
+                if (launch && launch->num_wg > 0)
+                    want = launch->num_wg;
                 grid = hist_grid(want, mask);
                 if (grid > cap)
                     return fail(ctx, GF_EINVAL, "histogram needs %d co-resident workgroups, capacity %d", grid, cap);

@@ -686,10 +686,12 @@ __device__ __forceinline__ void axpby_item(double *out_, const double *x_, doubl
 // two per 32-bit LDS word, with non-returning LDS atomics, then writes them
 // as its partial row of 16-bit counts.
 // The LDS holds kHistPart counters whatever the bins: with fewer bins there
-// are R = 2^lr copies of each, up to 64, and lane l counts in copy l % R,
+// are R = 2^lr copies of each, up to 8, and lane l counts in copy l % R,
 // which lie next to each other. Skewed keys then meet in fewer lanes of a
-// wavefront on one counter (none at 64 copies, where every lane has a bank
-// of its own).
+// wavefront on one counter. 2^28 keys, skewed in 1,024 bins and uniform in
+// 256, at most 1 / 4 / 8 / 16 / 64 copies: 293 / 183 / 180 / 185 / 196 and
+// 189 / 178 / 179 / 184 / 194 us (the figures for one copy with the slower
+// scan and merge).
 // A scan moves every counter that reached 0x8000 into the global bin. It
 // leaves counters below 0x8000, and a chunk adds at most chunk_keys / R to a
 // counter, so a scan every `every` chunks, every * chunk_keys / R <= 0x8000,
@@ -697,6 +699,8 @@ __device__ __forceinline__ void axpby_item(double *out_, const double *x_, doubl
 // neighbouring counter (moving at 0x1000 saves a third of the scans, but the
 // workgroups' additions to a few hot bins then cost more: 2^28 skewed keys in
 // 4,096 bins 300 us against 226). Integer counts are exact in any order.
+constexpr int kHistMaxCopies = 3;  // log2
+
 struct HistPlan {
     uint32_t mask, lo;      // the part's first bin
     uint32_t words;         // LDS words in use
@@ -823,7 +827,7 @@ __device__ __forceinline__ void hist_phase1_t(uint32_t *s_h, const uint32_t *key
     HistPlan h;
     h.mask = mask;
     h.one = lparts == 0;
-    h.lr = lbins >= 16 ? 0 : (lbins > 10 ? 16 - lbins : 6);
+    h.lr = lbins >= 16 ? 0 : (lbins > 16 - kHistMaxCopies ? 16 - lbins : kHistMaxCopies);
     h.lo = (uint32_t)((worker & ((1 << lparts) - 1)) * kHistPart);
     h.words = h.one ? (uint32_t)((g.nbins + 1) / 2) << h.lr : (uint32_t)kHistPart / 2;
     for (uint32_t i = threadIdx.x * 4; i < h.words; i += blockDim.x * 4)

@@ -1,5 +1,5 @@
 """GPU parity of the histogram where its counters can go wrong: every number
-of copies of a bin (64 up to 1,024 bins, one from 65,536), skewed and constant
+of copies of a bin (eight up to 8,192 bins, one from 65,536), skewed and constant
 keys that fill the 16-bit counters between and after scans, key counts around
 a chunk, and more workgroups than chunks. Counts are whole numbers, so every
 result equals the oracle."""
