@@ -226,14 +226,19 @@ typedef struct {
 } gf_instance;
 
 /* Launch configuration. Zero fields mean "choose": the persistent grid is
- * sized from occupancy; tiles come from the tuning database, else defaults. */
+ * sized from occupancy; tiles come from the tuning database, else defaults,
+ * which follow the region's size where no launch or only num_wg and xcd_remap
+ * are given. A persistent program whose body is one Jacobi region, scalar
+ * steps and the SWAP of its two grids then takes several sweeps per pass over
+ * the grid (same grids; a sum is taken over other partials). */
 typedef struct {
     int32_t wg_size;     /* threads per workgroup (multiple of 64, <= 1024) */
     int32_t num_wg;      /* workgroups (persistent: <= co-resident capacity);
-                            0 = default: persistent, up to two per CU with
-                            balanced rounds of work items; per region, one
-                            per work item up to 16 per CU, SpMV up to the
-                            region kernel's resident capacity */
+                            0 = default: persistent, up to two per CU (one
+                            for small programs with an SpMV) with balanced
+                            rounds of work items; per region, one per work
+                            item up to 16 per CU, SpMV up to the region
+                            kernel's resident capacity, histogram one per CU */
     int32_t tile_y;      /* 3D stencil: rows per tile (1, 2, 4, 8 or 16); 2D stencil:
                           * rows per segment a workgroup marches through (>= 1) */
     int32_t tile_z;      /* 3D stencil z-segment length */
@@ -247,7 +252,8 @@ typedef struct {
 typedef struct {
     int32_t regions;       /* region executions enqueued */
     int32_t launches;      /* kernel launches enqueued */
-    int32_t barriers;      /* grid barriers executed per persistent launch */
+    int32_t barriers;      /* grid barriers of a persistent launch (one per pass
+                              where a pass takes several sweeps) */
     int32_t num_wg;        /* workgroups used (largest launch) */
     int32_t wg_size;
     int32_t rpc_posted;    /* filled by gf_sync: RPC requests serviced so far */
