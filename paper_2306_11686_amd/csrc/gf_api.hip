@@ -2142,6 +2142,19 @@ static gf_status region_run(gf_ctx *ctx, const gf_program *prog, const gf_instan
         const int cap = std::min(4096, persistent_capacity(p, t, ctx->num_cu));
         if (cap <= 0)
             return fail(ctx, GF_EHIP, "occupancy query failed");
+        // What is refused does not depend on the grids' size: instances and
+        // given grids are held to the capacity of the fixed default tile (the
+        // one gf_persistent_capacity reports), which the size-dependent tile's
+        // is not below.
+        if (n_inst > 1 || (launch && launch->num_wg > 0)) {
+            const int limit =
+                std::min(cap, persistent_capacity(p, choose_tiling(p, launch), ctx->num_cu));
+            if (n_inst == 1 && launch->num_wg > limit)
+                return fail(ctx, GF_EINVAL, "num_wg %d exceeds the co-resident capacity %d", launch->num_wg, limit);
+            if (n_inst > 1 && n_inst > limit && !program_is_hist_family(p))
+                return fail(ctx, GF_EINVAL, "%d instances need at least %d co-resident workgroups, capacity %d",
+                            n_inst, n_inst, limit);
+        }
         // Several sweeps per pass where the caller leaves the tile to the
         // library; a given tile is run as given, one sweep per pass. A grid
         // size the plain kernel can hold and the fused one cannot, and a

@@ -218,3 +218,24 @@ def test_fused_3d_tile_edges(gfx, n, num_wg):
     b = _run(gfx, prog, u0, w0, 8, gf.Launch.make(tile_y=4, tile_z=8))
     for x, y in zip(a[:3], b[:3]):
         assert np.array_equal(x, y)
+
+
+def test_capacity_does_not_follow_the_grid_side(gfx):
+    """A grid of workgroups past gf_persistent_capacity is refused whatever
+    tile the library would choose for the grid's side, and so are more
+    instances than that."""
+    import torch
+    import paper_2306_11686_amd as gf
+    from paper_2306_11686_amd import programs
+    prog, n = programs.jacobi3d(4), 8
+    cap = gfx.capacity(prog)
+    u = torch.zeros((n, n, n), dtype=torch.float64, device="cuda")
+    def instance():
+        return gf.Instance.make({0: u.clone(), 1: u.clone(), 2: torch.zeros(4, dtype=torch.float64, device="cuda")},
+                                scalars(), ip=(n,))
+    with pytest.raises(gf.GfError):
+        gfx.run(prog, instance(), mode=gf.GF_EXEC_PERSISTENT, launch=gf.Launch.make(num_wg=cap + 1))
+    with pytest.raises(gf.GfError):
+        gfx.run(prog, [instance() for _ in range(cap + 1)], mode=gf.GF_EXEC_PERSISTENT)
+    gfx.run(prog, instance(), mode=gf.GF_EXEC_PERSISTENT, launch=gf.Launch.make(num_wg=cap))
+    gfx.sync()
