@@ -1121,7 +1121,7 @@ int64_t stencil_side(const DProg &p, const gf_instance *inst, int n_inst)
 //   multiple of 64, whose rows start on the same channels.
 // Without an instance (the persistent capacity of a program): 3D tiles of 8
 // rows, the largest the tuner takes.
-Tiling choose_tiling(const DProg &p, const gf_launch *l, const gf_instance *inst = nullptr, int n_inst = 0)
+Tiling choose_tiling(const DProg &p, const gf_launch *l, int mode, const gf_instance *inst = nullptr, int n_inst = 0)
 {
     Tiling t;
     std::memset(&t, 0, sizeof t);
@@ -1172,6 +1172,8 @@ Tiling choose_tiling(const DProg &p, const gf_launch *l, const gf_instance *inst
     }
     if (l && l->tile_z)
         t.tile_z = l->tile_z;
+    // a persistent grid would take twice the items in a second round
+    t.lone_x = mode != GF_EXEC_PERSISTENT && t.wg_size <= 128 ? 2 : 1;
     return t;
 }
 
@@ -2035,7 +2037,7 @@ int32_t gf_persistent_capacity(gf_ctx *ctx, const gf_program *prog, int32_t wg_s
         return 0;
     gf_launch l{};
     l.wg_size = wg_size;
-    Tiling t = choose_tiling(p, wg_size > 0 ? &l : nullptr);
+    Tiling t = choose_tiling(p, wg_size > 0 ? &l : nullptr, GF_EXEC_PERSISTENT);
     if (check_tiling(ctx, p, t) != GF_OK)
         return 0;
     hipSetDevice(ctx->device);
@@ -2116,7 +2118,7 @@ static gf_status region_run(gf_ctx *ctx, const gf_program *prog, const gf_instan
             }
         }
     }
-    Tiling t = choose_tiling(p, launch, inst, n_inst);
+    Tiling t = choose_tiling(p, launch, mode, inst, n_inst);
     if ((st = check_tiling(ctx, p, t)) != GF_OK)
         return st;
     // per instance: its own rows per tile when a shape gives them (the 3D
@@ -2148,7 +2150,7 @@ static gf_status region_run(gf_ctx *ctx, const gf_program *prog, const gf_instan
         // is not below.
         if (n_inst > 1 || (launch && launch->num_wg > 0)) {
             const int limit =
-                std::min(cap, persistent_capacity(p, choose_tiling(p, launch), ctx->num_cu));
+                std::min(cap, persistent_capacity(p, choose_tiling(p, launch, mode), ctx->num_cu));
             if (n_inst == 1 && launch->num_wg > limit)
                 return fail(ctx, GF_EINVAL, "num_wg %d exceeds the co-resident capacity %d", launch->num_wg, limit);
             if (n_inst > 1 && n_inst > limit && !program_is_hist_family(p))
@@ -2562,7 +2564,7 @@ bool launch_runnable(gf_ctx *ctx, const DProg &p, const gf_instance *inst, int n
 {
     const std::string saved = ctx->err;
     bool ok = true;
-    const Tiling t = choose_tiling(p, &l, inst, n_inst);
+    const Tiling t = choose_tiling(p, &l, mode, inst, n_inst);
     if (check_tiling(ctx, p, t) != GF_OK)
         ok = false;
     for (int i = 0; ok && i < n_inst; ++i)
@@ -3055,7 +3057,7 @@ int32_t gf_tune_batched(gf_ctx *ctx, const gf_program *prog, const gf_instance *
                 seg_of[kv.first] = bs;
                 // workgroup-milliseconds per work item at the chosen rows
                 double items = 0.0;
-                Tiling tt = choose_tiling(p, &common, inst, n_inst);
+                Tiling tt = choose_tiling(p, &common, mode, inst, n_inst);
                 tt.tile_y = bs;
                 for (int i : kv.second)
                     items += (double)std::max<int64_t>(1, max_items(p, inst[i], tt));
@@ -3067,7 +3069,7 @@ int32_t gf_tune_batched(gf_ctx *ctx, const gf_program *prog, const gf_instance *
                 std::vector<double> wv(n_inst, 0.0);
                 for (int i = 0; i < n_inst; ++i) {
                     per[i].tile_y = seg_of[cls[i]];
-                    Tiling tt = choose_tiling(p, &common, inst, n_inst);
+                    Tiling tt = choose_tiling(p, &common, mode, inst, n_inst);
                     tt.tile_y = per[i].tile_y;
                     const double items = (double)std::max<int64_t>(1, max_items(p, inst[i], tt));
                     wv[i] = variant == 0 ? items * cost_of[cls[i]] : items;

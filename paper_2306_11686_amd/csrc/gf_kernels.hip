@@ -20,17 +20,29 @@ __host__ __device__ inline int64_t cdiv(int64_t a, int64_t b) { return (a + b - 
 
 struct StencilGeom {
     int64_t nxc, nyt, nzs;  // x chunks, y tiles, z segments
+    bool single;            // 3D: one column per thread
 };
 
-// 3D: a work item is a chunk of columns (two per thread) times tile_y rows
-// times a segment of tile_z planes.
+// 3D: a work item is a chunk of columns (two per thread, one for `single`)
+// times tile_y rows times a segment of tile_z planes.
+// An odd side takes one column per thread while its tiles are few: the launch
+// is then bound by the latency of a plane's chain, which two values per thread
+// lengthen; more tiles are bound by the loads, which pairs halve. One against
+// two per thread, us per sweep, side, tile (one-column items): 129 8x64 (32)
+// 168 and 200, 129 4x16 (256) 31 and 38, 177 2x64 (264) 63 and 68, 241 8x64
+// (120) 169 and 204; 255 2x16 (2,032) 80 and 65, 257 4x64 (512) 161 and 131,
+// 415 8x64 (728) 547 and 296. One launch per region of small workgroups
+// (t.lone_x = 2): 161 2x64 in 64 threads (720) 57 and 66.
 __host__ __device__ inline StencilGeom j3_geom(int64_t n, const Tiling &t)
 {
     StencilGeom g;
     const int64_t interior = n > 2 ? n - 2 : 0;
-    g.nxc = cdiv(n, 2 * (int64_t)t.wg_size);
     g.nyt = cdiv(interior, t.tile_y);
     g.nzs = cdiv(interior, t.tile_z);
+    g.nxc = cdiv(n, t.wg_size);
+    g.single = (n & 1) && g.nxc * g.nyt * g.nzs <= t.lone_x * (n < 192 ? 512 : (n < 300 ? 256 : 0));
+    if (!g.single)
+        g.nxc = cdiv(n, 2 * (int64_t)t.wg_size);
     return g;
 }
 
@@ -146,6 +158,85 @@ __device__ __forceinline__ double wave_shl1(double v)
 
 namespace gf {
 
+// 3D 7-point Jacobi, one column per thread (j3_geom's `single`): the thread
+// keeps its column of TY rows of planes z-1, z, z+1 in registers and marches z
+// over a segment, so a value of u is fetched once per tile plus the halo rows
+// and planes; the x-neighbours are re-read from cache.
+template <int TY>
+__device__ __forceinline__ double j3s_item(const double *u_, double *w_, int64_t n, int64_t item, const Tiling &t,
+                                           bool want_red)
+{
+    GF_GLOBAL const double *__restrict__ u = gptr(u_);
+    GF_GLOBAL double *__restrict__ w = gptr(w_);
+    const StencilGeom g = j3_geom(n, t);
+    const int64_t xc = item % g.nxc;
+    const int64_t rest = item / g.nxc;
+    const int64_t yt = rest % g.nyt;
+    const int64_t zs = rest / g.nyt;
+    const int64_t x = xc * blockDim.x + threadIdx.x;
+    const int64_t y0 = 1 + yt * TY;
+    const int ny = (int)(n - 1 - y0 < TY ? n - 1 - y0 : TY);
+    const int64_t z0 = 1 + zs * t.tile_z;
+    const int64_t z1 = (z0 + t.tile_z < n - 1) ? z0 + t.tile_z : n - 1;
+    const bool xload = x < n;
+    const bool xin = x >= 1 && x <= n - 2;
+    const int64_t SY = n, SZ = n * n;
+    const double c6 = 1.0 / 6.0;
+    double mx = -INFINITY;
+    double pm[TY], pc[TY + 2], pn[TY + 2];
+#pragma unroll
+    for (int r = 0; r < TY; ++r)
+        pm[r] = 0.0;
+#pragma unroll
+    for (int r = 0; r < TY + 2; ++r)
+        pc[r] = pn[r] = 0.0;
+    if (xload) {
+        GF_GLOBAL const double *b = u + (z0 - 1) * SZ + y0 * SY + x;
+#pragma unroll
+        for (int r = 0; r < TY; ++r)
+            if (r < ny)
+                pm[r] = b[r * SY];
+        b = u + z0 * SZ + (y0 - 1) * SY + x;
+#pragma unroll
+        for (int r = 0; r < TY + 2; ++r)
+            if (r < ny + 2)
+                pc[r] = b[r * SY];
+    }
+    for (int64_t z = z0; z < z1; ++z) {
+        if (xload) {
+            GF_GLOBAL const double *b = u + (z + 1) * SZ + (y0 - 1) * SY + x;
+#pragma unroll
+            for (int r = 0; r < TY + 2; ++r)
+                if (r < ny + 2)
+                    pn[r] = b[r * SY];
+        }
+        if (xin) {
+            GF_GLOBAL const double *row = u + z * SZ + y0 * SY + x;
+            GF_GLOBAL double *out = w + z * SZ + y0 * SY + x;
+#pragma unroll
+            for (int r = 0; r < TY; ++r) {
+                if (r < ny) {
+                    const double xl = row[r * SY - 1];
+                    const double xr = row[r * SY + 1];
+                    const double v = (((xl + xr) + (pc[r] + pc[r + 2])) + (pm[r] + pn[r + 1])) * c6;
+                    __builtin_nontemporal_store(v, out + r * SY);
+                    if (want_red) {
+                        const double d = fabs(v - pc[r + 1]);
+                        mx = d > mx ? d : mx;
+                    }
+                }
+            }
+        }
+#pragma unroll
+        for (int r = 0; r < TY; ++r)
+            pm[r] = pc[r + 1];
+#pragma unroll
+        for (int r = 0; r < TY + 2; ++r)
+            pc[r] = pn[r];
+    }
+    return mx;
+}
+
 // 3D 7-point Jacobi: each thread owns an x-pair (one 16-byte load
 // per row), a column of TY rows, and marches z. x-neighbours come from the
 // adjacent lanes by DPP shifts; the edge lanes of each wavefront swap their
@@ -160,20 +251,16 @@ namespace gf {
 // without per-row guards; lanes past the row end load a clamped in-bounds
 // address and store nothing. For odd n (ODD) the rows start on 8-byte
 // boundaries, which the 16-byte accesses take, and column n-1 falls to a
-// thread of its own, which loads the pair (n-2, n-1) and keeps the second.
+// thread of its own, which loads the pair (n-2, n-1) and hands the second to
+// its left neighbour.
 template <int TY, bool ODD>
-__device__ __forceinline__ gf_d2 ld_row(GF_GLOBAL const double *p, int r, bool lone)
+__device__ __forceinline__ gf_d2 ld_row(GF_GLOBAL const double *p, int r)
 {
     typedef typename std::conditional<ODD, gf_d2u, gf_d2>::type A;
-    gf_d2 v;
     // r indexes rows y0-1 .. y0+TY; rows y0-1, y0, y0+TY-1, y0+TY are shared
     if (r >= 2 && r <= TY - 1)
-        v = __builtin_nontemporal_load((GF_GLOBAL const A *)p);
-    else
-        v = *(GF_GLOBAL const A *)p;
-    if constexpr (ODD)
-        v.x = lone ? v.y : v.x;
-    return v;
+        return __builtin_nontemporal_load((GF_GLOBAL const A *)p);
+    return *(GF_GLOBAL const A *)p;
 }
 
 // One tile of planes [z0, z1). PF (1 or 2) planes ahead of the computed
@@ -201,6 +288,10 @@ __device__ __forceinline__ double j3v2_tile(GF_GLOBAL const double *__restrict__
     const int64_t SY = n, SZ = n * n;
     const double c6 = 1.0 / 6.0;
     double mx = -INFINITY;
+    // the value of a thread's first column, as its left neighbour sees it
+    // (chosen where it is handed over: a choice beside the load waits for the
+    // plane in flight, and took an odd side's 8-row tiles 1.5 times as long)
+    auto first = [&](const gf_d2 &c) -> double { return lone ? c.y : c.x; };
     // pm: plane z-1 (own rows); pc: plane z; pn: plane z+1; pa: z+2 (PF = 2);
     // pf: the plane being requested (z+1+PF)
     gf_d2 pm[TY], pc[TY + 2], pn[TY + 2], pa[PF == 2 ? TY + 2 : 1], pf[TY + 2];
@@ -208,32 +299,32 @@ __device__ __forceinline__ double j3v2_tile(GF_GLOBAL const double *__restrict__
     GF_GLOBAL const double *col = u + (y0 - 1) * SY + xs;  // row y0-1 of plane 0
 #pragma unroll
     for (int r = 0; r < TY; ++r)
-        pm[r] = (FULL || r < ny) ? ld_row<TY, ODD>(col + (z0 - 1) * SZ + (r + 1) * SY, r + 1, lone) : zero2;
+        pm[r] = (FULL || r < ny) ? ld_row<TY, ODD>(col + (z0 - 1) * SZ + (r + 1) * SY, r + 1) : zero2;
     // planes z0 and z0+1 exist (z0+1 <= z1 <= n-1); z0+2 may be past the grid
 #pragma unroll
     for (int r = 0; r < TY + 2; ++r) {
-        pc[r] = (FULL || r < ny + 2) ? ld_row<TY, ODD>(col + z0 * SZ + r * SY, r, lone) : zero2;
-        pn[r] = (FULL || r < ny + 2) ? ld_row<TY, ODD>(col + (z0 + 1) * SZ + r * SY, r, lone) : zero2;
+        pc[r] = (FULL || r < ny + 2) ? ld_row<TY, ODD>(col + z0 * SZ + r * SY, r) : zero2;
+        pn[r] = (FULL || r < ny + 2) ? ld_row<TY, ODD>(col + (z0 + 1) * SZ + r * SY, r) : zero2;
         pf[r] = zero2;
     }
     if constexpr (PF == 2) {
         const bool have = z0 + 2 <= z1;
 #pragma unroll
         for (int r = 0; r < TY + 2; ++r)
-            pa[r] = (have && (FULL || r < ny + 2)) ? ld_row<TY, ODD>(col + (z0 + 2) * SZ + r * SY, r, lone) : zero2;
+            pa[r] = (have && (FULL || r < ny + 2)) ? ld_row<TY, ODD>(col + (z0 + 2) * SZ + r * SY, r) : zero2;
     }
     for (int64_t z = z0; z < z1; ++z) {
         if (z + 1 + PF <= z1) {
 #pragma unroll
             for (int r = 0; r < TY + 2; ++r)
                 if (FULL || r < ny + 2)
-                    pf[r] = ld_row<TY, ODD>(col + (z + 1 + PF) * SZ + r * SY, r, lone);
+                    pf[r] = ld_row<TY, ODD>(col + (z + 1 + PF) * SZ + r * SY, r);
         }
         const int par = (int)(z & 1);
         if (lane == 0) {
 #pragma unroll
             for (int r = 0; r < TY; ++r)
-                s_edge[par][wv][r][0] = pc[r + 1].x;
+                s_edge[par][wv][r][0] = first(pc[r + 1]);
         }
         if (lane == kWave - 1) {
 #pragma unroll
@@ -263,7 +354,7 @@ __device__ __forceinline__ double j3v2_tile(GF_GLOBAL const double *__restrict__
             if (FULL || r < ny) {
                 const gf_d2 c = pc[r + 1];
                 const double sl = wave_shr1(c.y);
-                const double sr = wave_shl1(c.x);
+                const double sr = wave_shl1(first(c));
                 const double el = wv > 0 ? s_edge[par][wv - 1][r][1] : gl[r];
                 const double er = wv < nw - 1 ? s_edge[par][wv + 1][r][0] : gr[r];
                 const double xl = lane == 0 ? el : sl;
@@ -1062,6 +1153,8 @@ __device__ __forceinline__ double region_item(const DStep &st, void *const *op, 
     switch (st.kind) {
     case GF_R_JACOBI3D:
         if constexpr ((KMASK >> GF_R_JACOBI3D) & 1u) {
+            if (j3_geom(n, t).single)
+                return j3s_item<TY>((const double *)op[0], (double *)op[1], n, item, t, red);
             return j3v2_item<TY, PF>((const double *)op[0], (double *)op[1], n, item, t, red);
         }
         break;
@@ -1354,6 +1447,10 @@ constexpr int persistent_min_waves()
     if (KMASK == kFamFused2)
         return 3;
     if (KMASK == kFamFused3)
+        return 2;
+    // 3D tiles of four rows: 256 registers and a few more, which would leave
+    // one workgroup per CU
+    if (((KMASK >> GF_R_JACOBI3D) & 1u) && TY == 4)
         return 2;
     if (((KMASK >> GF_R_SPMV) & 1u) && !((KMASK >> GF_R_JACOBI3D) & 1u))
         return 4;
@@ -1875,15 +1972,19 @@ __device__ inline void run_glue(const RegionLaunch &rl, const RpcRing &rpc, int3
     }
 }
 
-template <unsigned KMASK>
+// The 3D stencil's tiles need a register or two more than this many waves
+// leave; the compiler fits them without spilling.
+template <unsigned KMASK, int TY, int PF>
 constexpr int region_min_waves()
 {
+    if (KMASK == ((1u << GF_R_JACOBI3D) | (1u << GF_R_OWNER)))
+        return TY == 1 ? 7 - PF : (TY == 4 ? 3 : 1);
     return (KMASK >> GF_R_SPMV) & 1u ? 4 : 1;
 }
 
 template <unsigned KMASK, int TY, int PF>
 __global__ void __launch_bounds__(family_max_threads<KMASK>())
-    __attribute__((amdgpu_waves_per_eu(region_min_waves<KMASK>()))) k_region(RegionLaunch rl, Tiling t, Scratch scr,
+    __attribute__((amdgpu_waves_per_eu(region_min_waves<KMASK, TY, PF>()))) k_region(RegionLaunch rl, Tiling t, Scratch scr,
                                                                          RpcRing rpc)
 {
     __shared__ double s_red[kLdsRed];
@@ -2150,6 +2251,7 @@ int phases_capacity(int wg_size, int num_cu)
 constexpr unsigned kFamJ3 = (1u << GF_R_JACOBI3D) | (1u << GF_R_OWNER);
 static_assert(persistent_min_waves<kFamJ3, 2, 1>() == 3, "3D stencil family mask");
 constexpr unsigned kFamJ2 = (1u << GF_R_JACOBI2D) | (1u << GF_R_OWNER);
+static_assert(region_min_waves<kFamJ3, 1, 1>() == 6, "3D stencil family mask");
 static_assert(persistent_min_waves<kFamJ2, 1, 1>() == 3, "2D stencil family mask");
 constexpr unsigned kFamVec =
     (1u << GF_R_SPMV) | (1u << GF_R_DOT) | (1u << GF_R_AXPBY) | (1u << GF_R_OWNER) | (1u << GF_R_PHASES);

@@ -1,0 +1,25 @@
+"""Tiles and launch rules that follow the grid's side, against the oracle."""
+import numpy as np
+import pytest
+
+import gf_inputs as gi
+from tests.gpu_helpers import run_jacobi3d
+
+pytestmark = pytest.mark.gpu
+
+
+# items of one column per thread: 8; 3 * 127 * 2 = 762 and 3 * 64 * 2 = 384 (limit
+# 512, per region in small workgroups 1,024); 189 * 3 = 567 and 189 * 2 = 378;
+# 96 * 3 = 288 and 96 * 2 = 192 (limit 256); 3 * 80 * 3 = 720; 2 * 38 * 3 = 228
+# and 2 * 38 * 5 = 380; none from side 300 on
+@pytest.mark.parametrize("n,wg,ty,tz", [(65, 256, 8, 64), (129, 64, 1, 64), (129, 64, 2, 64), (191, 256, 1, 64),
+                                        (191, 256, 1, 95), (193, 256, 2, 95), (193, 256, 2, 96), (299, 256, 8, 100),
+                                        (161, 64, 2, 64), (299, 256, 8, 64), (301, 256, 16, 64), (3, 64, 1, 1), (5, 64, 16, 2)])
+def test_odd_sides_with_one_and_two_columns_per_thread(gfx, oracle_lib, n, wg, ty, tz):
+    import paper_2306_11686_amd as gf
+    print(f"odd side n={n} wg={wg} tile {ty}x{tz}", flush=True)
+    u0 = gi.grid3d(n, seed=31)
+    g_ref, r_ref = oracle_lib.jacobi3d(u0, 2)
+    for mode in (gf.GF_EXEC_PERSISTENT, gf.GF_EXEC_PER_REGION):
+        g, r, _ = run_jacobi3d(gfx, u0, 2, mode, launch=gf.Launch.make(wg_size=wg, tile_y=ty, tile_z=tz))
+        assert np.array_equal(g, g_ref) and np.array_equal(r, r_ref)
