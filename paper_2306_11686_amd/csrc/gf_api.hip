@@ -1086,6 +1086,13 @@ unsigned program_region_mask(const DProg &p)
     return m;
 }
 
+// Per-instance shape of a batched run: rows per tile (0: the launch's) and
+// the relative weight of its share of workgroups (<= 0: its work items).
+struct InstShape {
+    int32_t tile_y;
+    double weight;
+};
+
 // Largest length of the program's regions of the kinds in `kinds` over the
 // instances (0: none, or no instance given).
 int64_t region_length(const DProg &p, unsigned kinds, const gf_instance *inst, int n_inst)
@@ -1121,17 +1128,21 @@ int64_t stencil_side(const DProg &p, const gf_instance *inst, int n_inst)
 //   multiple of 64, whose rows start on the same channels.
 // Without an instance (the persistent capacity of a program): 3D tiles of 8
 // rows, the largest the tuner takes.
-Tiling choose_tiling(const DProg &p, const gf_launch *l, int mode, const gf_instance *inst = nullptr, int n_inst = 0)
+Tiling choose_tiling(const DProg &p, const gf_launch *l, int mode, const gf_instance *inst = nullptr, int n_inst = 0,
+                     const InstShape *shape = nullptr)
 {
     Tiling t;
     std::memset(&t, 0, sizeof t);
     const unsigned m = program_region_mask(p);
     const bool is3 = m & (1u << GF_R_JACOBI3D), is2 = m & (1u << GF_R_JACOBI2D);
     // a launch that names a tile keeps the fixed defaults for what it leaves
-    // out (the tuner's and the predictor's shapes are meant that way); so does
-    // a program that records thread ids, whose grid is sized from the tiles
-    const bool named = (l && (l->wg_size || l->tile_y || l->tile_z)) ||
+    // out (the tuner's and the predictor's shapes are meant that way); so do a
+    // program that records thread ids, whose grid is sized from the tiles, and
+    // 3D instances with their own rows per tile, which have to be the launch's
+    bool named = (l && (l->wg_size || l->tile_y || l->tile_z)) ||
                        (m & ((1u << GF_R_OWNER) | (1u << GF_R_PHASES)));
+    for (int i = 0; is3 && shape && i < n_inst; ++i)
+        named = named || shape[i].tile_y > 0;
     const int64_t n = named ? 0 : stencil_side(p, inst, n_inst);
     t.wg_size = program_is_hist_family(p) ? 1024 : 256;
     if (n > 0 && (m & ~((1u << GF_R_JACOBI3D) | (1u << GF_R_JACOBI2D))) == 0)
@@ -1578,13 +1589,6 @@ std::string graph_key(const DProg &p, const gf_instance *inst, int n_inst, const
 }
 
 }  // namespace
-
-// Per-instance shape of a batched run: rows per tile (0: the launch's) and
-// the relative weight of its share of workgroups (<= 0: its work items).
-struct InstShape {
-    int32_t tile_y;
-    double weight;
-};
 
 // ---- fused sweeps (gf_fused.h) ------------------------------------------
 // A program whose body is one stencil region, scalar steps and, after the
@@ -2118,7 +2122,7 @@ static gf_status region_run(gf_ctx *ctx, const gf_program *prog, const gf_instan
             }
         }
     }
-    Tiling t = choose_tiling(p, launch, mode, inst, n_inst);
+    Tiling t = choose_tiling(p, launch, mode, inst, n_inst, shape);
     if ((st = check_tiling(ctx, p, t)) != GF_OK)
         return st;
     // per instance: its own rows per tile when a shape gives them (the 3D

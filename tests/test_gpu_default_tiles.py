@@ -23,3 +23,34 @@ def test_odd_sides_with_one_and_two_columns_per_thread(gfx, oracle_lib, n, wg, t
     for mode in (gf.GF_EXEC_PERSISTENT, gf.GF_EXEC_PER_REGION):
         g, r, _ = run_jacobi3d(gfx, u0, 2, mode, launch=gf.Launch.make(wg_size=wg, tile_y=ty, tile_z=tz))
         assert np.array_equal(g, g_ref) and np.array_equal(r, r_ref)
+
+
+@pytest.mark.parametrize("mode", ["persistent", "per_region"])
+def test_rows_per_tile_of_3d_instances_whatever_the_side(gfx, oracle_lib, mode):
+    """Instances that give their rows per tile and leave the rest of the
+    launch out run with the fixed default tile: eight rows are taken, others
+    refused, also on small grids, whose own default is another."""
+    import torch
+    import paper_2306_11686_amd as gf
+    from paper_2306_11686_amd import programs
+    from tests.gpu_helpers import dev, host, scalars
+    m = gf.GF_EXEC_PERSISTENT if mode == "persistent" else gf.GF_EXEC_PER_REGION
+    sides, sweeps = [33, 20], 4
+    grids = [gi.grid3d(n, seed=40 + n) for n in sides]
+    prog = programs.jacobi3d(sweeps)
+
+    def instances():
+        us = [dev(g) for g in grids]
+        rs = [torch.zeros(sweeps, dtype=torch.float64, device="cuda") for _ in sides]
+        return us, [gf.Instance.make({0: u, 1: u.clone(), 2: r}, scalars(), ip=(n,))
+                    for u, r, n in zip(us, rs, sides)]
+
+    for rows in ((8, 8), (8, 0), (0, 0)):
+        us, insts = instances()
+        gfx.run_batched(prog, insts, [gf.Launch.make(tile_y=r) for r in rows], mode=m)
+        gfx.sync()
+        for u, g in zip(us, grids):
+            assert np.array_equal(host(u), oracle_lib.jacobi3d(g, sweeps)[0]), rows
+    for rows in ((2, 2), (4, 8), (0, 2)):
+        with pytest.raises(gf.GfError):
+            gfx.run_batched(prog, instances()[1], [gf.Launch.make(tile_y=r) for r in rows], mode=m)
