@@ -227,10 +227,11 @@ typedef struct {
 
 /* Launch configuration. Zero fields mean "choose": the persistent grid is
  * sized from occupancy; tiles come from the tuning database, else defaults,
- * which follow the region's size where no launch or only num_wg and xcd_remap
- * are given. A persistent program whose body is one Jacobi region, scalar
- * steps and the SWAP of its two grids then takes several sweeps per pass over
- * the grid (same grids; a sum is taken over other partials). */
+ * which follow the region's size where no launch is given or its wg_size,
+ * tile_y, tile_z and prefetch are 0. A persistent program whose body is one
+ * Jacobi region, scalar steps and the SWAP of its two grids then takes several
+ * sweeps per pass over the grid, if items is 0 too (same grids; a sum is taken
+ * over other partials). */
 typedef struct {
     int32_t wg_size;     /* threads per workgroup (multiple of 64, <= 1024) */
     int32_t num_wg;      /* workgroups (persistent: <= co-resident capacity);

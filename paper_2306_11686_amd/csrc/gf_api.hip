@@ -1139,7 +1139,7 @@ Tiling choose_tiling(const DProg &p, const gf_launch *l, int mode, const gf_inst
     // out (the tuner's and the predictor's shapes are meant that way); so do a
     // program that records thread ids, whose grid is sized from the tiles, and
     // 3D instances with their own rows per tile, which have to be the launch's
-    bool named = (l && (l->wg_size || l->tile_y || l->tile_z)) ||
+    bool named = (l && (l->wg_size || l->tile_y || l->tile_z || l->prefetch)) ||
                        (m & ((1u << GF_R_OWNER) | (1u << GF_R_PHASES)));
     for (int i = 0; is3 && shape && i < n_inst; ++i)
         named = named || shape[i].tile_y > 0;

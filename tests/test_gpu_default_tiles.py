@@ -54,3 +54,22 @@ def test_rows_per_tile_of_3d_instances_whatever_the_side(gfx, oracle_lib, mode):
     for rows in ((2, 2), (4, 8), (0, 2)):
         with pytest.raises(gf.GfError):
             gfx.run_batched(prog, instances()[1], [gf.Launch.make(tile_y=r) for r in rows], mode=m)
+
+
+@pytest.mark.parametrize("mode", ["persistent", "per_region"])
+def test_prefetch_names_the_fixed_tile(gfx, oracle_lib, mode):
+    """prefetch = 2 alone: a 3D launch keeps the fixed default tile, and a 2D
+    one, whose fixed tile has 16 rows, is refused at every side."""
+    import paper_2306_11686_amd as gf
+    from tests.gpu_helpers import run_jacobi2d
+    m = gf.GF_EXEC_PERSISTENT if mode == "persistent" else gf.GF_EXEC_PER_REGION
+    l = gf.Launch.make(prefetch=2)
+    for n in (33, 64):
+        u0 = gi.grid3d(n, seed=50 + n)
+        g, r, st = run_jacobi3d(gfx, u0, 5, m, launch=l)
+        g_ref, r_ref = oracle_lib.jacobi3d(u0, 5)
+        assert np.array_equal(g, g_ref) and np.array_equal(r, r_ref)
+        assert st["wg_size"] == 256
+    for n in (64, 512, 2048):
+        with pytest.raises(gf.GfError):
+            run_jacobi2d(gfx, gi.grid2d(n, seed=3), 2, m, launch=l)
