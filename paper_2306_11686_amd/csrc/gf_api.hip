@@ -2125,19 +2125,27 @@ static gf_status region_run(gf_ctx *ctx, const gf_program *prog, const gf_instan
     Tiling t = choose_tiling(p, launch, mode, inst, n_inst, shape);
     if ((st = check_tiling(ctx, p, t)) != GF_OK)
         return st;
+    // What is refused does not depend on the grids' size: what the fixed
+    // default tile does not hold is refused also where the tile follows them.
+    const Tiling fixed = choose_tiling(p, launch, mode);
+    if ((st = check_tiling(ctx, p, fixed)) != GF_OK)
+        return st;
     // per instance: its own rows per tile when a shape gives them (the 3D
     // stencil's rows are compiled into the kernel, so they must agree)
     std::vector<Tiling> ti(n_inst, t);
     for (int i = 0; i < n_inst; ++i) {
+        Tiling tf = fixed;
         if (shape && shape[i].tile_y > 0) {
             if ((program_region_mask(p) & (1u << GF_R_JACOBI3D)) && shape[i].tile_y != t.tile_y)
                 return fail(ctx, GF_EINVAL, "instance %d: 3D stencil rows per tile %d differ from the launch's %d", i,
                             shape[i].tile_y, t.tile_y);
-            ti[i].tile_y = shape[i].tile_y;
+            ti[i].tile_y = tf.tile_y = shape[i].tile_y;
             if ((st = check_tiling(ctx, p, ti[i])) != GF_OK)
                 return st;
         }
         if ((st = check_instance(ctx, p, inst[i], ti[i], i)) != GF_OK)
+            return st;
+        if (std::memcmp(&tf, &ti[i], sizeof tf) != 0 && (st = check_instance(ctx, p, inst[i], tf, i)) != GF_OK)
             return st;
     }
     if (stats)
@@ -2148,13 +2156,11 @@ static gf_status region_run(gf_ctx *ctx, const gf_program *prog, const gf_instan
         const int cap = std::min(4096, persistent_capacity(p, t, ctx->num_cu));
         if (cap <= 0)
             return fail(ctx, GF_EHIP, "occupancy query failed");
-        // What is refused does not depend on the grids' size: instances and
-        // given grids are held to the capacity of the fixed default tile (the
-        // one gf_persistent_capacity reports), which the size-dependent tile's
-        // is not below.
+        // instances and given grids are held to the capacity of the fixed
+        // default tile (the one gf_persistent_capacity reports), which the
+        // size-dependent tile's is not below
         if (n_inst > 1 || (launch && launch->num_wg > 0)) {
-            const int limit =
-                std::min(cap, persistent_capacity(p, choose_tiling(p, launch, mode), ctx->num_cu));
+            const int limit = std::min(cap, persistent_capacity(p, fixed, ctx->num_cu));
             if (n_inst == 1 && launch->num_wg > limit)
                 return fail(ctx, GF_EINVAL, "num_wg %d exceeds the co-resident capacity %d", launch->num_wg, limit);
             if (n_inst > 1 && n_inst > limit && !program_is_hist_family(p))

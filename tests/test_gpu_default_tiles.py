@@ -73,3 +73,28 @@ def test_prefetch_names_the_fixed_tile(gfx, oracle_lib, mode):
     for n in (64, 512, 2048):
         with pytest.raises(gf.GfError):
             run_jacobi2d(gfx, gi.grid2d(n, seed=3), 2, m, launch=l)
+
+
+def test_reduction_capacity_does_not_follow_the_grid_side(gfx):
+    """The largest 2D grids have more reduction tiles of the fixed 16 rows
+    than the scratch holds, and are refused also where the default tile has
+    32 rows; a side below the limit is accepted."""
+    import torch
+    import paper_2306_11686_amd as gf
+    from paper_2306_11686_amd import programs
+    from tests.gpu_helpers import scalars
+    n = 92700                                   # ceil(n / 512) * ceil((n - 2) / 16) = 182 * 5794 > 2^20
+    if torch.cuda.mem_get_info()[0] < (20 << 30) + 16 * n * n:
+        pytest.skip("two grids of this side do not fit the card")
+    u = torch.empty(n * n, dtype=torch.float64, device="cuda")
+    w = torch.empty(n * n, dtype=torch.float64, device="cuda")
+    r = torch.zeros(1, dtype=torch.float64, device="cuda")
+    inst = gf.Instance.make({0: u, 1: w, 2: r}, scalars(), ip=(n,))
+    for mode in (gf.GF_EXEC_PER_REGION, gf.GF_EXEC_PERSISTENT):
+        with pytest.raises(gf.GfError):
+            gfx.run(programs.jacobi2d(1), inst, mode=mode)
+    ok = gf.Instance.make({0: u, 1: w, 2: r}, scalars(), ip=(92000,))   # 180 * 5750 < 2^20
+    gfx.run(programs.jacobi2d(1), ok, mode=gf.GF_EXEC_PER_REGION)
+    gfx.sync()
+    del u, w, inst, ok
+    torch.cuda.empty_cache()
