@@ -581,8 +581,8 @@ __device__ __forceinline__ void j3f_item(const double *u_, double *w_, J3fEdges<
     const int64_t ylo = 1 + yt * g.height;
     const int64_t yhi = ylo + g.height < n - 1 ? ylo + g.height : n - 1;
     const int64_t ymax = n > kJ3fTile ? n - kJ3fTile : 0;
-    int64_t r0 = ylo - M > 0 ? ylo - M : 0;
-    r0 = (r0 < ymax ? r0 : ymax) + wv * kJ3fRows;
+    int64_t rt = ylo - M > 0 ? ylo - M : 0;  // the tile's first row
+    rt = rt < ymax ? rt : ymax;
     const int64_t halo = (M + 1) & ~1;
     const int64_t cols = (n + 1) & ~(int64_t)1;
     const int64_t xa = c * g.width;
@@ -592,12 +592,14 @@ __device__ __forceinline__ void j3f_item(const double *u_, double *w_, J3fEdges<
 #pragma unroll
     for (int s = 0; s < M; ++s)
         acc[s] = -INFINITY;
-    // the rows the stages compute, and the columns they load
-    const bool edge = x0 == 0 || x0 + 128 >= n || r0 == 0 || r0 + kJ3fRows >= n;
+    // the rows the stages compute, and the columns they load; the same for all
+    // wavefronts of the workgroup, which have to meet at one barrier (not at
+    // the two versions' own)
+    const bool edge = x0 == 0 || x0 + 128 >= n || rt == 0 || rt + kJ3fTile >= n;
     // uniform: kept in scalar registers
     auto uni = [](int64_t v) -> int32_t { return __builtin_amdgcn_readfirstlane((int32_t)v); };
-    const int32_t side = uni(n), xs = uni(x0), xl = uni(xa), xh = uni(xa + g.width), rs = uni(r0), yl = uni(ylo),
-                  yh = uni(yhi), zl = uni(z0), zh = uni(z1);
+    const int32_t side = uni(n), xs = uni(x0), xl = uni(xa), xh = uni(xa + g.width),
+                  rs = uni(rt) + wv * kJ3fRows, yl = uni(ylo), yh = uni(yhi), zl = uni(z0), zh = uni(z1);
     if (__builtin_amdgcn_readfirstlane(edge))
         j3f_tile<M, true>(gptr(u_), gptr(w_), edges, side, xs, xl, xh, rs, yl, yh, zl, zh, wv, acc);
     else
