@@ -346,6 +346,11 @@ __device__ __forceinline__ void j2f_item(const double *u_, double *w_, int64_t n
 // per SIMD.
 // Only run when the two buffers' outer layers agree (the kernel compares
 // them first), so a point of the outer layer keeps its value at every stage.
+// Where they differ every pass takes one sweep (30 sweeps, us, agreeing,
+// differing, a sweep at a time with the fixed tile: side 64 233 / 313 / 4,938,
+// 256 1,056 / 2,197 / 5,655, 512 5,790 / 12,700 / 13,440). Three sweeps with the
+// outer values of the next two read where a stage needs them were no faster
+// (13,200 at 512) and slowed the others by 8 %.
 // ---------------------------------------------------------------------------
 
 constexpr int kJ3fRows = 4;    // rows per wavefront
@@ -419,8 +424,8 @@ struct J3fEdges {
 };
 
 // Planes [z0, z1), rows [ylo, yhi) of u^(k+M), by a wavefront that holds rows
-// [r0, r0 + kJ3fRows). EDGE: these rows or the columns touch the outer layer. acc[s]: the lane's max |difference| of
-// sweep k + s + 1.
+// [r0, r0 + kJ3fRows). EDGE: the tile's rows or columns touch the outer
+// layer. acc[s]: the lane's max |difference| of sweep k + s + 1.
 template <int M, bool EDGE>
 __device__ __forceinline__ void j3f_tile(GF_GLOBAL const double *__restrict__ u, GF_GLOBAL double *__restrict__ w,
                                          J3fEdges<M> &edges, int32_t n, int32_t x0, int32_t xa, int32_t xb, int32_t r0,

@@ -239,3 +239,54 @@ def test_capacity_does_not_follow_the_grid_side(gfx):
         gfx.run(prog, [instance() for _ in range(cap + 1)], mode=gf.GF_EXEC_PERSISTENT)
     gfx.run(prog, instance(), mode=gf.GF_EXEC_PERSISTENT, launch=gf.Launch.make(num_wg=cap))
     gfx.sync()
+
+
+def _passes(kind, sweeps):
+    """Fused passes of a run: full ones, then three sweeps, the last alone."""
+    full, n = (7 if kind == 2 else 3), 0
+    while sweeps > 0:
+        sweeps -= full if sweeps > full else (3 if sweeps > 3 else 1)
+        n += 1
+    return n
+
+
+@pytest.mark.parametrize("n,num_wg", [(29, 0), (40, 3), (64, 0), (131, 0), (258, 100)])
+def test_fused_3d_runs_the_passes_it_reports(gfx, n, num_wg):
+    """A 3D run whose tile is left to the library takes the fused kernel
+    (512 threads, one barrier per pass and one after the comparison of the
+    outer layers), with few long segments and many short ones, and gives what
+    a sweep at a time gives, also where the two buffers' outer layers differ."""
+    import paper_2306_11686_amd as gf
+    from paper_2306_11686_amd import programs
+    u0 = gi.um11(21, 32, np.arange(n ** 3, dtype=np.uint64)).reshape(n, n, n)
+    given = gf.Launch.make(wg_size=256, tile_y=4, tile_z=32)
+    own = gf.Launch.make(num_wg=num_wg) if num_wg else None
+    for sweeps in (4, 9, 11):
+        prog = programs.jacobi3d(sweeps)
+        for w0 in (u0, _outer_differs(u0, 22)):
+            a = _run(gfx, prog, u0, w0, sweeps, own)
+            b = _run(gfx, prog, u0, w0, sweeps, given)
+            assert all(np.array_equal(a[k], b[k]) for k in range(3))
+            assert a[4]["wg_size"] == 512 and a[4]["barriers"] == _passes(3, sweeps) + 1
+            assert b[4]["barriers"] == sweeps
+
+
+def test_fused_batches_take_the_fused_kernels(gfx):
+    """Batches of instances run fused too: 128 threads in 2D, 512 in 3D, and
+    the barriers of the longest instance."""
+    import torch
+    import paper_2306_11686_amd as gf
+    from paper_2306_11686_amd import programs
+    sweeps = 16
+    for kind, sides, grid, prog in ((2, [400, 65, 3], gi.grid2d, programs.jacobi2d(sweeps)),
+                                    (3, [33, 70, 8], gi.grid3d, programs.jacobi3d(sweeps))):
+        insts = []
+        for n in sides:
+            u = dev(grid(n, seed=n))
+            insts.append(gf.Instance.make({0: u, 1: u.clone(), 2: torch.zeros(sweeps, dtype=torch.float64,
+                                                                              device="cuda")}, scalars(), ip=(n,)))
+        st = gfx.run(prog, insts, mode=gf.GF_EXEC_PERSISTENT)
+        gfx.sync()
+        assert st["wg_size"] == (128 if kind == 2 else 512)
+        # the 2D grid of side 3 takes a sweep per pass
+        assert st["barriers"] == (sweeps if kind == 2 else _passes(3, sweeps) + 1)
