@@ -1620,19 +1620,29 @@ int fusable_region(const DProg &p)
     return same ? rs : -1;
 }
 
-// Sweeps of a full pass, and the sides below which a pass takes one.
+// Sweeps of a full pass over an n-sided grid.
 int fused_max(int kind, int64_t n) { return fused_sweeps(kind, n, kFusedMax2 + 1); }
 
 // Planes per segment a batched 3D run's shares are computed with.
 constexpr int32_t kFusedBatchZ = 32;
 
-// Partial values the largest pass over an n-sided grid writes.
+// Partial values the largest pass over an n-sided grid writes (3D: with zlen
+// planes per segment).
 int64_t fused_partials(int kind, int64_t n, int32_t zlen)
 {
     int64_t most = 0;
-    for (int m : {1, 3, kFusedMax2})
-        most = std::max<int64_t>(most, m * fused_items(kind, n, m, zlen));
+    for (int m = 1; m <= fused_max(kind, n); m += 2)
+        if (m == 1 || m == 3 || m == kFusedMax2)
+            most = std::max<int64_t>(most, m * fused_items(kind, n, m, zlen));
     return most;
+}
+
+// What an instance of a batched run may write, whatever segments its group
+// takes (3D: they are no shorter than this).
+int64_t fused_batch_partials(int kind, int64_t n)
+{
+    const int64_t planes = (n - 2 + kFusedMaxSegs3 - 1) / kFusedMaxSegs3;
+    return fused_partials(kind, n, (int32_t)std::max<int64_t>(1, planes));
 }
 
 // The grids of an instance and the arrays its body records into do not
@@ -1827,7 +1837,7 @@ gf_status run_batched(gf_ctx *ctx, const DProg &p, const gf_instance *inst, int 
         } else {
             const DStep &st = p.steps[fused_rs];
             items[i] = fused_wg_items(st.kind, inst[i].ip[st.np], kFusedBatchZ);
-            r = fused_partials(st.kind, inst[i].ip[st.np], 1);  // 3D: whatever segments the group takes
+            r = fused_batch_partials(st.kind, inst[i].ip[st.np]);
         }
         for (int k = 0; k < p.n_steps && fused_rs < 0; ++k)
             if (is_region(p.steps[k].kind) && p.steps[k].red_op != GF_OP_NONE)
@@ -2190,7 +2200,7 @@ static gf_status region_run(gf_ctx *ctx, const gf_program *prog, const gf_instan
         if (n_inst > 1 && fused_rs >= 0) {
             int64_t part = 0;
             for (int i = 0; i < n_inst; ++i)
-                part += fused_partials(p.steps[fused_rs].kind, inst[i].ip[p.steps[fused_rs].np], 1);
+                part += fused_batch_partials(p.steps[fused_rs].kind, inst[i].ip[p.steps[fused_rs].np]);
             if (part > ctx->scr.partials_cap)
                 fused_rs = -1;
         }

@@ -385,7 +385,7 @@ __host__ __device__ inline int32_t j3f_zlen(int64_t n, int M, int64_t G)
 {
     const int64_t in = n > 2 ? n - 2 : 1;
     int64_t best = 0, best_cost = 0;
-    for (int64_t zs = 1; zs <= in && zs <= 64; ++zs) {
+    for (int64_t zs = 1; zs <= in && zs <= kFusedMaxSegs3; ++zs) {
         const int64_t zl = (in + zs - 1) / zs;
         const int64_t items = j3f_geom(n, M, (int32_t)zl).items;
         const int64_t rounds = (items + G - 1) / G;

@@ -28,6 +28,7 @@ constexpr int kFusedMax3 = 3;
 // share a tile's rows.
 constexpr int kFusedWg2 = 128;
 constexpr int kFusedWg3 = 512;
+constexpr int kFusedMaxSegs3 = 64;  // z segments of a 3D pass
 constexpr int kFusedMinIters = 4;  // fewer sweeps: nothing to fuse (the last is a pass of its own)
 constexpr int kFusedMinSide2 = 16;  // smaller 2D grids: one sweep per pass
 

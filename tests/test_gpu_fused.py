@@ -290,3 +290,25 @@ def test_fused_batches_take_the_fused_kernels(gfx):
         assert st["wg_size"] == (128 if kind == 2 else 512)
         # the 2D grid of side 3 takes a sweep per pass
         assert st["barriers"] == (sweeps if kind == 2 else _passes(3, sweeps) + 1)
+
+
+def test_fused_3d_batches_of_large_grids(gfx):
+    """The scratch that a batch reserves for its partials is what its passes
+    can write: two grids of 256 or one of 400 fit it many times over."""
+    import torch
+    import paper_2306_11686_amd as gf
+    from paper_2306_11686_amd import programs
+    sweeps = 7
+    prog = programs.jacobi3d(sweeps)
+    for sides in ((256, 256), (400, 40)):
+        grids = [gi.grid3d(n, seed=60 + i) for i, n in enumerate(sides)]
+        us, ws = [dev(g) for g in grids], [dev(g) for g in grids]
+        rs = [torch.zeros(sweeps, dtype=torch.float64, device="cuda") for _ in sides]
+        st = gfx.run(prog, [gf.Instance.make({0: u, 1: w, 2: r}, scalars(), ip=(n,))
+                            for u, w, r, n in zip(us, ws, rs, sides)], mode=gf.GF_EXEC_PERSISTENT)
+        gfx.sync()
+        assert st["wg_size"] == 512 and st["barriers"] == _passes(3, sweeps) + 1
+        for i, g in enumerate(grids):
+            b = _run(gfx, prog, g, g, sweeps, gf.Launch.make(wg_size=256, tile_y=4, tile_z=32))
+            assert np.array_equal(host(us[i]), b[0]) and np.array_equal(host(ws[i]), b[1])
+            assert np.array_equal(host(rs[i]), b[2])
