@@ -254,10 +254,7 @@ typedef struct {
     int32_t regions;       /* region executions enqueued */
     int32_t launches;      /* kernel launches enqueued */
     int32_t barriers;      /* grid barriers of a persistent launch (one per pass
-                              where a pass takes several sweeps; a 3D run then
-                              compares its two grids' outer layers first, and
-                              only if they differ, which is not known when this
-                              is filled, there is one per sweep) */
+                              where a pass takes several sweeps) */
     int32_t num_wg;        /* workgroups used (largest launch) */
     int32_t wg_size;
     int32_t rpc_posted;    /* filled by gf_sync: RPC requests serviced so far */

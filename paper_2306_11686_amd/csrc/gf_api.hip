@@ -1684,8 +1684,6 @@ int64_t fused_wg_items(int kind, int64_t n, int32_t zlen)
 
 // Grid barriers of a fused run: one per pass, none after a last pass
 // without a reduction; 3D: one after the comparison of the outer layers.
-// Where those differ (only the kernel knows) a pass takes one sweep, and there
-// is a barrier per sweep.
 int64_t fused_barriers(const DProg &p, int rs, int64_t n)
 {
     int64_t passes = 0;

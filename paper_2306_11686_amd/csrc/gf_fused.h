@@ -344,13 +344,15 @@ __device__ __forceinline__ void j2f_item(const double *u_, double *w_, int64_t n
 // three sweeps, 2.4 GB (an eighth of it halos) at 5 TB/s, with the vector
 // units half busy: bound by HBM and by the steps' latency at two wavefronts
 // per SIMD.
-// Only run when the two buffers' outer layers agree (the kernel compares
-// them first), so a point of the outer layer keeps its value at every stage.
-// Where they differ every pass takes one sweep (30 sweeps, us, agreeing,
-// differing, a sweep at a time with the fixed tile: side 64 233 / 313 / 4,938,
-// 256 1,056 / 2,197 / 5,655, 512 5,790 / 12,700 / 13,440). Three sweeps with the
-// outer values of the next two read where a stage needs them were no faster
-// (13,200 at 512) and slowed the others by 8 %.
+// Where the two buffers' outer layers agree (the kernel compares them first) a
+// point of the outer layer keeps its value at every stage. Where they differ
+// (DIFF), sweep k + s leaves there what its buffer holds: the lanes that hold
+// an outer column request its values at the start of a step, outer rows and
+// planes are read as they come. 30 sweeps, us, agreeing, differing, a sweep at
+// a time with the fixed tile: side 64 238 / 260 / 4,938, 256 1,042 / 1,383 /
+// 5,655, 512 5,865 / 8,390 / 13,440. One sweep per pass, as differing layers
+// took at first: 313 / 2,197 / 12,700. All outer values read where they are
+// needed: 13,200 at 512, and 8 % slower where they agree.
 // ---------------------------------------------------------------------------
 
 constexpr int kJ3fRows = 4;    // rows per wavefront
@@ -425,8 +427,9 @@ struct J3fEdges {
 
 // Planes [z0, z1), rows [ylo, yhi) of u^(k+M), by a wavefront that holds rows
 // [r0, r0 + kJ3fRows). EDGE: the tile's rows or columns touch the outer
-// layer. acc[s]: the lane's max |difference| of sweep k + s + 1.
-template <int M, bool EDGE>
+// layer. DIFF: the two buffers' outer layers differ. acc[s]: the lane's
+// max |difference| of sweep k + s + 1.
+template <int M, bool EDGE, bool DIFF>
 __device__ __forceinline__ void j3f_tile(GF_GLOBAL const double *__restrict__ u, GF_GLOBAL double *__restrict__ w,
                                          J3fEdges<M> &edges, int32_t n, int32_t x0, int32_t xa, int32_t xb, int32_t r0,
                                          int32_t ylo, int32_t yhi, int32_t z0, int32_t z1, int wv, double (&acc)[M])
@@ -455,6 +458,13 @@ __device__ __forceinline__ void j3f_tile(GF_GLOBAL const double *__restrict__ u,
             return gf_d2{lone ? v.y : v.x, v.y};
         return v;
     };
+    // DIFF: row y of plane z of sweep k + s, at points of the outer layer
+    auto clamped = [&](int32_t v) -> int32_t { return v < 0 ? 0 : (v > n - 1 ? n - 1 : v); };
+    auto ld_outer = [&](int s, int32_t z, int32_t y) -> gf_d2 {
+        const gf_d2 v = *row_at<const gf_d2u>((s & 1 ? w : u) + clamped(z) * plane + clamped(y) * pitch, xs);
+        return gf_d2{lone ? v.y : v.x, v.y};
+    };
+    const uint32_t xe = 8u * (uint32_t)(by ? x + 1 : (EDGE && x > n - 1 ? n - 1 : x));  // the lane's outer column
     const gf_d2 zero2 = {0.0, 0.0};
     // q[s][slot][row]: stage s's planes
     gf_d2 q[M][3][TY];
@@ -476,6 +486,14 @@ __device__ __forceinline__ void j3f_tile(GF_GLOBAL const double *__restrict__ u,
         constexpr int k = decltype(kc)::value;
         constexpr bool ENDS = decltype(ends)::value;
         constexpr int kc1 = (k + 2) % 3, km = (k + 1) % 3;  // the planes one and two before
+        double xo[M > 1 ? M - 1 : 1][TY];  // stage s + 1's values in the lane's outer column
+        if constexpr (DIFF && EDGE)
+#pragma unroll
+            for (int s = 1; s < M; ++s)
+#pragma unroll
+                for (int j = 0; j < TY; ++j)
+                    xo[s - 1][j] = *row_at<const double>((s & 1 ? w : u) + clamped(z - s) * plane +
+                                                             clamped(r0 + j) * pitch, xe);
         __syncthreads();  // the edge rows of the step before are in LDS, those of the one before that free
         gf_d2 nu[M], nd[M];
 #pragma unroll
@@ -502,8 +520,19 @@ __device__ __forceinline__ void j3f_tile(GF_GLOBAL const double *__restrict__ u,
                 if constexpr (EDGE || ENDS) {
                     const int32_t y = r0 + j;
                     const bool flat = y <= 0 || y >= n - 1 || z - s <= 0 || z - s >= n - 1;
-                    out.x = (bx || flat) ? c.x : out.x;
-                    out.y = (by || flat) ? c.y : out.y;
+                    if constexpr (DIFF) {
+                        if (s < M) {
+                            if constexpr (EDGE) {
+                                out.x = bx ? xo[s < M ? s - 1 : 0][j] : out.x;
+                                out.y = by ? xo[s < M ? s - 1 : 0][j] : out.y;
+                            }
+                            if (flat)
+                                out = ld_outer(s, z - s, y);
+                        }
+                    } else {
+                        out.x = (bx || flat) ? c.x : out.x;
+                        out.y = (by || flat) ? c.y : out.y;
+                    }
                 }
                 // computed here: sunk towards its use in the next steps, the
                 // value keeps all of its inputs in registers
@@ -572,7 +601,7 @@ __device__ __forceinline__ void j3f_tile(GF_GLOBAL const double *__restrict__ u,
 }
 
 // One workgroup item: wavefront wv's rows.
-template <int M>
+template <int M, bool DIFF>
 __device__ __forceinline__ void j3f_item(const double *u_, double *w_, J3fEdges<M> &edges, int64_t n, int32_t zlen,
                                          int64_t item, int wv, double (&acc)[M])
 {
@@ -606,9 +635,9 @@ __device__ __forceinline__ void j3f_item(const double *u_, double *w_, J3fEdges<
     const int32_t side = uni(n), xs = uni(x0), xl = uni(xa), xh = uni(xa + g.width),
                   rs = uni(rt) + wv * kJ3fRows, yl = uni(ylo), yh = uni(yhi), zl = uni(z0), zh = uni(z1);
     if (__builtin_amdgcn_readfirstlane(edge))
-        j3f_tile<M, true>(gptr(u_), gptr(w_), edges, side, xs, xl, xh, rs, yl, yh, zl, zh, wv, acc);
+        j3f_tile<M, true, DIFF>(gptr(u_), gptr(w_), edges, side, xs, xl, xh, rs, yl, yh, zl, zh, wv, acc);
     else
-        j3f_tile<M, false>(gptr(u_), gptr(w_), edges, side, xs, xl, xh, rs, yl, yh, zl, zh, wv, acc);
+        j3f_tile<M, false, DIFF>(gptr(u_), gptr(w_), edges, side, xs, xl, xh, rs, yl, yh, zl, zh, wv, acc);
 }
 
 }  // namespace gf

@@ -1462,10 +1462,11 @@ constexpr int persistent_min_waves()
 // partials, the M values in s_redv (LDS). The others go straight on: no
 // stencil region reads a scalar, and the partials of the next pass go to the
 // other half. last: no barrier is needed after a pass without reductions.
-template <unsigned KMASK, int M, typename Bar>
+// DIFF: the two grids' outer layers differ (3D). edges: LDS of the 3D tile.
+template <unsigned KMASK, int M, bool DIFF, typename Bar>
 __device__ __forceinline__ bool fused_pass(const double *src, double *dst, int64_t n, int32_t zlen, bool red, bool last,
                                            double *part, double *s_redw, double *s_redv, int64_t worker, int64_t G,
-                                           bool first, Bar &barrier)
+                                           bool first, void *edges, Bar &barrier)
 {
     constexpr bool k3D = KMASK == kFamFused3;
     constexpr int OP = k3D ? GF_OP_MAX : GF_OP_SUM;
@@ -1476,8 +1477,7 @@ __device__ __forceinline__ bool fused_pass(const double *src, double *dst, int64
     for (int64_t it = worker * nw + wv; it < items; it += G * nw) {
         double acc[M];
         if constexpr (k3D) {
-            __shared__ J3fEdges<M> s_edges;
-            j3f_item<M>(src, dst, s_edges, n, zlen, uniform_i64(it) / kJ3fWaves, wv, acc);
+            j3f_item<M, DIFF>(src, dst, *(J3fEdges<M> *)edges, n, zlen, uniform_i64(it) / kJ3fWaves, wv, acc);
         } else {
             j2f_item<M>(src, dst, n, uniform_i64(it), acc);
         }
@@ -1583,6 +1583,8 @@ __device__ __forceinline__ void fused_program(const DProg &prog, const DInst &in
     constexpr int kMax = k3D ? kFusedMax3 : kFusedMax2;
     __shared__ double s_redw[kMax * (family_max_threads<KMASK>() / kWave)];
     __shared__ double s_redv[kMax];
+    // 3D: the edge rows, whatever the sweeps of a pass
+    __shared__ typename std::conditional<k3D, J3fEdges<kFusedMax3>, char>::type s_edges;
     const bool first = worker == G - 1;
     int rs = prog.n_pro;
     while (prog.steps[rs].kind >= 32)
@@ -1596,36 +1598,40 @@ __device__ __forceinline__ void fused_program(const DProg &prog, const DInst &in
     __syncthreads();
     const double *src = (const double *)uniform_ptr(s_arr[st.arr[0]]);
     double *dst = (double *)uniform_ptr(s_arr[st.arr[1]]);
-    bool fuse = true;
+    bool differ = false;
     if constexpr (k3D) {
         if (zlen <= 0)
             zlen = j3f_zlen(n, kFusedMax3, G);
         zlen = __builtin_amdgcn_readfirstlane(zlen);
-        // several sweeps per pass only where the two outer layers agree; a
-        // difference leaves this launch's epoch in the group line's word
+        // whether the two outer layers agree: a difference leaves this
+        // launch's epoch in the group line's word
         uint32_t *word = gline + kGroupOuterWord;
         if (!outer3_agrees(gptr(src), gptr((const double *)dst), n, worker, G))
             __hip_atomic_store(word, scr.epoch, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
         if (!barrier(nullptr))
             return;
-        fuse = __builtin_amdgcn_readfirstlane(
-                   (int)__hip_atomic_load(word, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT)) != (int)scr.epoch;
+        differ = __builtin_amdgcn_readfirstlane(
+                     (int)__hip_atomic_load(word, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT)) == (int)scr.epoch;
     }
     const bool serial = first && __builtin_amdgcn_readfirstlane(threadIdx.x / kWave) == 0;
     int parity = 0;
     for (int32_t iter = 0; iter < prog.iters;) {
         const int32_t left = prog.iters - iter;
         double *part = scr.partials + (parity ? scr.partials_cap : 0) + part_off;
-        const int m = fuse ? fused_sweeps(k3D ? GF_R_JACOBI3D : GF_R_JACOBI2D, n, left) : 1;
+        const int m = fused_sweeps(k3D ? GF_R_JACOBI3D : GF_R_JACOBI2D, n, left);
+        auto pass = [&](auto sweeps, auto diff) -> bool {
+            return fused_pass<KMASK, decltype(sweeps)::value, decltype(diff)::value>(
+                src, dst, n, zlen, red, left == 1, part, s_redw, s_redv, worker, G, first, &s_edges, barrier);
+        };
         bool ok;
         if (!k3D && m == kMax)
-            ok = fused_pass<KMASK, kMax>(src, dst, n, zlen, red, false, part, s_redw, s_redv, worker, G, first,
-                                         barrier);
+            ok = pass(std::integral_constant<int, kMax>{}, std::false_type{});
+        else if (k3D && m == 3 && differ)
+            ok = pass(std::integral_constant<int, 3>{}, std::bool_constant<k3D>{});
         else if (m == 3)
-            ok = fused_pass<KMASK, 3>(src, dst, n, zlen, red, false, part, s_redw, s_redv, worker, G, first, barrier);
+            ok = pass(std::integral_constant<int, 3>{}, std::false_type{});
         else
-            ok = fused_pass<KMASK, 1>(src, dst, n, zlen, red, left == 1, part, s_redw, s_redv, worker, G, first,
-                                      barrier);
+            ok = pass(std::integral_constant<int, 1>{}, std::false_type{});
         if (!ok)
             return;
         parity ^= 1;
