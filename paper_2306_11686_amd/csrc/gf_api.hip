@@ -1112,20 +1112,83 @@ int64_t stencil_side(const DProg &p, const gf_instance *inst, int n_inst)
         region_length(p, (1u << GF_R_JACOBI3D) | (1u << GF_R_JACOBI2D), inst, n_inst), 1 << 20);
 }
 
-// Defaults. Streaming regions: 4 elements per thread. Stencils follow the
-// grid side n, so that small grids still give every CU several wavefronts
-// (one launch per sweep, us per sweep, one fixed tile against these rules:
-// 3D 256 x 8 rows x 64 planes, n = 65 / 129 / 257 / 450 / 512: 165 / 173 /
-// 186 / 321 / 450 and 14 / 23 / 75 / 278 / 412; 2D 256 x 16 rows, n = 64 /
-// 512 / 2048: 12.8 / 13.1 / 22.6 and 9.5 / 10.2 / 22.6):
-// - workgroups no wider than a row (two columns per thread);
-// - 2D: n / 128 rows per segment as a power of two, between 2 and 32;
+// Largest 3D side whose default tile in launches per region follows it. Past
+// it the fixed 8 rows x 64 planes is as good or better (us per sweep, the rules
+// below against it: 544 1,149 and 719, 640 1,330 and 1,000, 768 1,780 and
+// 1,570, 1,000 3,335 and 3,090): the grids no longer fit the caches, and fewer
+// halo rows count for more than wavefronts.
+constexpr int64_t kFollow3 = 512;
+
+// Whether a 3D grid's tiles, if few, are planned at one column per thread (a
+// workgroup then covers a row).
+bool one_column(int64_t n) { return (n & 1) && n <= 256; }
+
+// The default tile of an n-sided grid, t.wg_size being set: rows, and planes of
+// a 3D segment, so that small grids still give every CU several wavefronts
+// (one launch per sweep, us per sweep, the fixed tile against these rules:
+// 3D n = 65 / 129 / 257 / 450 / 512: 165 / 173 / 186 / 321 / 450 and 14 / 23 /
+// 75 / 278 / 412; 2D n = 64 / 512 / 2048: 12.8 / 13.1 / 22.6 and 9.5 / 10.2 /
+// 22.6):
+// - 2D: n / 128 rows per segment as a power of two, between 2 and 32; n / 64 in
+//   the persistent kernel, whose barrier costs more with more workgroups (us
+//   per sweep, n / 128 against n / 64: 700 24.5 and 21.6, 1,000 28.8 and 23.6,
+//   2,048 40.9 and 37.9), with 16 at most from side 6,000 (16,384: 910 with 32,
+//   864 with 16);
 // - 3D: 2 rows per tile and z split into the segments that give 3,840
 //   wavefronts (a segment reads two planes more than it writes: no shorter
 //   than 8 planes, 4 below side 96); from side 416, where the rows fill
 //   whole workgroups and halo rows cost more than wavefronts gain, 4 rows and
-//   2,048 wavefronts (n = 450: 278 against 330 us), but for sides that are a
-//   multiple of 64, whose rows start on the same channels.
+//   2,048 wavefronts (n = 450: 278 against 330 us; persistent 512 451 against
+//   519; past side 512, persistent only, 3,840: 576 881 against 1,170 with the
+//   fixed tile, 768 1,920 against 1,960), but in launches per sweep of sides
+//   that are a multiple of 64, whose rows start on the same channels (512: 429
+//   with 4 rows, 416 with 2).
+// G > 0: the caller gave the workgroups, so more and smaller tiles only add
+// halos. The tile is then the one of 2, 4 or 8 (2D: to 32) rows whose rounds of
+// work items read the fewest rows: an item reads two rows and two planes more
+// than it writes (2D: about six rows for the start of its march). us per sweep
+// in 64 / 256 workgroups, the rules above, this one and the fixed tile: 3D 256
+// 586 / 174, 335 / 107, 360 / 192; 2D 1,000 35.0 / 17.7, 21.5 / 16.6, 23.8 / 18.1.
+void follow_side(Tiling &t, int64_t n, bool is3, int mode, int64_t G)
+{
+    auto split = [](int64_t len, int64_t parts) { return (len + parts - 1) / parts; };
+    // few tiles of an odd side take one column per thread
+    const bool lone = is3 && G > 0 && one_column(n);
+    const int64_t cols = split(n, (lone ? 1 : 2) * (int64_t)t.wg_size);
+    const int64_t in = std::max<int64_t>(n - 2, 1);
+    if (G > 0) {
+        int64_t best = INT64_MAX;
+        for (int32_t ty = is3 ? 8 : 32; ty >= 2; ty /= 2)
+            for (int64_t segs = is3 ? std::max<int64_t>(1, in / (n < 96 ? 4 : 8)) : 1; segs >= 1; --segs) {
+                const int64_t tz = is3 ? split(in, segs) : 1;
+                const int64_t items = cols * split(in, ty) * (is3 ? split(in, tz) : 1);
+                const int64_t cost = split(items, G) * (is3 ? (ty + 2) * (tz + 2) : ty + 6);
+                if (cost < best) {
+                    best = cost;
+                    t.tile_y = ty;
+                    t.tile_z = is3 ? (int32_t)tz : t.tile_z;
+                }
+            }
+        return;
+    }
+    const bool persistent = mode == GF_EXEC_PERSISTENT;
+    if (!is3) {
+        t.tile_y = 2;
+        for (int64_t r = persistent ? 256 : 512; r <= n && t.tile_y < (persistent && n >= 6000 ? 16 : 32); r *= 2)
+            t.tile_y *= 2;
+        return;
+    }
+    const bool tall = n >= 416 && (persistent || n % 64 != 0);
+    t.tile_y = tall ? 4 : 2;
+    const int64_t tiles = cols * split(in, t.tile_y);
+    int64_t segs = (tall && n <= kFollow3 ? 2048 : 3840) / (t.wg_size / kWave) / tiles;
+    segs = std::max<int64_t>(1, std::min<int64_t>(segs, in / (n < 96 ? 4 : 8)));
+    t.tile_z = (int32_t)split(in, segs);
+}
+
+// Defaults. Streaming regions: 4 elements per thread. Stencils follow the grid
+// side (follow_side) with workgroups no wider than a row, at two columns per
+// thread; large 3D grids keep the fixed tile.
 // Without an instance (the persistent capacity of a program): 3D tiles of 8
 // rows, the largest the tuner takes.
 Tiling choose_tiling(const DProg &p, const gf_launch *l, int mode, const gf_instance *inst = nullptr, int n_inst = 0,
@@ -1143,22 +1206,23 @@ Tiling choose_tiling(const DProg &p, const gf_launch *l, int mode, const gf_inst
                        (m & ((1u << GF_R_OWNER) | (1u << GF_R_PHASES)));
     for (int i = 0; is3 && shape && i < n_inst; ++i)
         named = named || shape[i].tile_y > 0;
-    const int64_t n = named ? 0 : stencil_side(p, inst, n_inst);
+    int64_t n = named ? 0 : stencil_side(p, inst, n_inst);
+    if (is3 && n > kFollow3 && mode != GF_EXEC_PERSISTENT)
+        n = 0;
     t.wg_size = program_is_hist_family(p) ? 1024 : 256;
-    if (n > 0 && (m & ~((1u << GF_R_JACOBI3D) | (1u << GF_R_JACOBI2D))) == 0)
-        t.wg_size = (int32_t)std::min<int64_t>(256, std::max<int64_t>(64, ((n + 1) / 2 + 63) / 64 * 64));
+    int64_t G = l && l->num_wg > 0 ? l->num_wg : 0;
+    if (n > 0 && (m & ~((1u << GF_R_JACOBI3D) | (1u << GF_R_JACOBI2D))) == 0) {
+        const int64_t threads = is3 && G > 0 && one_column(n) ? n : (n + 1) / 2;
+        t.wg_size = (int32_t)std::min<int64_t>(256, std::max<int64_t>(64, (threads + 63) / 64 * 64));
+    }
     if (program_is_hist_family(p)) {
         // four groups per thread, whose next four are requested ahead; fewer
         // where the chunks would not reach every CU
         const int64_t keys = named ? 0 : region_length(p, 1u << GF_R_HIST, inst, n_inst);
         t.items = keys > 0 && keys < (1 << 21) ? 1 : (keys > 0 && keys < (1 << 22) ? 2 : 4);
     }
-    const bool tall = n >= 416 && n % 64 != 0;
     t.tile_y = is3 ? 8 : (is2 ? 16 : 1);
-    if (n > 0)
-        t.tile_y = is3 && tall ? 4 : 2;
-    for (int64_t r = 512; n > 0 && is2 && !is3 && r <= n && t.tile_y < 32; r *= 2)
-        t.tile_y *= 2;
+    t.tile_z = 64;
     t.prefetch = 1;
     if (!program_is_hist_family(p))
         t.items = 4;
@@ -1168,21 +1232,24 @@ Tiling choose_tiling(const DProg &p, const gf_launch *l, int mode, const gf_inst
             t.wg_size = l->wg_size;
         if (l->tile_y)
             t.tile_y = l->tile_y;
+        if (l->tile_z)
+            t.tile_z = l->tile_z;
         if (l->items)
             t.items = l->items;
         t.xcd_remap = l->xcd_remap;
         if (l->prefetch)
             t.prefetch = l->prefetch;
     }
-    t.tile_z = 64;
-    if (n > 2 && t.wg_size >= kWave && t.tile_y > 0) {
-        const int64_t tiles = ((n + 2 * t.wg_size - 1) / (2 * t.wg_size)) * ((n - 2 + t.tile_y - 1) / t.tile_y);
-        int64_t segs = (tall ? 2048 : 3840) / (t.wg_size / kWave) / tiles;
-        segs = std::max<int64_t>(1, std::min<int64_t>(segs, (n - 2) / (n < 96 ? 4 : 8)));
-        t.tile_z = (int32_t)std::min<int64_t>((n - 2 + segs - 1) / segs, 1 << 20);
+    if (n > 0 && (is2 || is3)) {
+        if (G > 0 && mode == GF_EXEC_PERSISTENT) {
+            // of a batch's workgroups the largest instance's share
+            double all = 0.0;
+            for (int i = 0; i < n_inst; ++i)
+                all += std::pow((double)stencil_side(p, inst + i, 1) / (double)n, is3 ? 3 : 2);
+            G = std::max<int64_t>(1, (int64_t)((double)G / all));
+        }
+        follow_side(t, n, is3, mode, G);
     }
-    if (l && l->tile_z)
-        t.tile_z = l->tile_z;
     // a persistent grid would take twice the items in a second round
     t.lone_x = mode != GF_EXEC_PERSISTENT && t.wg_size <= 128 ? 2 : 1;
     return t;
@@ -1570,7 +1637,7 @@ gf_status enqueue_per_region(gf_ctx *ctx, const DProg &p, const gf_instance &in,
         stats->regions += regions;
         stats->launches += launches;
         stats->num_wg = std::max(stats->num_wg, max_grid);
-        stats->wg_size = t.wg_size;
+        stats->wg_size = std::max(stats->wg_size, t.wg_size);
     }
     return GF_OK;
 }
@@ -2144,6 +2211,9 @@ static gf_status region_run(gf_ctx *ctx, const gf_program *prog, const gf_instan
     std::vector<Tiling> ti(n_inst, t);
     for (int i = 0; i < n_inst; ++i) {
         Tiling tf = fixed;
+        // launches of their own: each instance's default follows its own side
+        if (!shape && n_inst > 1 && (mode == GF_EXEC_PER_REGION || mode == GF_EXEC_PER_REGION_GRAPH))
+            ti[i] = choose_tiling(p, launch, mode, inst + i, 1);
         if (shape && shape[i].tile_y > 0) {
             if ((program_region_mask(p) & (1u << GF_R_JACOBI3D)) && shape[i].tile_y != t.tile_y)
                 return fail(ctx, GF_EINVAL, "instance %d: 3D stencil rows per tile %d differ from the launch's %d", i,
@@ -2309,8 +2379,8 @@ static gf_status region_run(gf_ctx *ctx, const gf_program *prog, const gf_instan
     // GF_EXEC_PER_REGION_GRAPH: capture the per-region launch sequence once
     // per (program, bindings, tilings, stream) and replay it.
     std::string key = graph_key(p, inst, n_inst, t, launch, stream);
-    for (int i = 0; shape && i < n_inst; ++i)
-        key.append((const char *)&ti[i].tile_y, sizeof ti[i].tile_y);
+    for (int i = 0; i < n_inst; ++i)
+        key.append((const char *)&ti[i], sizeof ti[i]);
     auto it = ctx->graphs.find(key);
     if (it == ctx->graphs.end()) {
         hipStream_t cs = ctx->capture_stream;

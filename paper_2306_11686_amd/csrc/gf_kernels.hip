@@ -32,7 +32,7 @@ struct StencilGeom {
 // 168 and 200, 129 4x16 (256) 31 and 38, 177 2x64 (264) 63 and 68, 241 8x64
 // (120) 169 and 204; 255 2x16 (2,032) 80 and 65, 257 4x64 (512) 161 and 131,
 // 415 8x64 (728) 547 and 296. One launch per region of small workgroups
-// (t.lone_x = 2): 161 2x64 in 64 threads (720) 57 and 66.
+// (t.lone_x = 2): 161 2x64 in 64 threads (720) 57 and 66, but 65 2x5 (832) 21 and 19.
 __host__ __device__ inline StencilGeom j3_geom(int64_t n, const Tiling &t)
 {
     StencilGeom g;
@@ -40,7 +40,7 @@ __host__ __device__ inline StencilGeom j3_geom(int64_t n, const Tiling &t)
     g.nyt = cdiv(interior, t.tile_y);
     g.nzs = cdiv(interior, t.tile_z);
     g.nxc = cdiv(n, t.wg_size);
-    g.single = (n & 1) && g.nxc * g.nyt * g.nzs <= t.lone_x * (n < 192 ? 512 : (n < 300 ? 256 : 0));
+    g.single = (n & 1) && g.nxc * g.nyt * g.nzs <= (n < 128 ? 512 : t.lone_x * (n < 192 ? 512 : (n < 300 ? 256 : 0)));
     if (!g.single)
         g.nxc = cdiv(n, 2 * (int64_t)t.wg_size);
     return g;

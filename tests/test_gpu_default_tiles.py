@@ -98,3 +98,65 @@ def test_reduction_capacity_does_not_follow_the_grid_side(gfx):
     gfx.sync()
     del u, w, inst, ok
     torch.cuda.empty_cache()
+
+
+# the sides at which a rule changes, in both orders of a list of instances
+@pytest.mark.parametrize("mode", ["persistent", "per_region", "per_region_graph"])
+@pytest.mark.parametrize("sides", [(33, 129, 20), (20, 255, 64), (257, 3, 96)])
+def test_default_tiles_of_3d_instances(gfx, oracle_lib, mode, sides):
+    """Each instance of a list against the oracle, in a second run of the
+    same list too (a replay in graph mode); with a given number of workgroups
+    the tile is another one. Three sweeps: no fused passes."""
+    import torch
+    import paper_2306_11686_amd as gf
+    from paper_2306_11686_amd import programs
+    from tests.gpu_helpers import dev, host, scalars
+    m = {"persistent": gf.GF_EXEC_PERSISTENT, "per_region": gf.GF_EXEC_PER_REGION,
+         "per_region_graph": gf.GF_EXEC_PER_REGION_GRAPH}[mode]
+    sweeps, grids = 3, [gi.grid3d(n, seed=70 + n) for n in sides]
+    us, ws = [dev(g) for g in grids], [dev(g) for g in grids]
+    rs = [torch.zeros(sweeps, dtype=torch.float64, device="cuda") for _ in sides]
+    insts = [gf.Instance.make({0: u, 1: w, 2: r}, scalars(), ip=(n,)) for u, w, r, n in zip(us, ws, rs, sides)]
+    refs = [oracle_lib.jacobi3d(g, sweeps) for g in grids]
+    for launch in (None, None, gf.Launch.make(num_wg=16), gf.Launch.make(num_wg=100)):
+        for u, w, g in zip(us, ws, grids):
+            u.copy_(dev(g))
+            w.copy_(u)
+        gfx.run(programs.jacobi3d(sweeps), insts, mode=m, launch=launch)
+        gfx.sync()
+        for i, (g_ref, r_ref) in enumerate(refs):
+            assert np.array_equal(host(ws[i]), g_ref) and np.array_equal(host(rs[i]), r_ref), (i, launch)
+
+
+@pytest.mark.parametrize("mode", ["persistent", "per_region"])
+@pytest.mark.parametrize("n", [255, 256, 511, 513, 1025])
+@pytest.mark.parametrize("num_wg", [0, 7, 200])
+def test_default_tiles_2d(gfx, oracle_lib, n, num_wg, mode):
+    import paper_2306_11686_amd as gf
+    from tests.gpu_helpers import run_jacobi2d
+    m = gf.GF_EXEC_PERSISTENT if mode == "persistent" else gf.GF_EXEC_PER_REGION
+    u0 = gi.grid2d(n, seed=80)
+    g, r, _ = run_jacobi2d(gfx, u0, 3, m, launch=gf.Launch.make(num_wg=num_wg) if num_wg else None)
+    g_ref, _, r_comp, _ = oracle_lib.jacobi2d(u0, 3)
+    assert np.array_equal(g, g_ref) and np.all(np.abs(r - r_comp) <= 1e-12 * r_comp)
+
+
+def test_instances_of_a_per_region_run_follow_their_own_side(gfx):
+    """A small grid beside a large one runs the launch it gets alone: the
+    workgroups of the largest launch are those of its own tile."""
+    import paper_2306_11686_amd as gf
+    from paper_2306_11686_amd import programs
+    import torch
+    from tests.gpu_helpers import scalars
+
+    def inst(n):
+        u = torch.zeros((n, n, n), dtype=torch.float64, device="cuda")
+        return gf.Instance.make({0: u, 1: u.clone(), 2: scalars()}, scalars(), ip=(n,))
+
+    a, b = inst(64), inst(300)
+    prog = programs.jacobi3d(1)
+    for mode in (gf.GF_EXEC_PER_REGION, gf.GF_EXEC_PER_REGION_GRAPH):
+        alone = [gfx.run(prog, i, mode=mode)["num_wg"] for i in (a, b)]
+        assert gfx.run(prog, [a, b], mode=mode)["num_wg"] == max(alone)
+        assert gfx.run(prog, [a, a], mode=mode)["num_wg"] == alone[0]
+    gfx.sync()
