@@ -1186,6 +1186,32 @@ void follow_side(Tiling &t, int64_t n, bool is3, int mode, int64_t G)
     t.tile_z = (int32_t)split(in, segs);
 }
 
+// Histogram: groups of four keys per thread and chunk. Four, whose next four
+// are requested ahead, for many keys. For fewer the workgroups that get a chunk
+// count: each zeroes and writes a row of the bins, which the merge reads, and
+// is a member of the persistent kernel's barriers. Up to 64 of them then, or 128
+// of eight groups (us, every CU a chunk early against this: 10^6 keys in 256
+// bins persistent 46 and 39.5, in 65,536 34 and 23; 4 10^6 in 65,536 31.6 and
+// 27.9; 8 10^6 in 256, persistent, four and eight groups 49.7 and 52.8). Launches per region of few bins have short rows and no
+// barrier: fewer groups where the chunks would not reach every CU (2 10^6
+// keys, 256 bins: 18.2 us, 19.1 with the other rule).
+int32_t hist_items(const DProg &p, int64_t keys, int mode)
+{
+    int64_t parts = 1, bins = 1;
+    for (int i = 0; i < p.n_steps; ++i)
+        if (p.steps[i].kind == GF_R_HIST) {
+            parts = std::max(parts, hist_parts(p.steps[i].mask));
+            bins = std::max<int64_t>(bins, (int64_t)p.steps[i].mask + 1);
+        }
+    if (mode != GF_EXEC_PERSISTENT && bins < 16384)
+        return keys < (1 << 21) ? 1 : (keys < (1 << 22) ? 2 : 4);
+    auto chunks = [&](int64_t items) { return (keys + items * 4096 - 1) / (items * 4096) * parts; };
+    for (int32_t items = 1; items <= 8; items *= 2)
+        if (chunks(items) <= 64)
+            return items;
+    return chunks(8) <= 128 ? 8 : 4;
+}
+
 // Defaults. Streaming regions: 4 elements per thread. Stencils follow the grid
 // side (follow_side) with workgroups no wider than a row, at two columns per
 // thread; large 3D grids keep the fixed tile.
@@ -1216,10 +1242,8 @@ Tiling choose_tiling(const DProg &p, const gf_launch *l, int mode, const gf_inst
         t.wg_size = (int32_t)std::min<int64_t>(256, std::max<int64_t>(64, (threads + 63) / 64 * 64));
     }
     if (program_is_hist_family(p)) {
-        // four groups per thread, whose next four are requested ahead; fewer
-        // where the chunks would not reach every CU
         const int64_t keys = named ? 0 : region_length(p, 1u << GF_R_HIST, inst, n_inst);
-        t.items = keys > 0 && keys < (1 << 21) ? 1 : (keys > 0 && keys < (1 << 22) ? 2 : 4);
+        t.items = keys > 0 ? hist_items(p, keys, mode) : 4;
     }
     t.tile_y = is3 ? 8 : (is2 ? 16 : 1);
     t.tile_z = 64;

@@ -997,17 +997,26 @@ __device__ __forceinline__ void hist_phase1(const uint32_t *keys, uint32_t *bins
 }
 
 // Histogram, phase 2: bins[b] += the sum of b's entries over the `rows_used`
-// partial rows (row w holds part w % parts). A workgroup takes tiles of
-// blockDim / 4 bins: eight adjacent bins per thread, 32 threads each with
-// every 32nd row of the part, their sums added in LDS, so that a bin gets one
-// atomic. Bound by the latency of the rows. 256 rows of 65,536 bins took 21
+// partial rows (row w holds part w % parts). A workgroup takes tiles of bins,
+// eight adjacent ones per thread, and so many threads with a slice of the
+// part's rows each, whose sums are added in LDS, that a bin gets one atomic.
+// Bound by the latency of the rows. 256 rows of 65,536 bins took 21
 // us with slices of 16 rows that each added to the bins, and take 8.
-constexpr int kHistSlices = 32;
+// Few rows of many bins have few slices (with 32 always, 31 of 32 threads idle,
+// 2^20 bins and 1,000 keys took 29.9 us in all, 19.0 with one); few bins have
+// threads enough for one row each (256 bins, 25 rows: 17.4 us in all, 18.6 with
+// four slices).
+__host__ __device__ inline int hist_slices(int64_t nbins, int64_t part_rows)
+{
+    return part_rows >= 32 || nbins <= 1 << 17 ? 32 : (part_rows >= 4 ? 4 : 1);
+}
+// Bins of a workgroup's tile.
+__host__ __device__ inline int hist_tile(int threads, int slices) { return threads / slices * 8; }
 
 __device__ __forceinline__ void hist_merge(uint32_t *bins_, const uint32_t *rows_, uint32_t mask, int64_t rows_used,
                                            int64_t block, int64_t nblocks)
 {
-    __shared__ uint32_t s_sum[kMaxWgHist / 4];
+    __shared__ uint32_t s_sum[2 * kMaxWgHist];  // four slices or more
     typedef uint16_t gf_h8 __attribute__((ext_vector_type(8)));
     GF_GLOBAL uint32_t *bins = gptr(bins_);
     GF_GLOBAL const uint16_t *rows = (GF_GLOBAL const uint16_t *)gptr(rows_);
@@ -1015,35 +1024,45 @@ __device__ __forceinline__ void hist_merge(uint32_t *bins_, const uint32_t *rows
     const int lbins = __builtin_popcount(mask);
     const int lparts = lbins > 16 ? lbins - 16 : 0;
     const int64_t per_part = rows_used >> lparts;  // rows of each part
-    const int octs = blockDim.x / kHistSlices;
+    const int slices = hist_slices(nbins, per_part);
+    const int octs = blockDim.x / slices;
     const int o = threadIdx.x % octs, sl = threadIdx.x / octs;
-    const int span = octs * 8;
+    const int span = hist_tile(blockDim.x, slices);
     for (int64_t first = block * span; first < nbins; first += nblocks * span) {
-        if ((int)threadIdx.x < span)
-            s_sum[threadIdx.x] = 0u;
-        __syncthreads();
+        if (slices > 1) {
+            for (int i = threadIdx.x; i < span; i += blockDim.x)
+                s_sum[i] = 0u;
+            __syncthreads();
+        }
         const int64_t b0 = first + o * 8;
         if (b0 < nbins) {
             GF_GLOBAL const uint16_t *p = rows + (b0 / kHistPart) * kHistPart + b0 % kHistPart;
             uint32_t sum[8] = {};
 #pragma unroll 8
-            for (int64_t j = sl; j < per_part; j += kHistSlices) {
+            for (int64_t j = sl; j < per_part; j += slices) {
                 const gf_h8 r = *(GF_GLOBAL const gf_h8 *)(p + (j << lparts) * kHistPart);
 #pragma unroll
                 for (int q = 0; q < 8; ++q)
                     sum[q] += r[q];
             }
 #pragma unroll
-            for (int q = 0; q < 8; ++q)
-                if (sum[q])
+            for (int q = 0; q < 8; ++q) {
+                if (!sum[q])
+                    continue;
+                if (slices > 1)
                     __hip_atomic_fetch_add(&s_sum[q * octs + o], sum[q], __ATOMIC_RELAXED,
                                            __HIP_MEMORY_SCOPE_WORKGROUP);
+                else if (b0 + q < nbins)
+                    __hip_atomic_fetch_add(&bins[b0 + q], sum[q], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            }
         }
+        if (slices == 1)
+            continue;
         __syncthreads();
-        if ((int)threadIdx.x < span && first + threadIdx.x < nbins) {
-            const uint32_t v = s_sum[threadIdx.x % 8 * octs + threadIdx.x / 8];
+        for (int i = threadIdx.x; i < span && first + i < nbins; i += blockDim.x) {
+            const uint32_t v = s_sum[i % 8 * octs + i / 8];
             if (v)
-                __hip_atomic_fetch_add(&bins[first + threadIdx.x], v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                __hip_atomic_fetch_add(&bins[first + i], v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
         }
         __syncthreads();
     }
@@ -2391,7 +2410,8 @@ int64_t hist_parts(uint32_t mask) { return cdiv((int64_t)mask + 1, kHistPart); }
 hipError_t launch_hist_merge(const RegionLaunch &rl, int64_t rows_used, const Scratch &scr, const RpcRing &rpc,
                              int num_cu, hipStream_t s)
 {
-    int64_t g = cdiv((int64_t)rl.step.mask + 1, kMaxWg / 4);
+    const int64_t part_rows = rows_used / hist_parts(rl.step.mask);
+    int64_t g = cdiv((int64_t)rl.step.mask + 1, hist_tile(kMaxWg, hist_slices((int64_t)rl.step.mask + 1, part_rows)));
     if (g > (int64_t)num_cu * 16)
         g = (int64_t)num_cu * 16;
     hipLaunchKernelGGL(k_hist_merge, dim3((unsigned)g), dim3(kMaxWg), 0, s, rl, rows_used, scr, rpc);

@@ -37,3 +37,36 @@ def test_hist_counters(gfx, oracle_lib, mode, kind, nbins, n, num_wg, items):
             launch=gf.Launch.make(num_wg=num_wg, items=items) if num_wg else None)
     gfx.sync()
     assert np.array_equal(host(bins), oracle_lib.hist_u32(keys, nbins, bins=init.copy()))
+
+
+# rows of a part: 1, 3, 4, 31, 32 and 64 (where the merge's slices change); four
+# parts, 69 chunks of 1,024 keys each
+@pytest.mark.parametrize("mode", ["per_region", "persistent"])
+@pytest.mark.parametrize("part_rows", [1, 3, 4, 31, 32, 64])
+def test_merge_of_few_and_many_rows_per_part(gfx, oracle_lib, part_rows, mode):
+    import paper_2306_11686_amd as gf
+    from paper_2306_11686_amd import programs
+    n, nbins = 70001, 1 << 18
+    keys = _keys("skewed", n)
+    bins = dev(np.zeros(nbins, dtype=np.uint32))
+    inst = gf.Instance.make({0: dev(keys), 1: bins}, scalars(), ip=(n,))
+    gfx.run(programs.histogram(nbins), inst,
+            mode=gf.GF_EXEC_PER_REGION if mode == "per_region" else gf.GF_EXEC_PERSISTENT,
+            launch=gf.Launch.make(wg_size=256, items=1, num_wg=4 * part_rows))
+    gfx.sync()
+    assert np.array_equal(host(bins), oracle_lib.hist_u32(keys, nbins))
+
+
+@pytest.mark.parametrize("mode", ["per_region", "persistent"])
+@pytest.mark.parametrize("nbins", [2, 256, 16384, 1 << 17, 1 << 20])
+@pytest.mark.parametrize("n", [3, 5000, 300001, 2500000])
+def test_default_chunks(gfx, oracle_lib, n, nbins, mode):
+    import paper_2306_11686_amd as gf
+    from paper_2306_11686_amd import programs
+    keys = _keys("uniform", n)
+    bins = dev(np.zeros(nbins, dtype=np.uint32))
+    inst = gf.Instance.make({0: dev(keys), 1: bins}, scalars(), ip=(n,))
+    gfx.run(programs.histogram(nbins), inst,
+            mode=gf.GF_EXEC_PER_REGION if mode == "per_region" else gf.GF_EXEC_PERSISTENT)
+    gfx.sync()
+    assert np.array_equal(host(bins), oracle_lib.hist_u32(keys, nbins))
