@@ -33,7 +33,7 @@ constexpr int kSumThreads = 64;       // k_mlp_update: one wavefront per workgro
 constexpr int kSumLoads = 48;         // partial rows a thread has in flight
 constexpr int kLossParts = 32;        // partial sums of the loss, over 256 elements each per turn
 constexpr int kLossSpan = 256;
-constexpr int kLossTurns = 4;         // turns in flight (48 loads per lane)
+constexpr int kLossLoads = 48;        // loads in flight per thread
 
 // A kernel argument may be aligned to 4 bytes only.
 typedef float gf_f4u __attribute__((ext_vector_type(4), aligned(4)));
@@ -62,43 +62,54 @@ __device__ __forceinline__ void loss_final(const float *__restrict__ part, float
     *loss = acc * inv_norm;
 }
 
-// Partial sum `b` of sum m (y - t)^2, by one wavefront: 256 strands of
-// elements b * 256 + strand + i * 32 * 256, each lane four of them, halved
-// pairwise.
+// Partial sum `b` of sum m (y - t)^2, by T threads (one wavefront, or four): 256
+// strands of elements b * 256 + strand + i * 32 * 256, each thread 256 / T of
+// them, halved pairwise. The sum does not depend on T.
+template <int T>
 __device__ __forceinline__ void loss_part(const float *__restrict__ y, const float *__restrict__ tgt,
                                           const float *__restrict__ mask, int64_t count, int b,
                                           float *__restrict__ part)
 {
-    constexpr int Q = kLossSpan / kWave;
-    const int lane = threadIdx.x & (kWave - 1);
+    constexpr int Q = kLossSpan / T;             // strands of a thread
+    constexpr int R = kLossLoads / (3 * Q);      // turns in flight
+    const int tid = threadIdx.x;
     float acc[Q] = {};
-    for (int64_t base = (int64_t)b * kLossSpan; base < count; base += kLossTurns * kLossParts * kLossSpan) {
-        float yv[kLossTurns][Q], tv[kLossTurns][Q], mv[kLossTurns][Q];
+    for (int64_t base = (int64_t)b * kLossSpan; base < count; base += R * kLossParts * kLossSpan) {
+        float yv[R][Q], tv[R][Q], mv[R][Q];
 #pragma unroll
-        for (int r = 0; r < kLossTurns; ++r)
+        for (int r = 0; r < R; ++r)
 #pragma unroll
             for (int q = 0; q < Q; ++q) {
-                const int64_t i = base + r * kLossParts * kLossSpan + q * kWave + lane;
+                const int64_t i = base + r * kLossParts * kLossSpan + q * T + tid;
                 const int64_t at = i < count ? i : count - 1;
                 yv[r][q] = y[at];
                 tv[r][q] = tgt[at];
                 mv[r][q] = mask[at];
             }
 #pragma unroll
-        for (int r = 0; r < kLossTurns; ++r)
+        for (int r = 0; r < R; ++r)
 #pragma unroll
             for (int q = 0; q < Q; ++q) {
-                const int64_t i = base + r * kLossParts * kLossSpan + q * kWave + lane;
+                const int64_t i = base + r * kLossParts * kLossSpan + q * T + tid;
                 const float d = yv[r][q] - tv[r][q];
                 const float t = mv[r][q] * d * d;
                 acc[q] = i < count ? acc[q] + t : acc[q];
             }
     }
-    float s = (acc[0] + acc[2]) + (acc[1] + acc[3]);
+    float s;
+    if constexpr (T == kWave) {
+        s = (acc[0] + acc[2]) + (acc[1] + acc[3]);
+    } else {
+        __shared__ float s_acc[kLossSpan];
+        s_acc[tid] = acc[0];
+        __syncthreads();
+        const int l = tid & (kWave - 1);
+        s = (s_acc[l] + s_acc[l + 2 * kWave]) + (s_acc[l + kWave] + s_acc[l + 3 * kWave]);
+    }
 #pragma unroll
     for (int w = kWave / 2; w > 0; w >>= 1)
         s += __shfl_down(s, w, kWave);
-    if (lane == 0)
+    if (tid == 0)
         part[b] = s;
 }
 
@@ -356,7 +367,7 @@ __global__ void __launch_bounds__(kSumThreads) k_mlp_update(const float *__restr
 {
     constexpr int kSumBlocks = (kNParams + kSumThreads - 1) / kSumThreads;
     if (ADAM && blockIdx.x >= kSumBlocks) {
-        loss_part(y, tgt, mask, count, blockIdx.x - kSumBlocks, lpart);
+        loss_part<kWave>(y, tgt, mask, count, blockIdx.x - kSumBlocks, lpart);
         return;
     }
     const int i = blockIdx.x * kSumThreads + threadIdx.x;
@@ -379,13 +390,14 @@ __global__ void __launch_bounds__(kSumThreads) k_mlp_update(const float *__restr
         g[i] = acc;
 }
 
-// Masked MSE: per-wavefront partial sums of m (y - t)^2, summed in order by
-// one thread of the last launch (tiny sizes).
-__global__ void __launch_bounds__(kWave) k_mlp_loss_part(const float *__restrict__ y, const float *__restrict__ tgt,
+// Masked MSE: partial sums of m (y - t)^2, summed in order by one thread of the
+// last launch. Alone on the chip a part takes four wavefronts: with one,
+// 50,000 samples took 47 us, 18 with four.
+__global__ void __launch_bounds__(kLossSpan) k_mlp_loss_part(const float *__restrict__ y, const float *__restrict__ tgt,
                                                          const float *__restrict__ mask, int64_t count,
                                                          float *__restrict__ part)
 {
-    loss_part(y, tgt, mask, count, blockIdx.x, part);
+    loss_part<kLossSpan>(y, tgt, mask, count, blockIdx.x, part);
 }
 
 __global__ void k_mlp_loss_final(const float *__restrict__ part, float inv_norm, float *__restrict__ loss)
@@ -432,7 +444,7 @@ hipError_t launch_mlp_backward(const float *P, const float *feats, const float *
 hipError_t launch_mlp_loss(const float *y, const float *tgt, const float *mask, int64_t count, float inv_norm,
                            float *part, float *loss, hipStream_t s)
 {
-    hipLaunchKernelGGL(k_mlp_loss_part, dim3(kLossParts), dim3(kWave), 0, s, y, tgt, mask, count, part);
+    hipLaunchKernelGGL(k_mlp_loss_part, dim3(kLossParts), dim3(kLossSpan), 0, s, y, tgt, mask, count, part);
     hipLaunchKernelGGL(k_mlp_loss_final, dim3(1), dim3(kWave), 0, s, part, inv_norm, loss);
     return hipGetLastError();
 }

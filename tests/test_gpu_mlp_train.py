@@ -35,3 +35,27 @@ def test_training_equals_single_calls_bitwise(gfx, batch):
     torch.cuda.synchronize()
     for a, b in ((p, q), (m, mq), (v, vq), (hist, hq)):
         assert torch.isfinite(a).all() and torch.equal(a, b)
+
+
+@pytest.mark.parametrize("batch", [7, 8, 255, 4095, 4096, 4097, 50001])
+def test_loss_alone_and_in_training_bitwise(gfx, batch):
+    """The loss call sums with four wavefronts per part, training with one:
+    the same sum, at counts around a turn (8,192 elements) and a trip of
+    sixteen, and close to the sum in 64 bits (each of at most 300 terms in a
+    strand and 14 halvings and parts rounds once: 2^-24 * 320 of the sum)."""
+    import torch
+    rng = np.random.default_rng(batch)
+    new = lambda a: torch.from_numpy(np.asarray(a, np.float32)).cuda()
+    p, f, tgt = new(rng.standard_normal(NP) * 0.2), new(rng.standard_normal((batch, IN))), new(rng.random((batch, K)))
+    mask = new(rng.random((batch, K)) < 0.9)
+    inv = 1.0 / (batch * K)
+    y, loss = torch.zeros(batch, K, device="cuda"), torch.zeros(2, device="cuda")
+    gfx.mlp_forward(p, f, batch, y)
+    gfx.mlp_loss(y, tgt, mask, batch * K, inv, loss)
+    gfx.train_predictor(p, torch.zeros(NP, device="cuda"), torch.zeros(NP, device="cuda"), f, tgt, mask, batch, inv, 1,
+                        1e-3, loss[1:])
+    torch.cuda.synchronize()
+    assert loss[0] == loss[1]
+    d = y.double().cpu().numpy() - tgt.double().cpu().numpy()
+    ref = float((mask.double().cpu().numpy() * d * d).sum() * np.float64(np.float32(inv)))
+    assert abs(float(loss[0]) - ref) <= 2.0 ** -24 * 320 * ref
