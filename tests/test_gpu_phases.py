@@ -125,3 +125,18 @@ def test_phases_argument_errors(gfx):
         with pytest.raises(gf.GfError):
             gfx.run(gf.Program.make([st], [], 0), inst)
     gfx.sync()
+
+
+@pytest.mark.parametrize("mode", ["persistent", "per_region"])
+@pytest.mark.parametrize("n", [1, 2, 63, 64, 65, 191, 192, 193, 256, 1535, 1536, 1537, 1601, 3100])
+def test_ranges_of_about_one_and_eight_elements_per_thread(gfx, oracle_lib, n, mode):
+    """Three workgroups of 64 threads: ranges that are empty, below, at and
+    past one element per thread, and around the eight that are requested
+    together, the shifted operand wrapping in and between the ranges."""
+    import paper_2306_11686_amd as gf
+    a0 = gi.um11(9, 21, np.arange(n, dtype=np.uint64))
+    for shift in sorted({0, 1 % n, n // 2, n - 1}):
+        ga, gb, own, st = _run_phases(gfx, gf, a0, 4, shift, _mode(gf, mode), gf.Launch.make(wg_size=64, num_wg=3))
+        ra, rb = oracle_lib.phases(a0, 4, shift)
+        assert np.array_equal(ga, ra) and np.array_equal(gb, rb), shift
+        assert np.array_equal(own, oracle_lib.static_owner(n, st["num_wg"] * 64))
