@@ -260,7 +260,7 @@ typedef struct {
     int32_t rpc_posted;    /* filled by gf_sync: RPC requests serviced so far */
     int32_t candidate;     /* gf_region_run with launch NULL: the launch shape the
                               installed predictor or its autotuner fallback chose
-                              (0..31), -1 if none */
+                              (0..31), -1 if none or the library's own choice */
     int32_t launch_source; /* where the launch shape came from: GF_LAUNCH_* */
 } gf_run_stats;
 
@@ -302,11 +302,14 @@ const char *gf_last_error(const gf_ctx *ctx);
  * workgroups with group barriers (GF_EXEC_PERSISTENT), or as per-instance
  * launches (per-region modes). launch may be NULL: with an installed
  * predictor the predicted launch shape is used (gf_predict_launch; for SpMV
- * programs that call waits for hip_stream); when the predictor defers (the
+ * programs that call waits for hip_stream), but for a persistent run that
+ * takes several sweeps per pass, whose shape is the library's own (no
+ * predicted shape does, and all are slower); when the predictor defers (the
  * program lies outside its training distribution, e.g. several instances)
  * the autotuner decides: every candidate shape is timed on copies of the
  * instances' arrays and scalars (allocated for the call and freed; the
- * program's printf and host-call steps left out), the fastest is used and
+ * program's printf and host-call steps left out), and so is the library's own
+ * choice where it takes several sweeps per pass; the fastest is used and
  * cached in the ctx for this program, sizes and mode (opts.tune_fallback).
  * Without a predictor, or with the fallback off, the defaults are used.
  * stats (nullable) receives counts. Asynchronous: results are valid after
@@ -516,7 +519,8 @@ int32_t gf_tune_pick(const float *ms, int32_t n);
  * 0: its number of work items). wg_size, items, xcd_remap and prefetch are
  * taken from launches[0]; the grid is the co-resident capacity. In the
  * persistent mode the instances are packed onto the eight XCDs and each
- * instance's workgroups stay on one XCD (see DESIGN of the batched launch);
+ * instance's workgroups stay on one XCD. Without rows or weights in any launch
+ * it is gf_region_run with launches[0];
  * the per-region modes launch each instance with its own rows per tile.
  * Same conventions as gf_region_run otherwise. */
 gf_status gf_region_run_batched(gf_ctx *ctx, const gf_program *prog, const gf_instance *inst,

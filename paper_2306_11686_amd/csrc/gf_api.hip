@@ -1742,6 +1742,8 @@ bool fusable_instance(const DProg &p, int rs, const gf_instance &in)
 {
     const DStep &r = p.steps[rs];
     const uint64_t n = (uint64_t)in.ip[r.np];
+    if (n > 1 << 20)
+        return false;  // refused
     const uint64_t bytes = (r.kind == GF_R_JACOBI3D ? n * n * n : n * n) * 8;
     // slots as the prologue's swaps leave them
     void *arr[GF_MAX_ARRAYS];
@@ -1783,6 +1785,41 @@ int64_t fused_barriers(const DProg &p, int rs, int64_t n)
     if (p.steps[rs].kind == GF_R_JACOBI3D)
         ++passes;
     return p.steps[rs].red_op == GF_OP_NONE ? passes - 1 : passes;
+}
+
+// The region of a persistent run that takes several sweeps per pass, its step
+// index or -1: the tile is left to the library (a given one is run as given, a
+// sweep per pass), the program and every instance allow it, and the fused
+// kernel holds the workgroups, the instances and the scratch their partials.
+// What it does not hold runs plainly. *cap: its co-resident workgroups; *zlen:
+// planes per segment of a single 3D run.
+int fused_run(gf_ctx *ctx, const DProg &p, const gf_instance *inst, int n_inst, const gf_launch *l, int *cap,
+              int32_t *zlen)
+{
+    if (l && (l->wg_size || l->tile_y || l->tile_z || l->items || l->prefetch))
+        return -1;
+    const int rs = fusable_region(p);
+    for (int i = 0; i < n_inst; ++i)
+        if (rs < 0 || !fusable_instance(p, rs, inst[i]))
+            return -1;
+    const DStep &st = p.steps[rs];
+    Tiling t;
+    std::memset(&t, 0, sizeof t);
+    t.wg_size = fused_wg(st.kind);
+    t.tile_y = t.prefetch = 1;
+    *cap = std::min(4096, persistent_capacity(p, t, ctx->num_cu, true));
+    const int num_wg = l ? l->num_wg : 0;
+    if (*cap <= 0 || n_inst > *cap || (n_inst == 1 && num_wg > *cap))
+        return -1;
+    int64_t part = 0;
+    if (n_inst == 1) {
+        *zlen = fused_zlen(inst[0].ip[st.np], num_wg > 0 ? num_wg : *cap);
+        part = fused_partials(st.kind, inst[0].ip[st.np], *zlen);
+    } else {
+        for (int i = 0; i < n_inst; ++i)
+            part += fused_batch_partials(st.kind, inst[i].ip[st.np]);
+    }
+    return part <= ctx->scr.partials_cap ? rs : -1;
 }
 
 // Workgroups for the instances `ids` out of `budget` (each >= 1 and at most
@@ -2189,7 +2226,13 @@ static gf_status region_run(gf_ctx *ctx, const gf_program *prog, const gf_instan
         int32_t k = predict_launch(ctx, p, inst, n_inst, mode, stream, &predicted);
         if (k < -1)
             return (gf_status)k;
-        if (k >= 0) {
+        int fcap;
+        int32_t fz;
+        if (k >= 0 && mode == GF_EXEC_PERSISTENT && fused_run(ctx, p, inst, n_inst, nullptr, &fcap, &fz) >= 0) {
+            // the shapes the predictor knows take one sweep per pass: all 32 of
+            // them took longer than the library's own, by 1.07 (2D side 8, four
+            // sweeps) to 3.2 times (3D side 200, 30 sweeps)
+        } else if (k >= 0) {
             note.cand = k;
             note.source = GF_LAUNCH_PREDICTED;
             launch = &predicted;
@@ -2216,7 +2259,7 @@ static gf_status region_run(gf_ctx *ctx, const gf_program *prog, const gf_instan
                 return region_run(ctx, prog, inst, n_inst, mode, &common, stats, hip_stream, sh.data());
             }
             if (k >= 0) {
-                note.cand = k;
+                note.cand = k < GF_NUM_CANDIDATES ? k : -1;
                 note.source = cached ? GF_LAUNCH_TUNED_CACHED : GF_LAUNCH_TUNED;
                 launch = &predicted;
             }
@@ -2270,38 +2313,10 @@ static gf_status region_run(gf_ctx *ctx, const gf_program *prog, const gf_instan
                 return fail(ctx, GF_EINVAL, "%d instances need at least %d co-resident workgroups, capacity %d",
                             n_inst, n_inst, limit);
         }
-        // Several sweeps per pass where the caller leaves the tile to the
-        // library; a given tile is run as given, one sweep per pass. A grid
-        // size the plain kernel can hold and the fused one cannot, and a
-        // batch with more instances than its capacity, run plainly too.
-        int fused_rs = -1, fcap = 0;
+        // several sweeps per pass where the caller leaves the tile to the library
+        int fcap = 0;
         int32_t fused_z = 0;  // 3D: planes per segment
-        if (!shape && (!launch || (!launch->wg_size && !launch->tile_y && !launch->tile_z && !launch->items &&
-                                   !launch->prefetch)))
-            fused_rs = fusable_region(p);
-        for (int i = 0; i < n_inst && fused_rs >= 0; ++i)
-            if (!fusable_instance(p, fused_rs, inst[i]))
-                fused_rs = -1;
-        if (fused_rs >= 0) {
-            Tiling ft = t;
-            ft.wg_size = fused_wg(p.steps[fused_rs].kind);
-            fcap = std::min(4096, persistent_capacity(p, ft, ctx->num_cu, true));
-            if (fcap <= 0 || n_inst > fcap || (launch && launch->num_wg > fcap && n_inst == 1))
-                fused_rs = -1;
-        }
-        if (n_inst > 1 && fused_rs >= 0) {
-            int64_t part = 0;
-            for (int i = 0; i < n_inst; ++i)
-                part += fused_batch_partials(p.steps[fused_rs].kind, inst[i].ip[p.steps[fused_rs].np]);
-            if (part > ctx->scr.partials_cap)
-                fused_rs = -1;
-        }
-        if (n_inst == 1 && fused_rs >= 0) {
-            const int64_t n = inst[0].ip[p.steps[fused_rs].np];
-            fused_z = fused_zlen(n, launch && launch->num_wg > 0 ? launch->num_wg : fcap);
-            if (fused_partials(p.steps[fused_rs].kind, n, fused_z) > ctx->scr.partials_cap)
-                fused_rs = -1;
-        }
+        const int fused_rs = shape ? -1 : fused_run(ctx, p, inst, n_inst, launch, &fcap, &fused_z);
         if (fused_rs >= 0) {
             t.wg_size = fused_wg(p.steps[fused_rs].kind);
             t.tile_z = fused_z;  // a batched 3D run (0): chosen by each group
@@ -2806,7 +2821,9 @@ std::string fallback_key(const DProg &p, const gf_instance *inst, int n_inst, in
 // read), with the program's host calls and printfs left out (they do not
 // depend on the launch shape and must not run more than once), pick the
 // fastest and remember it for this program, sizes and mode. Per-region
-// graph runs are tuned as per-region launches. Returns the candidate index,
+// graph runs are tuned as per-region launches. Where the library's own choice
+// takes several sweeps per pass, which no candidate does, it is timed with them.
+// Returns the candidate index, GF_NUM_CANDIDATES for the library's own choice,
 // -1 if none could run, or a negative gf_status below -1 on failure.
 int32_t tune_fallback(gf_ctx *ctx, const gf_program *prog, const DProg &p, const gf_instance *inst, int n_inst,
                       int mode, hipStream_t s, gf_launch *out, bool *cached, std::vector<gf_launch> *per)
@@ -2859,13 +2876,26 @@ int32_t tune_fallback(gf_ctx *ctx, const gf_program *prog, const DProg &p, const
             st = hipfail(ctx, e, "autotuner fallback: copying the instance");
     }
     int32_t best = -1;
+    gf_launch own;
+    std::memset(&own, 0, sizeof own);
+    own.xcd_remap = 1;
+    int fcap;
+    int32_t fz;
+    const bool fused =
+        st == GF_OK && mode == GF_EXEC_PERSISTENT && fused_run(ctx, p, inst, n_inst, nullptr, &fcap, &fz) >= 0;
     if (st == GF_OK && n_inst > 1 && mode == GF_EXEC_PERSISTENT) {
         // batched persistent run: a shape per instance (gf_tune_batched)
         std::vector<gf_launch> outs(n_inst);
-        float ms = 0.0f;
-        const int32_t ran = gf_tune_batched(ctx, &tp, tinst.data(), n_inst, 3, outs.data(), &ms, s);
+        float ms = 0.0f, own_ms = INFINITY;
+        int32_t ran = gf_tune_batched(ctx, &tp, tinst.data(), n_inst, 3, outs.data(), &ms, s);
+        if (ran >= 0 && fused)
+            ran = std::min(ran, gf_tune(ctx, &tp, tinst.data(), n_inst, mode, &own, 1, 3, &own_ms, nullptr, s));
         if (ran < 0) {
             st = (gf_status)ran;
+        } else if (own_ms <= ms) {
+            *out = own;
+            best = GF_NUM_CANDIDATES;
+            ctx->tuned[key] = {own, best, {}};
         } else {
             *out = outs[0];
             *per = outs;
@@ -2873,9 +2903,11 @@ int32_t tune_fallback(gf_ctx *ctx, const gf_program *prog, const DProg &p, const
             ctx->tuned[key] = {outs[0], -1, outs};
         }
     } else if (st == GF_OK) {
-        gf_launch cand[GF_NUM_CANDIDATES];
-        float ms[GF_NUM_CANDIDATES];
-        const int32_t nc = gf_tune_candidates(ctx, &tp, tinst.data(), cand);
+        gf_launch cand[GF_NUM_CANDIDATES + 1];
+        float ms[GF_NUM_CANDIDATES + 1];
+        int32_t nc = gf_tune_candidates(ctx, &tp, tinst.data(), cand);
+        if (nc >= 0 && fused)
+            cand[nc++] = own;
         const int tmode = mode == GF_EXEC_PER_REGION_GRAPH ? GF_EXEC_PER_REGION : mode;
         if (nc < 0) {
             st = (gf_status)nc;
@@ -2977,11 +3009,13 @@ gf_status gf_region_run_batched(gf_ctx *ctx, const gf_program *prog, const gf_in
     if (mode == GF_EXEC_KERNEL_SPLIT)
         return fail(ctx, GF_EUNSUPPORTED, "the kernel split runs one instance");
     std::vector<InstShape> sh(n_inst);
+    bool named = false;
     for (int i = 0; i < n_inst; ++i) {
         if (launches[i].tile_y < 0 || launches[i].num_wg < 0)
             return fail(ctx, GF_EINVAL, "instance %d: negative rows per tile or weight", i);
         sh[i].tile_y = launches[i].tile_y;
         sh[i].weight = (double)launches[i].num_wg;
+        named = named || launches[i].tile_y > 0 || launches[i].num_wg > 0;
     }
     gf_launch common = launches[0];
     common.num_wg = 0;
@@ -2991,7 +3025,8 @@ gf_status gf_region_run_batched(gf_ctx *ctx, const gf_program *prog, const gf_in
     gf_status st = order_before(ctx, s);
     if (st != GF_OK)
         return st;
-    st = region_run(ctx, prog, inst, n_inst, mode, &common, stats, hip_stream, sh.data());
+    // no rows and no weights: nothing of the instances' own
+    st = region_run(ctx, prog, inst, n_inst, mode, &common, stats, hip_stream, named ? sh.data() : nullptr);
     if (st == GF_OK)
         mark_after(ctx, s);
     return st;

@@ -47,11 +47,14 @@ def lookup(key: str, path: str = DEFAULT_DB):
 
 def tune(ctx, program, instances, key: str | None = None, mode: int = GF_EXEC_PERSISTENT, reps: int = 3,
          candidates=None, path: str = DEFAULT_DB):
-    """Time the candidates on real runs, record the best under `key`.
+    """Time the candidates on real runs, record the best under `key`. Without
+    candidates of the caller's they are the library's 32 and the launch that
+    leaves every choice to the library (its own tiles, and several sweeps per
+    pass, are no candidate's).
 
     Returns (best Launch, list of (Launch, ms))."""
     cands = candidates if candidates is not None else ctx.tune_candidates(program, instances if not isinstance(
-        instances, (list, tuple)) else instances[0])
+        instances, (list, tuple)) else instances[0]) + [Launch.make()]
     ms, best = ctx.tune(program, instances, mode=mode, candidates=cands, reps=reps)
     if best < 0:
         raise RuntimeError("no candidate launch could run")
@@ -81,14 +84,22 @@ def lookup_batched(key: str, path: str = DEFAULT_DB):
 
 
 def tune_batched(ctx, program, instances, key: str | None = None, reps: int = 3, path: str = DEFAULT_DB):
-    """The library's batched autotuner (gf_tune_batched): a shape per instance;
-    records (rows per tile, relative share) per instance under `key`.
-    Returns (launches, median ms of the chosen plan)."""
+    """The library's batched autotuner (gf_tune_batched), a shape per instance,
+    against the launch that leaves every choice to the library; records the
+    faster under `key`: (rows per tile, relative share) per instance, or that
+    launch. Returns (launches, median ms of the chosen plan)."""
     launches, ms = ctx.tune_batched(program, instances, reps=reps)
+    own_ms, _ = ctx.tune(program, instances, mode=GF_EXEC_PERSISTENT, candidates=[Launch.make()], reps=reps)
+    own = own_ms[0] <= ms
+    if own:
+        launches, ms = [Launch.make() for _ in instances], own_ms[0]
     if key is not None:
         db = load_db(path)
-        db[key] = {"wg_size": int(launches[0].wg_size), "xcd_remap": int(launches[0].xcd_remap),
-                   "per_instance": [[int(l.tile_y), int(l.num_wg)] for l in launches],
-                   "ms": round(ms, 4), "mode": int(GF_EXEC_PERSISTENT)}
+        if own:
+            db[key] = launch_to_dict(launches[0])
+        else:
+            db[key] = {"wg_size": int(launches[0].wg_size), "xcd_remap": int(launches[0].xcd_remap),
+                       "per_instance": [[int(l.tile_y), int(l.num_wg)] for l in launches]}
+        db[key].update({"ms": round(ms, 4), "mode": int(GF_EXEC_PERSISTENT)})
         save_db(db, path)
     return launches, ms

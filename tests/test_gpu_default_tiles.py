@@ -75,7 +75,7 @@ def test_prefetch_names_the_fixed_tile(gfx, oracle_lib, mode):
             run_jacobi2d(gfx, gi.grid2d(n, seed=3), 2, m, launch=l)
 
 
-def test_reduction_capacity_does_not_follow_the_grid_side(gfx):
+def test_reduction_capacity_does_not_follow_the_grid_side():
     """The largest 2D grids have more reduction tiles of the fixed 16 rows
     than the scratch holds, and are refused also where the default tile has
     32 rows; a side below the limit is accepted."""
@@ -90,12 +90,14 @@ def test_reduction_capacity_does_not_follow_the_grid_side(gfx):
     w = torch.empty(n * n, dtype=torch.float64, device="cuda")
     r = torch.zeros(1, dtype=torch.float64, device="cuda")
     inst = gf.Instance.make({0: u, 1: w, 2: r}, scalars(), ip=(n,))
+    ctx = gf.Context(0)                         # without a predictor
     for mode in (gf.GF_EXEC_PER_REGION, gf.GF_EXEC_PERSISTENT):
         with pytest.raises(gf.GfError):
-            gfx.run(programs.jacobi2d(1), inst, mode=mode)
+            ctx.run(programs.jacobi2d(1), inst, mode=mode)
     ok = gf.Instance.make({0: u, 1: w, 2: r}, scalars(), ip=(92000,))   # 180 * 5750 < 2^20
-    gfx.run(programs.jacobi2d(1), ok, mode=gf.GF_EXEC_PER_REGION)
-    gfx.sync()
+    ctx.run(programs.jacobi2d(1), ok, mode=gf.GF_EXEC_PER_REGION)
+    ctx.sync()
+    ctx.close()
     del u, w, inst, ok
     torch.cuda.empty_cache()
 
@@ -141,7 +143,7 @@ def test_default_tiles_2d(gfx, oracle_lib, n, num_wg, mode):
     assert np.array_equal(g, g_ref) and np.all(np.abs(r - r_comp) <= 1e-12 * r_comp)
 
 
-def test_instances_of_a_per_region_run_follow_their_own_side(gfx):
+def test_instances_of_a_per_region_run_follow_their_own_side():
     """A small grid beside a large one runs the launch it gets alone: the
     workgroups of the largest launch are those of its own tile."""
     import paper_2306_11686_amd as gf
@@ -155,8 +157,9 @@ def test_instances_of_a_per_region_run_follow_their_own_side(gfx):
 
     a, b = inst(64), inst(300)
     prog = programs.jacobi3d(1)
-    for mode in (gf.GF_EXEC_PER_REGION, gf.GF_EXEC_PER_REGION_GRAPH):
-        alone = [gfx.run(prog, i, mode=mode)["num_wg"] for i in (a, b)]
-        assert gfx.run(prog, [a, b], mode=mode)["num_wg"] == max(alone)
-        assert gfx.run(prog, [a, a], mode=mode)["num_wg"] == alone[0]
-    gfx.sync()
+    with gf.Context(0) as ctx:                  # without a predictor
+        for mode in (gf.GF_EXEC_PER_REGION, gf.GF_EXEC_PER_REGION_GRAPH):
+            alone = [ctx.run(prog, i, mode=mode)["num_wg"] for i in (a, b)]
+            assert ctx.run(prog, [a, b], mode=mode)["num_wg"] == max(alone)
+            assert ctx.run(prog, [a, a], mode=mode)["num_wg"] == alone[0]
+        ctx.sync()

@@ -246,3 +246,73 @@ def test_predict_launch_skips_candidates_that_cannot_run():
         assert k == 3 + 16
     finally:
         ctx.close()
+
+
+def _run_fused(ctx, gf, oracle_lib, kind, sides, sweeps, run):
+    """`run` on fresh instances; the stats, every grid checked."""
+    import torch
+    from paper_2306_11686_amd import programs
+    from tests.gpu_helpers import host
+    grid = gi.grid2d if kind == 2 else gi.grid3d
+    prog = programs.jacobi2d(sweeps) if kind == 2 else programs.jacobi3d(sweeps)
+    us = [dev(grid(n, seed=n)) for n in sides]
+    insts = [gf.Instance.make({0: u, 1: u.clone(), 2: torch.zeros(sweeps, dtype=torch.float64, device="cuda")},
+                              scalars(), ip=(n,)) for u, n in zip(us, sides)]
+    st = run(prog, insts)
+    ctx.sync()
+    assert sweeps % 2 == 0
+    for u, n in zip(us, sides):
+        ref = (oracle_lib.jacobi2d if kind == 2 else oracle_lib.jacobi3d)(grid(n, seed=n), sweeps)[0]
+        assert np.array_equal(host(u), ref)
+    return st
+
+
+@pytest.mark.parametrize("kind,sides", [(3, [66]), (2, [200]), (2, [40, 70, 33, 100])])
+def test_predictor_and_fallback_leave_several_sweeps_per_pass_to_the_library(oracle_lib, kind, sides):
+    """A persistent run that the library takes several sweeps per pass for
+    keeps doing so with a predictor installed: predicted shapes take one, and
+    the autotuner times the library's own beside them (2.5 times as fast as
+    the best of them at these sizes). Launches per region are predicted."""
+    import paper_2306_11686_amd as gf
+    sweeps, wg = 30, 128 if kind == 2 else 512
+    with gf.Context(0) as ctx:
+        run = lambda p, i: ctx.run(p, i, mode=gf.GF_EXEC_PERSISTENT)
+        _constant_predictor(ctx, 5)
+        st = _run_fused(ctx, gf, oracle_lib, kind, sides, sweeps, run)
+        assert (st["candidate"], st["launch_source"], st["wg_size"]) == (-1, gf.GF_LAUNCH_GIVEN, wg)
+        st = _run_fused(ctx, gf, oracle_lib, kind, sides, sweeps, lambda p, i: ctx.run(p, i, mode=gf.GF_EXEC_PER_REGION))
+        assert (st["candidate"], st["launch_source"]) == (5, gf.GF_LAUNCH_PREDICTED)
+        _constant_predictor(ctx, 5, std=1e-3)         # out of distribution: the autotuner decides
+        for want in (gf.GF_LAUNCH_TUNED, gf.GF_LAUNCH_TUNED_CACHED):
+            st = _run_fused(ctx, gf, oracle_lib, kind, sides, sweeps, run)
+            assert (st["candidate"], st["launch_source"], st["wg_size"]) == (-1, want, wg)
+
+
+def test_database_tuning_times_the_librarys_own_choice(gfx, oracle_lib, tmp_path):
+    """tuner.tune and tuner.tune_batched record the launch that leaves every
+    choice to the library where it is the fastest, and what they record runs
+    as that launch does, through gf_region_run_batched too."""
+    import paper_2306_11686_amd as gf
+    from paper_2306_11686_amd import tuner
+    path = str(tmp_path / "db.json")
+
+    def tune(prog, insts):
+        best, table = tuner.tune(gfx, prog, insts, key="one", reps=2, path=path)
+        assert len(table) == gf.GF_NUM_CANDIDATES + 1 and tuner.launch_to_dict(best) == \
+            tuner.launch_to_dict(gf.Launch.make())
+        assert tuner.launch_to_dict(tuner.lookup("one", path)) == tuner.launch_to_dict(gf.Launch.make())
+        launches, ms = tuner.tune_batched(gfx, prog, insts, key="two", reps=2, path=path)
+        assert ms > 0 and tuner.lookup_batched("two", path) is None
+        assert tuner.launch_to_dict(tuner.lookup("two", path)) == tuner.launch_to_dict(gf.Launch.make())
+        return gfx.run_batched(prog, insts, launches[:1])
+
+    import torch
+    from paper_2306_11686_amd import programs
+    u = dev(gi.grid2d(300, seed=2))
+    inst = gf.Instance.make({0: u, 1: u.clone(), 2: torch.zeros(40, dtype=torch.float64, device="cuda")}, scalars(),
+                            ip=(300,))
+    tune(programs.jacobi2d(40), [inst])
+    for n in (33, 128):
+        st = _run_fused(gfx, gf, oracle_lib, 2, [n, 20], 8,
+                        lambda p, i: gfx.run_batched(p, i, [gf.Launch.make() for _ in i]))
+        assert st["wg_size"] == 128
