@@ -1600,6 +1600,9 @@ struct SerialWave {
                     if ((iter + 1) % st.every == 0) {
                         if (lane < GF_MAX_SCALARS)
                             s_scal[lane] = scal;
+                        // lane 0 reads what the others wrote
+                        __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+                        __builtin_amdgcn_wave_barrier();
                         if (lane == 0)
                             serial_printf(rpc, st.fmt_id, st.nargs, st.flags, st.sc, iter, s_scal, err);
                     }
