@@ -2351,11 +2351,8 @@ static gf_status region_run(gf_ctx *ctx, const gf_program *prog, const gf_instan
             // one workgroup more for the serial steps, without work items
             if (fused_rs >= 0 && grid < fcap)
                 ++grid;
-            if (launch && launch->num_wg > 0) {
-                if (launch->num_wg > cap)
-                    return fail(ctx, GF_EINVAL, "num_wg %d exceeds the co-resident capacity %d", launch->num_wg, cap);
+            if (launch && launch->num_wg > 0)
                 grid = launch->num_wg;
-            }
             if (program_is_hist_family(p)) {
                 uint32_t mask = 0;
                 for (int k = 0; k < p.n_steps; ++k)

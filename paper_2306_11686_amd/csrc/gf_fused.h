@@ -44,21 +44,6 @@ __device__ __forceinline__ GF_GLOBAL V *row_at(GF_GLOBAL T *p, uint32_t byte)
     return (GF_GLOBAL V *)((GF_GLOBAL const char *)p + byte);
 }
 
-// The neighbouring lanes' values; the wavefront's end lanes get 0 (their
-// results are never used).
-__device__ __forceinline__ double lane_left(double v)
-{
-    const int lo = __builtin_amdgcn_mov_dpp(__double2loint(v), 0x138, 0xf, 0xf, true);
-    const int hi = __builtin_amdgcn_mov_dpp(__double2hiint(v), 0x138, 0xf, 0xf, true);
-    return __hiloint2double(hi, lo);
-}
-__device__ __forceinline__ double lane_right(double v)
-{
-    const int lo = __builtin_amdgcn_mov_dpp(__double2loint(v), 0x130, 0xf, 0xf, true);
-    const int hi = __builtin_amdgcn_mov_dpp(__double2hiint(v), 0x130, 0xf, 0xf, true);
-    return __hiloint2double(hi, lo);
-}
-
 // Values of a pass's reductions over one work item or all of them.
 template <int OP, int M>
 __device__ __forceinline__ void wave_reduce_m(double (&v)[M])
@@ -236,8 +221,8 @@ __device__ __forceinline__ void j2f_tile(GF_GLOBAL const double *__restrict__ u,
             if (r == 0 || r == n - 1) {
                 out = s == 1 ? eb : prev;
             } else {
-                const double xl = lane_left(c.y);
-                const double xr = lane_right(c.x);
+                const double xl = wave_shr1(c.y);
+                const double xr = wave_shl1(c.x);
                 out.x = ((xl + c.y) + (up.x + dn.x)) * 0.25;
                 out.y = ((c.x + xr) + (up.y + dn.y)) * 0.25;
                 if constexpr (XE) {
@@ -512,8 +497,8 @@ __device__ __forceinline__ void j3f_tile(GF_GLOBAL const double *__restrict__ u,
                 const gf_d2 up = j > 0 ? q[s - 1][kc1][j > 0 ? j - 1 : 0] : nu[s - 1];
                 const gf_d2 dn = j + 1 < TY ? q[s - 1][kc1][j + 1 < TY ? j + 1 : 0] : nd[s - 1];
                 const gf_d2 zm = q[s - 1][km][j], zp = q[s - 1][k][j];
-                const double xl = lane_left(c.y);
-                const double xr = lane_right(c.x);
+                const double xl = wave_shr1(c.y);
+                const double xr = wave_shl1(c.x);
                 gf_d2 out;
                 out.x = (((xl + c.y) + (up.x + dn.x)) + (zm.x + zp.x)) * c6;
                 out.y = (((c.x + xr) + (up.y + dn.y)) + (zm.y + zp.y)) * c6;

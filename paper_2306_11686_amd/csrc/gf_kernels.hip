@@ -138,17 +138,17 @@ __device__ inline int64_t region_items_dev(const DStep &st, int64_t n, const Til
 
 // Lane shifts across the whole wavefront (DPP wave_shr:1 / wave_shl:1):
 // lane i receives lane i-1's (shr) or lane i+1's (shl) value; the lane at
-// the wavefront edge receives 0 and is fixed up by the caller.
+// the wavefront edge receives 0 and is fixed up by the caller (or not used).
 __device__ __forceinline__ double wave_shr1(double v)
 {
-    const int lo = __builtin_amdgcn_update_dpp(0, __double2loint(v), 0x138, 0xf, 0xf, false);
-    const int hi = __builtin_amdgcn_update_dpp(0, __double2hiint(v), 0x138, 0xf, 0xf, false);
+    const int lo = __builtin_amdgcn_mov_dpp(__double2loint(v), 0x138, 0xf, 0xf, true);
+    const int hi = __builtin_amdgcn_mov_dpp(__double2hiint(v), 0x138, 0xf, 0xf, true);
     return __hiloint2double(hi, lo);
 }
 __device__ __forceinline__ double wave_shl1(double v)
 {
-    const int lo = __builtin_amdgcn_update_dpp(0, __double2loint(v), 0x130, 0xf, 0xf, false);
-    const int hi = __builtin_amdgcn_update_dpp(0, __double2hiint(v), 0x130, 0xf, 0xf, false);
+    const int lo = __builtin_amdgcn_mov_dpp(__double2loint(v), 0x130, 0xf, 0xf, true);
+    const int hi = __builtin_amdgcn_mov_dpp(__double2hiint(v), 0x130, 0xf, 0xf, true);
     return __hiloint2double(hi, lo);
 }
 
@@ -2700,11 +2700,7 @@ int64_t reduce_grid(int64_t n, int num_cu, int64_t max_wg)
     int64_t gmax = (int64_t)num_cu * 4;
     if (gmax > max_wg)
         gmax = max_wg;
-    if (g > gmax)
-        g = gmax;
-    if (g < 1)
-        g = 1;
-    return g;
+    return g > gmax ? gmax : g;
 }
 
 hipError_t launch_reduce(int op, int dt, const void *in, int64_t n, void *out, const Scratch &scr, int num_cu,
