@@ -1099,7 +1099,6 @@ __device__ __forceinline__ void owner_region(int32_t *owner, int64_t n, int64_t 
 // used. 2^22 doubles over 256 workgroups take 19 us per phase against 82 us
 // with strided blocks. t0 is the workgroup's first thread id.
 constexpr int kPhaseUnroll = 8;
-constexpr int kPhaseShort = 4;
 
 // dst[i] = src[i] + nb[i] over [lo, hi) (uniform bounds) by the whole
 // workgroup. Uniform bases and one 32-bit lane offset: with per-lane 64-bit
@@ -1127,7 +1126,7 @@ __device__ __forceinline__ void phase_piece(GF_GLOBAL const double *src, GF_GLOB
             (dst + i)[t] = (src + i)[t] + (nb + i)[t];
 }
 
-template <typename Bar>
+template <bool SHORT, typename Bar>
 __device__ bool phases_region(GF_GLOBAL double *a, GF_GLOBAL double *b, GF_GLOBAL int32_t *owner, int64_t n,
                               int64_t P, int64_t shift, int64_t t0, int64_t T, Bar bar)
 {
@@ -1150,28 +1149,17 @@ __device__ bool phases_region(GF_GLOBAL double *a, GF_GLOBAL double *b, GF_GLOBA
     for (int64_t p = 0; p < P; ++p) {
         if (p > 0 && !bar())
             return false;
-        // the second operand wraps at i = n - shift: two uniform pieces; a
-        // range of up to four elements per thread in one, all requested at once
-        // (100 and 1,000 doubles in one workgroup, us per phase: 1.15 and 1.65
-        // in two pieces, 0.81 and 1.21 so)
+        // the second operand wraps at i = n - shift: two uniform pieces.
+        // SHORT: a range of one element per thread in one (the persistent kernel,
+        // 100 doubles in one workgroup, us per phase: 1.15 in two pieces, 0.81
+        // so; with ranges of up to four elements per thread 1,000 went from 1.65
+        // to 1.21, but 2^22 took 1.5 % longer; k_phases, whose ranges of 10^5
+        // doubles seldom hold the wrap, 8.9 in pieces, 10.2 so)
         const int64_t wrap = n - shift;
-        if (hi - lo <= B) {
+        if (SHORT && hi - lo <= B) {
             const int64_t i = lo + threadIdx.x;
             if (i < hi)
                 dst[i] = src[i] + src[i < wrap ? i + shift : i - wrap];
-        } else if (hi - lo <= kPhaseShort * B) {
-            double x[kPhaseShort], y[kPhaseShort];
-#pragma unroll
-            for (int j = 0; j < kPhaseShort; ++j) {
-                const int64_t e = lo + j * B + threadIdx.x;
-                const int64_t i = e < hi ? e : hi - 1;
-                x[j] = src[i];
-                y[j] = src[i < wrap ? i + shift : i - wrap];
-            }
-#pragma unroll
-            for (int j = 0; j < kPhaseShort; ++j)
-                if (lo + j * B + threadIdx.x < hi)
-                    dst[lo + j * B + threadIdx.x] = x[j] + y[j];
         } else {
 #pragma unroll 1
             for (int w = 0; w < 2; ++w)
@@ -1872,7 +1860,7 @@ __global__ void __launch_bounds__(family_max_threads<KMASK>())
                 owner_region((int32_t *)op[0], n, st.chunk, G * blockDim.x, member * blockDim.x + threadIdx.x);
             } else if (st.kind == GF_R_PHASES) {
                 if constexpr ((KMASK >> GF_R_PHASES) & 1u) {
-                    if (!phases_region(gptr((double *)op[0]), gptr((double *)op[1]), gptr((int32_t *)op[2]), n,
+                    if (!phases_region<true>(gptr((double *)op[0]), gptr((double *)op[1]), gptr((int32_t *)op[2]), n,
                                        st.chunk, (int64_t)st.mask, member * blockDim.x, G * blockDim.x, barrier))
                         return;
                 }
@@ -2237,8 +2225,7 @@ __global__ void __launch_bounds__(kMaxWg) k_hist_merge(RegionLaunch rl, int64_t 
 // co-resident wave of workgroups. The last workgroup runs the glue.
 // ---------------------------------------------------------------------------
 
-// Seven waves per SIMD: the grid may be up to the resident workgroups.
-__global__ void __launch_bounds__(kMaxWg) __attribute__((amdgpu_waves_per_eu(7, 7))) k_phases(RegionLaunch rl, Scratch scr, RpcRing rpc)
+__global__ void __launch_bounds__(kMaxWg) k_phases(RegionLaunch rl, Scratch scr, RpcRing rpc)
 {
     __shared__ BarrierState s_bar;
     __shared__ int s_last;
@@ -2258,7 +2245,7 @@ __global__ void __launch_bounds__(kMaxWg) __attribute__((amdgpu_waves_per_eu(7, 
         }
         return tree_barrier(genw, tree, blockIdx.x, (uint32_t)G, &s_bar, scr.error, scr.barrier_timeout_ticks);
     };
-    if (!phases_region(gptr((double *)rl.arr[0]), gptr((double *)rl.arr[1]), gptr((int32_t *)rl.arr[2]), rl.n,
+    if (!phases_region<false>(gptr((double *)rl.arr[0]), gptr((double *)rl.arr[1]), gptr((int32_t *)rl.arr[2]), rl.n,
                        rl.step.chunk, (int64_t)rl.step.mask, (int64_t)blockIdx.x * blockDim.x, G * blockDim.x, bar))
         return;
     if (rl.n_glue == 0)
