@@ -3,10 +3,10 @@ winners in the tuning database.
 
     python -m paper_2306_11686_amd.tune_workloads [--db PATH] [--only jacobi3d_512,cg_128]
 
-Every candidate runs the real program (shortened where the launch shape's
-ranking does not depend on the run length: 40 of the 200 3D sweeps, 50 of
-the 500 CG iterations); the batched workload is tuned per instance by the
-batched autotuner (gf_tune_batched). Prints one JSON line per workload with the winner
+Every candidate, and the launch that leaves the shape to the library, runs the
+real program (shortened where the ranking does not depend on the run length:
+40 of the 200 3D sweeps, 50 of the 500 CG iterations); the batched workload is
+tuned per instance by the batched autotuner (gf_tune_batched). Prints one JSON line per workload with the winner
 and the spread of the candidates.
 """
 from __future__ import annotations
@@ -27,13 +27,14 @@ def log(msg):
 def main():
     ap = argparse.ArgumentParser()
     ap.add_argument("--db", default=tuner.DEFAULT_DB)
-    ap.add_argument("--only", default="jacobi3d_512,jacobi2d_256,cg_128,cg_128@per_region,hist_2^28,hist_2^28@per_region,batched_256,batched_256@per_region")
+    ap.add_argument("--only", default="jacobi3d_512,jacobi3d_512@per_region,jacobi2d_256,cg_128,cg_128@per_region,hist_2^28,hist_2^28@per_region,batched_256,batched_256@per_region")
     ap.add_argument("--reps", type=int, default=3)
     args = ap.parse_args()
     import torch
     ctx = Context(0, rpc_capture=True)
     builders = {
         "jacobi3d_512": lambda: workloads.jacobi3d(512, 40),
+        "jacobi3d_512@per_region": lambda: workloads.jacobi3d(512, 40),
         "jacobi2d_256": lambda: workloads.jacobi2d(ctx, 256, 100),
         "cg_128": lambda: workloads.cg(128, 50),
         "cg_128@per_region": lambda: workloads.cg(128, 50),
