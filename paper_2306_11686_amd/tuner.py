@@ -45,6 +45,12 @@ def lookup(key: str, path: str = DEFAULT_DB):
     return dict_to_launch(e) if e else None
 
 
+def record(key: str, launch: Launch, ms: float, mode: int, path: str = DEFAULT_DB) -> None:
+    db = load_db(path)
+    db[key] = {**launch_to_dict(launch), "ms": round(ms, 4), "mode": int(mode)}
+    save_db(db, path)
+
+
 def tune(ctx, program, instances, key: str | None = None, mode: int = GF_EXEC_PERSISTENT, reps: int = 3,
          candidates=None, path: str = DEFAULT_DB):
     """Time the candidates on real runs, record the best under `key`. Without
@@ -59,12 +65,7 @@ def tune(ctx, program, instances, key: str | None = None, mode: int = GF_EXEC_PE
     if best < 0:
         raise RuntimeError("no candidate launch could run")
     if key is not None:
-        db = load_db(path)
-        e = launch_to_dict(cands[best])
-        e["ms"] = round(ms[best], 4)
-        e["mode"] = int(mode)
-        db[key] = e
-        save_db(db, path)
+        record(key, cands[best], ms[best], mode, path)
     return cands[best], [(c, m) for c, m in zip(cands, ms)]
 
 
