@@ -16,10 +16,12 @@
 //
 // Sweep by sweep the 2D stencil is bound by HBM on large grids and batches,
 // and by the barrier, the reduction and the serial steps on small grids.
-// Fused it moves a seventh of the bytes and is bound by FP64 issue (about 20
-// instructions per pair of points and sweep) plus the steps at the ends of
-// the segments. Measured, sweep by sweep and fused: 256 uneven instances, 50
-// sweeps, 28.4 and 7.3 ms; 256^2 with printf, 100 sweeps, 1,246 and 312 us.
+// Fused it moves a fifth of the bytes. Measured, sweep by sweep and fused: 256
+// uneven instances, 50 sweeps, 28.4 and 6.7 ms; 256^2 with printf, 100 sweeps,
+// 1,246 and 290 us. The instances' eight passes move 25.3 GB (20.7 without
+// halos) at 3.8 TB/s with 39 % of the vector units' issue used (1.64e9
+// instructions of four cycles), so neither bounds them: the latency of a
+// march at three wavefronts per SIMD does, and the slowest group.
 //
 // Points of the outer layer are never written by a sweep, so u^s and u^(s-2)
 // agree there, in whichever buffers they are: a stage takes the values of the
@@ -325,10 +327,10 @@ __device__ __forceinline__ void j2f_item(const double *u_, double *w_, int64_t n
 // before are free, one step ahead of their use.
 // 512^3, 100 sweeps: 44.9 ms a sweep at a time; 20.6 with every wavefront
 // computing the rows around its three output rows itself (5 rows of work for
-// one output row and three sweeps); 16.3 so (3.7). About 480 us a pass of
-// three sweeps, 2.4 GB (an eighth of it halos) at 5 TB/s, with the vector
-// units half busy: bound by HBM and by the steps' latency at two wavefronts
-// per SIMD.
+// one output row and three sweeps); 16.3 to 16.7 so (3.7). About 490 us a
+// pass of three sweeps, 2.5 GB (reads 1.41, writes 1.08; an eighth of it
+// halos) at 5 TB/s, with 47 % of the vector units' issue used: bound by HBM and
+// by the steps' latency at two wavefronts per SIMD.
 // Where the two buffers' outer layers agree (the kernel compares them first) a
 // point of the outer layer keeps its value at every stage. Where they differ
 // (DIFF), sweep k + s leaves there what its buffer holds: the lanes that hold

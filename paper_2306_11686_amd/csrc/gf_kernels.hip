@@ -558,11 +558,16 @@ typedef int32_t gf_i4u __attribute__((ext_vector_type(4), aligned(4)));
 // extents a step earlier, and all gathers of x go out together. The lanes at
 // a slice's end load its last four nonzeros again, so that every load is
 // inside the slice and none is conditional.
-// Bound by the unit that makes the gathers' addresses (95 % busy): the 27-point
-// matrix of a 128^3 grid (56 million gathers) took 197 us when a slice's loads followed the previous slice's sum, and takes
-// 159. One nonzero per lane and round took 162 (fewer bank conflicts, more
-// instructions); columns and values through LDS with the gathers by rows
-// took 162 to 168 (fewer cache lines per gather, twice the LDS traffic).
+// Bound by the unit that makes the gathers' addresses (85 to 86 % busy by
+// TA_TA_BUSY over the cycles it was active): the 27-point matrix of a 128^3 grid
+// (56 million gathers) took 197 us when a slice's loads followed the previous
+// slice's sum, and takes 160. One nonzero per lane and round took 162 (fewer
+// bank conflicts, more instructions); columns and values through LDS with the
+// gathers by rows took 162 to 168 (fewer cache lines per gather, twice the LDS
+// traffic). The pipeline costs registers and so a wavefront per SIMD: one
+// launch per loop over rows of one or two nonzeros is 3 to 8 % slower than
+// without it, rows of three and more are faster. Five wavefronts per SIMD spill
+// (0.82 of the speed on the 27-point matrix).
 __device__ __forceinline__ void spmv_region(const int32_t *rowptr_, const int32_t *col_, const double *val_,
                                             const double *x_, double *y_, int64_t n, int64_t worker, int64_t G,
                                             int64_t nitems, int64_t R)
@@ -1444,6 +1449,10 @@ __device__ __forceinline__ void serial_step(const DStep &st, int32_t iter, bool 
 // every workgroup on its own LDS copy of the scalar variables, which stay
 // identical because every workgroup reduces the same partials in the same
 // order; only workgroup 0 performs side effects (records, RPC, write-back).
+// Fused programs are the exception: their scalars live on one workgroup alone,
+// the last worker of the instance, which runs the serial steps of a pass's
+// sweeps with all their side effects (the last worker, because it often has the
+// fewest items).
 // ---------------------------------------------------------------------------
 
 constexpr unsigned kFamHist = (1u << GF_R_HIST) | (1u << GF_R_OWNER);
@@ -2580,8 +2589,10 @@ struct RedVec {
 };
 
 // Up to this many elements one workgroup does the whole reduction: no
-// partials, no arrival counter and no cross-XCD hand-over (5,000 doubles,
-// enqueued back to back: 9.2 us a call against 10.7 us with two workgroups).
+// partials, no arrival counter and no cross-XCD hand-over. 5,000 doubles, call
+// and wait: 17.3 us against 19.1 with two workgroups; calls enqueued back to back
+// are bound by the host and take the same with either (7.7 or 10.3 us, by
+// process).
 constexpr int64_t kReduceOneWg = 8192;
 constexpr int kReduceUnroll = 8;  // 16-byte loads in flight per thread
 
