@@ -1260,7 +1260,7 @@ Tiling choose_tiling(const DProg &p, const gf_launch *l, int mode, const gf_inst
             t.tile_z = l->tile_z;
         if (l->items)
             t.items = l->items;
-        t.xcd_remap = l->xcd_remap;
+        t.xcd_remap = l->xcd_remap != 0;
         if (l->prefetch)
             t.prefetch = l->prefetch;
     }

@@ -106,9 +106,9 @@ struct Tiling {
     int32_t tile_y;
     int32_t tile_z;
     int32_t items;
-    int32_t xcd_remap;
+    int16_t xcd_remap;
+    int16_t lone_x;    // 3D stencil, odd side: factor of the items up to which a thread takes one column
     int32_t prefetch;  // 3D stencil: planes requested ahead of the one computed (1 or 2)
-    int32_t lone_x;    // 3D stencil, odd side: factor of the items up to which a thread takes one column
 };
 
 // One RPC request slot in pinned, coherent host memory (cf. the paper's
