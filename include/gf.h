@@ -238,7 +238,7 @@ typedef struct {
                             0 = default: persistent, up to two per CU (one
                             for small programs with an SpMV) with balanced
                             rounds of work items; per region, one per work
-                            item up to 16 per CU, SpMV up to the region
+                            item up to 16 per CU, SpMV about the region
                             kernel's resident capacity, histogram one per CU */
     int32_t tile_y;      /* 3D stencil: rows per tile (1, 2, 4, 8 or 16); 2D stencil:
                           * rows per segment a workgroup marches through (>= 1) */

@@ -1463,10 +1463,6 @@ int64_t max_items(const DProg &p, const gf_instance &in, const Tiling &t)
     return m;
 }
 
-// Grid of a per-region launch: one workgroup per work item up to 16 per CU;
-// SpMV, which is latency-bound and holds an LDS tile per workgroup, at most
-// one resident round (CG at 128^3: 122 ms per 500 iterations with 1,280
-// workgroups, five per CU, against 133 ms with 4,096 in rounds).
 // Histogram grid: a multiple of the bin-part count, at most kHistRowsMax.
 int hist_grid(int64_t want, uint32_t mask)
 {
@@ -1476,7 +1472,19 @@ int hist_grid(int64_t want, uint32_t mask)
     return (int)std::max<int64_t>(g, parts);
 }
 
-int region_grid(gf_ctx *ctx, const DStep &s, int64_t items, const Tiling &t)
+// Grid of a per-region launch: one workgroup per work item up to 16 per CU;
+// SpMV, whose workgroups pipeline their items, about one resident round: 1,024
+// of 256 threads. With few items past a round or two that left most of the chip
+// idle in the last one; the 27-point SpMV, us, with the resident workgroups
+// and with those of this rule: 53^3 (1,164 items) 17.3 / 13.0, 58^3 (1,525) 18.2 /
+// 15.0, 68^3 (2,457) 25.1 / 22.0; short rows then pay for the later workgroups
+// (196,000 rows of one nonzero 5.9 / 5.7, with glue 8.2 / 8.7). Fewer than a
+// sixteenth past gain nothing (51^3, 1,037 items: 11.9 / 12.2; 131,500 rows of one
+// nonzero 4.5 / 5.2), and past three rounds the later workgroups' items come
+// after the others' (112^3 107 / 115; a workgroup for each of a million rows'
+// 7,813 items: one nonzero a row 15 / 18). publish: every workgroup writes its L2
+// back, so no more of them than are resident.
+int region_grid(gf_ctx *ctx, const DStep &s, int64_t items, const Tiling &t, bool publish)
 {
     if (s.kind == GF_R_OWNER)
         return std::max(1, ctx->num_cu);
@@ -1490,8 +1498,15 @@ int region_grid(gf_ctx *ctx, const DStep &s, int64_t items, const Tiling &t)
         auto it = ctx->region_cap.find(key);
         if (it == ctx->region_cap.end())
             it = ctx->region_cap.emplace(key, region_capacity(s.kind, t, ctx->num_cu)).first;
-        if (it->second > 0)
+        if (it->second > 0) {
             cap = it->second;
+            // 256 threads, four workgroups to a CU by registers: where the last
+            // round would be of few items, some workgroups past the resident
+            // ones, which start as those end
+            const int64_t each = std::max<int64_t>(1, items / cap), past = (items + each - 1) / each - cap;
+            if (t.wg_size == 256 && each <= 2 && 16 * past >= cap && (each + 1) * past <= cap && !publish)
+                cap += past;
+        }
     }
     return (int)std::max<int64_t>(1, std::min<int64_t>(items, cap));
 }
@@ -1507,7 +1522,7 @@ gf_status launch_one(gf_ctx *ctx, const RegionLaunch &cur, const Tiling &t, cons
     const RpcRing rpc = ring_of(ctx);
     int grid = 1;
     if (is_region(cur.step.kind)) {
-        grid = region_grid(ctx, cur.step, cur.n_items, t);
+        grid = region_grid(ctx, cur.step, cur.n_items, t, cur.publish);
         if (l && l->num_wg > 0)
             grid = cur.step.kind == GF_R_HIST ? hist_grid(l->num_wg, cur.step.mask) : l->num_wg;
     }
