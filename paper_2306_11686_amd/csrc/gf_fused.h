@@ -18,7 +18,7 @@
 // and by the barrier, the reduction and the serial steps on small grids.
 // Fused it moves a fifth of the bytes. Measured, sweep by sweep and fused: 256
 // uneven instances, 50 sweeps, 28.4 and 6.7 ms; 256^2 with printf, 100 sweeps,
-// 1,246 and 290 us. The instances' eight passes move 25.3 GB (20.7 without
+// 1,246 and 290 us. The instances' eight passes move 25.4 GB (20.7 without
 // halos) at 3.8 TB/s with 39 % of the vector units' issue used (1.64e9
 // instructions of four cycles), so neither bounds them: the latency of a
 // march at three wavefronts per SIMD does, and the slowest group.

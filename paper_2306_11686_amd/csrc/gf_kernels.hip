@@ -39,10 +39,14 @@ __host__ __device__ inline StencilGeom j3_geom(int64_t n, const Tiling &t)
     const int64_t interior = n > 2 ? n - 2 : 0;
     g.nyt = cdiv(interior, t.tile_y);
     g.nzs = cdiv(interior, t.tile_z);
-    g.nxc = cdiv(n, t.wg_size);
-    g.single = (n & 1) && g.nxc * g.nyt * g.nzs <= (n < 128 ? 512 : t.lone_x * (n < 192 ? 512 : (n < 300 ? 256 : 0)));
-    if (!g.single)
-        g.nxc = cdiv(n, 2 * (int64_t)t.wg_size);
+    g.nxc = cdiv(n, 2 * (int64_t)t.wg_size);
+    g.single = false;
+    if (n & 1) {
+        const int64_t lone = cdiv(n, t.wg_size);
+        g.single = lone * g.nyt * g.nzs <= (n < 128 ? 512 : t.lone_x * (n < 192 ? 512 : (n < 300 ? 256 : 0)));
+        if (g.single)
+            g.nxc = lone;
+    }
     return g;
 }
 
