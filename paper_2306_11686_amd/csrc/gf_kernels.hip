@@ -1022,23 +1022,17 @@ __host__ __device__ inline int hist_slices(int64_t nbins, int64_t part_rows)
 // Bins of a workgroup's tile.
 __host__ __device__ inline int hist_tile(int threads, int slices) { return threads / slices * 8; }
 
-__device__ __forceinline__ void hist_merge(uint32_t *bins_, const uint32_t *rows_, uint32_t mask, int64_t rows_used,
-                                           int64_t block, int64_t nblocks)
+template <int kSlices>
+__device__ __forceinline__ void hist_merge_tiles(GF_GLOBAL uint32_t *bins, GF_GLOBAL const uint16_t *rows, int64_t nbins,
+                                                 int lparts, int64_t per_part, uint32_t *s_sum, int64_t block,
+                                                 int64_t nblocks)
 {
-    __shared__ uint32_t s_sum[2 * kMaxWgHist];  // four slices or more
     typedef uint16_t gf_h8 __attribute__((ext_vector_type(8)));
-    GF_GLOBAL uint32_t *bins = gptr(bins_);
-    GF_GLOBAL const uint16_t *rows = (GF_GLOBAL const uint16_t *)gptr(rows_);
-    const int64_t nbins = (int64_t)mask + 1;
-    const int lbins = __builtin_popcount(mask);
-    const int lparts = lbins > 16 ? lbins - 16 : 0;
-    const int64_t per_part = rows_used >> lparts;  // rows of each part
-    const int slices = hist_slices(nbins, per_part);
-    const int octs = blockDim.x / slices;
+    const int octs = blockDim.x / kSlices;
     const int o = threadIdx.x % octs, sl = threadIdx.x / octs;
-    const int span = hist_tile(blockDim.x, slices);
+    const int span = hist_tile(blockDim.x, kSlices);
     for (int64_t first = block * span; first < nbins; first += nblocks * span) {
-        if (slices > 1) {
+        if (kSlices > 1) {
             for (int i = threadIdx.x; i < span; i += blockDim.x)
                 s_sum[i] = 0u;
             __syncthreads();
@@ -1048,7 +1042,7 @@ __device__ __forceinline__ void hist_merge(uint32_t *bins_, const uint32_t *rows
             GF_GLOBAL const uint16_t *p = rows + (b0 / kHistPart) * kHistPart + b0 % kHistPart;
             uint32_t sum[8] = {};
 #pragma unroll 8
-            for (int64_t j = sl; j < per_part; j += slices) {
+            for (int64_t j = sl; j < per_part; j += kSlices) {
                 const gf_h8 r = *(GF_GLOBAL const gf_h8 *)(p + (j << lparts) * kHistPart);
 #pragma unroll
                 for (int q = 0; q < 8; ++q)
@@ -1058,14 +1052,14 @@ __device__ __forceinline__ void hist_merge(uint32_t *bins_, const uint32_t *rows
             for (int q = 0; q < 8; ++q) {
                 if (!sum[q])
                     continue;
-                if (slices > 1)
+                if (kSlices > 1)
                     __hip_atomic_fetch_add(&s_sum[q * octs + o], sum[q], __ATOMIC_RELAXED,
                                            __HIP_MEMORY_SCOPE_WORKGROUP);
                 else if (b0 + q < nbins)
                     __hip_atomic_fetch_add(&bins[b0 + q], sum[q], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
             }
         }
-        if (slices == 1)
+        if (kSlices == 1)
             continue;
         __syncthreads();
         for (int i = threadIdx.x; i < span && first + i < nbins; i += blockDim.x) {
@@ -1075,6 +1069,25 @@ __device__ __forceinline__ void hist_merge(uint32_t *bins_, const uint32_t *rows
         }
         __syncthreads();
     }
+}
+
+__device__ __forceinline__ void hist_merge(uint32_t *bins_, const uint32_t *rows_, uint32_t mask, int64_t rows_used,
+                                           int64_t block, int64_t nblocks)
+{
+    __shared__ uint32_t s_sum[2 * kMaxWgHist];  // four slices or more
+    GF_GLOBAL uint32_t *bins = gptr(bins_);
+    GF_GLOBAL const uint16_t *rows = (GF_GLOBAL const uint16_t *)gptr(rows_);
+    const int64_t nbins = (int64_t)mask + 1;
+    const int lbins = __builtin_popcount(mask);
+    const int lparts = lbins > 16 ? lbins - 16 : 0;
+    const int64_t per_part = rows_used >> lparts;  // rows of each part
+    const int slices = hist_slices(nbins, per_part);
+    if (slices == 32)
+        hist_merge_tiles<32>(bins, rows, nbins, lparts, per_part, s_sum, block, nblocks);
+    else if (slices == 4)
+        hist_merge_tiles<4>(bins, rows, nbins, lparts, per_part, s_sum, block, nblocks);
+    else
+        hist_merge_tiles<1>(bins, rows, nbins, lparts, per_part, s_sum, block, nblocks);
 }
 
 // GF_R_OWNER: the static schedule executed literally over all T threads.
