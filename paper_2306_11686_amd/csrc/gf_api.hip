@@ -1133,7 +1133,11 @@ bool one_column(int64_t n) { return (n & 1) && n <= 256; }
 //   the persistent kernel, whose barrier costs more with more workgroups (us
 //   per sweep, n / 128 against n / 64: 700 24.5 and 21.6, 1,000 28.8 and 23.6,
 //   2,048 40.9 and 37.9), with 16 at most from side 6,000 (16,384: 910 with 32,
-//   864 with 16);
+//   864 with 16). Launches per sweep: 16 from side 1,600 (1,550 19.0 with 8 and
+//   19.1 with 16, 1,700 21.4 and 20.5, 1,951 23.4 and 22.2), and 16, not 32, where
+//   32 give somewhat more workgroups than the five of a CU (4,500 72.9 with 32
+//   and 73.1 with 16, 4,700 87.4 and 81.5, 5,500 109.9 and 104.8, 5,700 120 and
+//   128);
 // - 3D: 2 rows per tile and z split into the segments that give 3,840
 //   wavefronts (a segment reads two planes more than it writes: no shorter
 //   than 8 planes, 4 below side 96); from side 416, where the rows fill
@@ -1176,6 +1180,9 @@ void follow_side(Tiling &t, int64_t n, bool is3, int mode, int64_t G)
         t.tile_y = 2;
         for (int64_t r = persistent ? 256 : 512; r <= n && t.tile_y < (persistent && n >= 6000 ? 16 : 32); r *= 2)
             t.tile_y *= 2;
+        const int64_t wgs = cols * split(in, t.tile_y);
+        if (!persistent && ((t.tile_y == 8 && n >= 1600) || (t.tile_y == 32 && wgs > 1280 && wgs < 2048)))
+            t.tile_y = 16;
         return;
     }
     const bool tall = n >= 416 && (persistent || n % 64 != 0);

@@ -163,3 +163,16 @@ def test_instances_of_a_per_region_run_follow_their_own_side():
             assert ctx.run(prog, [a, b], mode=mode)["num_wg"] == max(alone)
             assert ctx.run(prog, [a, a], mode=mode)["num_wg"] == alone[0]
         ctx.sync()
+
+
+# rows per segment in launches per sweep, and the workgroups (512 columns each) that they give
+@pytest.mark.parametrize("n,rows,columns", [(1599, 8, 4), (1600, 16, 4), (4500, 32, 9), (4608, 16, 9), (5631, 16, 11),
+                                            (5700, 32, 12)])
+def test_default_rows_of_2d_launches_per_sweep(gfx, oracle_lib, n, rows, columns):
+    import paper_2306_11686_amd as gf
+    from tests.gpu_helpers import run_jacobi2d
+    u0 = gi.grid2d(n, seed=81)
+    g, r, st = run_jacobi2d(gfx, u0, 2, gf.GF_EXEC_PER_REGION, launch=gf.Launch.make())
+    assert st["num_wg"] == columns * -(-(n - 2) // rows)
+    g_ref, _, r_comp, _ = oracle_lib.jacobi2d(u0, 2)
+    assert np.array_equal(g, g_ref) and np.all(np.abs(r - r_comp) <= 1e-12 * r_comp)
